@@ -720,11 +720,11 @@ static gws_status run_prep(gws_ctx *ctx, const Consts &k, const GView &g, const 
     return GWS_OK;
 }
 
-static int acc_grid(gws_ctx *ctx, int C, int F)
+static int acc_grid(gws_ctx *ctx, const Consts &k, int F)
 {
-    const int key = C * 16 + F;
+    const int key = (accumulate_on_mfma(k, F) ? 128 : 0) + k.C * 16 + F;
     auto it = ctx->acc_occ.find(key);
-    if (it == ctx->acc_occ.end()) it = ctx->acc_occ.emplace(key, accumulate_occupancy(C, F)).first;
+    if (it == ctx->acc_occ.end()) it = ctx->acc_occ.emplace(key, accumulate_occupancy(k, F)).first;
     return ctx->n_cu * it->second;
 }
 
@@ -831,7 +831,7 @@ static gws_status forward_run(gws_ctx *ctx, const gws_problem *prob, int S, cons
     }
     {
         StageScope sc(ctx, s, ST_ACCUM, !noalloc);
-        HIP_CHECK(ctx, launch_accumulate(*p, k, dtab, prefix, S, queue, acc_grid(ctx, k.C, F), s));
+        HIP_CHECK(ctx, launch_accumulate(*p, k, dtab, prefix, S, queue, acc_grid(ctx, k, F), s));
     }
     {
         StageScope sc(ctx, s, ST_REDUCE, !noalloc);
@@ -1333,7 +1333,7 @@ static gws_status prepare_plans(gws_ctx *ctx, const gws_problem *prob, int S, co
         const gws_status st = get_plan(ctx, prob->nx, prob->ny, d == 0 ? kTileCfg[cfg - 1][0] : ADJ_F, &p, mrx, mry);
         if (st != GWS_OK) return st;
         if (prob->xform == GWS_XFORM_DFT_BF16X3) HIP_CHECK(ctx, build_dft_mats(*p));
-        (void)acc_grid(ctx, prob->n_lambda, kTileCfg[cfg - 1][0]);
+        (void)acc_grid(ctx, make_consts(prob, 1), kTileCfg[cfg - 1][0]);
     }
     return GWS_OK;
 }

@@ -456,7 +456,14 @@ hipError_t launch_grad_final(const GView &g, const Consts &k, const uint32_t *va
 hipError_t launch_sum_counters(long long *const *src, int n, long long *dst, hipStream_t s);
 int adjoint_occupancy(int C, int depth);
 hipError_t launch_synth(GView g, float *base, int64_t n, uint64_t seed, const Consts &k, hipStream_t s);
-int accumulate_occupancy(int C, int F);
+// Whether the accumulation runs on the matrix cores (k_accum_mfma.hip) or term by term.
+constexpr int ACC_MFMA_POINTS = 700000;
+bool accumulate_on_mfma(const Consts &k, int F);
+bool grid_has_evanescent(const Consts &k);
+hipError_t launch_accumulate_mfma(const Plan &p, const Consts &k, const FwdScene *scenes, const int32_t *prefix,
+                                  int n_scenes, long long *queue, int grid, hipStream_t s);
+int accumulate_mfma_occupancy(int C);
+int accumulate_occupancy(const Consts &k, int F);
 hipError_t launch_zero_counters(long long *counters, uint32_t *bucket_hist, hipStream_t s);
 hipError_t launch_copy_counters(const long long *src, long long *dst, hipStream_t s);
 int fft_col_batch(int n);

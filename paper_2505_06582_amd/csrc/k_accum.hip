@@ -314,21 +314,33 @@ __global__ void __launch_bounds__(WG) k_reduce_partials(Consts k, const int32_t 
     }
 }
 
-static bool tile_needs_evanescent(const Plan &p, const Consts &k)
+bool grid_has_evanescent(const Consts &k)
 {
     // is any grid frequency at or beyond 1/lambda for some channel?
-    const double nux = (p.nx / 2) / (p.nx * k.px), nuy = (p.ny / 2) / (p.ny * k.py);
+    const double nux = (k.nx / 2) / (k.nx * k.px), nuy = (k.ny / 2) / (k.ny * k.py);
     const double nu2 = nux * nux + nuy * nuy;
     for (int c = 0; c < k.C; ++c)
         if (!(nu2 < k.inv_lambda[c] * k.inv_lambda[c])) return true;
     return false;
 }
 
+// Which accumulation runs.  The matrix-core one is laid out for 16-row sub-tiles (F = 4) and needs
+// every grid frequency to propagate.  The cross term's exponent grows as 1 / (nx ny) for a given
+// Gaussian, so on small grids most entries are evaluated term by term anyway, at three
+// wavefronts per SIMD instead of four.  Forward, this kernel against the matrix-core one, 500 /
+// 5000 / 50000 Gaussians of 2-20 pixels at three wavelengths (ms): 640 x 480 0.171 / 0.336 / 1.30
+// against 0.185 / 0.350 / 1.24, 1000 x 750 0.224 / 0.424 / 2.08 against 0.216 / 0.394 / 1.45,
+// 1920 x 1080 0.339 / 0.820 / 4.53 against 0.315 / 0.551 / 2.75.
+bool accumulate_on_mfma(const Consts &k, int F)
+{
+    return F == 4 && !grid_has_evanescent(k) && (int64_t)k.nx * k.ny >= (int64_t)ACC_MFMA_POINTS;
+}
+
 template <int C, int F>
 static hipError_t launch_acc_cf(const Plan &p, const Consts &k, const FwdScene *scenes, const int32_t *prefix,
                                 int n_scenes, long long *queue, int grid, hipStream_t s)
 {
-    if (tile_needs_evanescent(p, k))
+    if (grid_has_evanescent(k))
         hipLaunchKernelGGL((k_accumulate<C, true, F>), dim3(grid), dim3(WG), 0, s, k, p.tile_xy, scenes, prefix, n_scenes,
                            queue);
     else
@@ -351,6 +363,7 @@ static hipError_t launch_acc_c(const Plan &p, const Consts &k, const FwdScene *s
 hipError_t launch_accumulate(const Plan &p, const Consts &k, const FwdScene *scenes, const int32_t *prefix, int n_scenes,
                              long long *queue, int grid, hipStream_t s)
 {
+    if (accumulate_on_mfma(k, p.F)) return launch_accumulate_mfma(p, k, scenes, prefix, n_scenes, queue, grid, s);
     switch (k.C) {
     case 1: return launch_acc_c<1>(p, k, scenes, prefix, n_scenes, queue, grid, s);
     case 2: return launch_acc_c<2>(p, k, scenes, prefix, n_scenes, queue, grid, s);
@@ -393,8 +406,10 @@ static const void *acc_kernel_ptr(int F)
     }
 }
 
-int accumulate_occupancy(int C, int F)
+int accumulate_occupancy(const Consts &k, int F)
 {
+    if (accumulate_on_mfma(k, F)) return accumulate_mfma_occupancy(k.C);
+    const int C = k.C;
     int nb = 0;
     const void *kp = nullptr;
     switch (C) {

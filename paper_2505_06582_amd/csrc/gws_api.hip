@@ -382,7 +382,8 @@ static Layout make_layout(const gws_problem *p, int64_t n, int f_fwd, int f_bwd,
     L.off_vals_a = take(sizeof(uint32_t) * n);
     L.off_vals_b = take(sizeof(uint32_t) * n);
     L.off_sort_hist = take(sizeof(uint32_t) * 256 * L.sort_blocks);
-    L.off_records = take(sizeof(GRec) * n);
+    // the records, and behind them the matrix-core adjoint's coefficients
+    L.off_records = take((sizeof(GRec) + (!fwd_only && adjoint_on_mfma(make_consts(p, 0)) ? sizeof(float4) : 0)) * n);
     L.off_tile_L = take(sizeof(int32_t) * ntiles);
     L.off_tile_slots = take(sizeof(int2) * ntiles);
     L.off_items = take(sizeof(Item) * (L.max_slots_bound(part_bytes, C, ntiles)));
@@ -393,7 +394,10 @@ static Layout make_layout(const gws_problem *p, int64_t n, int f_fwd, int f_bwd,
     L.off_chunk_items = take(bw * sizeof(int2) * (nchunks + 1));
     L.off_range_base = take(bw * sizeof(int32_t) * (ntiles + 2));
     L.off_bpartials = take(bw * sizeof(float) * (size_t)L.max_bslots *
-                           std::max(adj_wg(C, true) * adj_nv(C, true), adj_wg(C, false) * adj_nv(C, false)));
+                           std::max(adjoint_on_mfma(make_consts(p, 0))
+                                        ? ADJ_MFMA_G * std::max(adj_nv(C, C < 4), adj_nv(C, false))
+                                        : 0,
+                                    std::max(adj_wg(C, true) * adj_nv(C, true), adj_wg(C, false) * adj_nv(C, false))));
     L.total = o;
     return L;
 }
@@ -403,7 +407,7 @@ static Layout make_layout(const gws_problem *p, int64_t n, int f_fwd, int f_bwd,
 struct BatchLayout {
     size_t total = 0;
     size_t off_ctrl = 0, off_ftab = 0, off_btab = 0, off_prefix = 0, off_spectra = 0, off_gspecs = 0, off_gpack = 0,
-           off_dpack = 0, off_d0 = 0, off_dftws = 0;
+           off_gexp = 0, off_dpack = 0, off_d0 = 0, off_dftws = 0;
     AdjGeom geo = {};
     int64_t pack_elems = 0;  // packed per-frequency elements of one scene (regions x blocks x C x 64)
     std::vector<size_t> scene_off;
@@ -432,8 +436,12 @@ static BatchLayout make_batch_layout(const gws_problem *p, int S, const int64_t 
     const size_t bw = fwd_only ? 0 : 1;
     B.off_gspecs = take(bw * sizeof(float2) * (size_t)S * C * M);
     B.off_gpack = take(bw * sizeof(float2) * (size_t)S * B.pack_elems);
-    B.off_dpack = take(bw * sizeof(float) * (size_t)B.pack_elems);
-    B.off_d0 = take(bw * sizeof(double) * (size_t)B.geo.nreg * 2 * C);
+    // the matrix-core adjoint's exponents and geometry table, or the term-by-term one's propagation
+    // tables
+    const bool mm = adjoint_on_mfma(make_consts(p, 0));
+    B.off_gexp = take(bw * mm * sizeof(int32_t) * (size_t)S * B.geo.nreg * 4);
+    B.off_dpack = take(bw * sizeof(float) * (mm ? (size_t)B.geo.nreg * 4 * adj_sub_table_floats(C) : (size_t)B.pack_elems));
+    B.off_d0 = take(bw * !mm * sizeof(double) * (size_t)B.geo.nreg * 2 * C);
     // the split-bf16 DFT's operand planes (both directions), when that transform is chosen
     B.off_dftws = take(p->xform == GWS_XFORM_DFT_BF16X3 ? dft_bf16x3_workspace(p->nx, p->ny, S * C) : 0);
     for (int i = 0; i < S; ++i) {
@@ -716,7 +724,8 @@ static gws_status run_prep(gws_ctx *ctx, const Consts &k, const GView &g, const 
     HIP_CHECK(ctx, launch_keys(g, k, B.keys_a, B.vals_a, B.bucket_hist, B.counters, s));
     HIP_CHECK(ctx, radix_sort_48(B.keys_a, B.vals_a, B.keys_b, B.vals_b, B.sort_hist, g.n, L.sort_blocks, s, keys_sorted,
                                  vals_sorted));
-    HIP_CHECK(ctx, launch_records(g, k, *keys_sorted, *vals_sorted, B.rec, g.n, B.counters, s));
+    HIP_CHECK(ctx, launch_records(g, k, *keys_sorted, *vals_sorted, B.rec, g.n, B.counters,
+                                  !k.forward && adjoint_on_mfma(k), s));
     return GWS_OK;
 }
 
@@ -728,11 +737,11 @@ static int acc_grid(gws_ctx *ctx, const Consts &k, int F)
     return ctx->n_cu * it->second;
 }
 
-static int adj_grid(gws_ctx *ctx, int C, int depth)
+static int adj_grid(gws_ctx *ctx, const Consts &k)
 {
-    const int key = 256 + C * 2 + (depth ? 1 : 0);
+    const int key = 256 + (adjoint_on_mfma(k) ? 128 : 0) + k.C * 2 + (k.depth_grad ? 1 : 0);
     auto it = ctx->acc_occ.find(key);
-    if (it == ctx->acc_occ.end()) it = ctx->acc_occ.emplace(key, adjoint_occupancy(C, depth)).first;
+    if (it == ctx->acc_occ.end()) it = ctx->acc_occ.emplace(key, adjoint_occupancy(k)).first;
     return ctx->n_cu * it->second;
 }
 
@@ -872,6 +881,7 @@ static gws_status backward_run(gws_ctx *ctx, const gws_problem *prob, int S, con
     k.depth_grad = grads->depth != nullptr;
     float2 *gspecs = (float2 *)(base + BL.off_gspecs);
     float2 *gpack = (float2 *)(base + BL.off_gpack);
+    int32_t *gexp = (int32_t *)(base + BL.off_gexp);
     float *dpack = (float *)(base + BL.off_dpack);
     double *d0 = (double *)(base + BL.off_d0);
     BwdTab tab;
@@ -889,8 +899,9 @@ static gws_status backward_run(gws_ctx *ctx, const gws_problem *prob, int S, con
             st = run_prep(ctx, k, scene_view(g, offsets[i], BL.n[i]), L, B, s, &keys, &vals);
             if (st != GWS_OK) return st;
             HIP_CHECK(ctx, launch_bin_backward(*p, keys, B.bitems, B.chunk_items, B.range_base, p->ntiles + 1,
-                                               L.max_bitems, B.counters, BL.n[i], adj_wg(k.C, k.depth_grad != 0), s));
-            tab.s[i] = BwdScene{B.rec, gpack + (int64_t)i * BL.pack_elems, B.bitems, B.bpartials, B.counters, BL.n[i]};
+                                               L.max_bitems, B.counters, BL.n[i], adjoint_chunk(k), s));
+            tab.s[i] = BwdScene{B.rec,    gpack + (int64_t)i * BL.pack_elems, gexp + (int64_t)i * BL.geo.nreg * 4,
+                                B.bitems, B.bpartials, B.counters, BL.n[i]};
             ctrs[i] = B.counters;
             vals_sorted[i] = vals;
         }
@@ -906,7 +917,10 @@ static gws_status backward_run(gws_ctx *ctx, const gws_problem *prob, int S, con
     }
     {
         StageScope sc(ctx, s, ST_DTABLE);
-        HIP_CHECK(ctx, launch_adj_pack(k, BL.geo, S, gspecs, gpack, dpack, d0, s));
+        if (adjoint_on_mfma(k))
+            HIP_CHECK(ctx, launch_adj_pack_sub(k, BL.geo, S, gspecs, gpack, gexp, dpack, s));
+        else
+            HIP_CHECK(ctx, launch_adj_pack(k, BL.geo, S, gspecs, gpack, dpack, d0, s));
     }
     BwdScene *dscenes = (BwdScene *)(base + BL.off_btab);
     int32_t *prefix = (int32_t *)(base + BL.off_prefix);
@@ -915,7 +929,7 @@ static gws_status backward_run(gws_ctx *ctx, const gws_problem *prob, int S, con
         StageScope sc(ctx, s, ST_ADJOINT);
         HIP_CHECK(ctx, launch_bwd_table(tab, dscenes, prefix, queue, s));
         HIP_CHECK(ctx, launch_adjoint(*p, k, dscenes, prefix, S, queue, dpack, d0, BL.geo,
-                                      adj_grid(ctx, k.C, k.depth_grad), s));
+                                      adj_grid(ctx, k), s));
     }
     {
         StageScope sc(ctx, s, ST_FINAL);
@@ -924,7 +938,7 @@ static gws_status backward_run(gws_ctx *ctx, const gws_problem *prob, int S, con
             const Bufs B = carve(L, base + BL.scene_off[i]);
             HIP_CHECK(ctx, launch_grad_final(scene_view(g, offsets[i], BL.n[i]), k, vals_sorted[i], B.chunk_items,
                                              B.range_base, B.bpartials, grad_view(grads, offsets[i], g->n), BL.n[i],
-                                             B.counters, adj_wg(k.C, k.depth_grad != 0), s));
+                                             B.counters, adjoint_chunk(k), s));
         }
     }
     HIP_CHECK(ctx, launch_sum_counters(ctrs.data(), S, ctx->d_stats, s));

@@ -63,6 +63,8 @@ __host__ __device__ constexpr int adj_waves_per_simd(int c, bool depth)
 {
     return (adj_lds_bytes(c, depth, adj_waves(c, depth)) <= 78 * 1024 ? 2 : 1) * adj_waves(c, depth) / 4;
 }
+// Gaussians per work-group of the matrix-core adjoint (k_adjoint_mfma.hip).
+constexpr int ADJ_MFMA_G = 512;
 // Region indexing of the packed per-frequency tables: region r = 2 ((ty - ty_min) ntx +
 // (tx - tx_min)) + half over the F = 8 tile grid.
 struct AdjGeom {
@@ -217,6 +219,57 @@ static __device__ __forceinline__ void reduce_transposed(float (&x)[V], float &y
     }
 }
 
+// Reduce NV per-lane values over the wavefront and add the totals to acc[0..NV) (LDS).
+// Up to 8 values (+ 1 carried along), 16, or 24 (16 + 8) use the transposed butterfly.
+template <int NV>
+static __device__ __forceinline__ void reduce_into(float (&x)[NV], float *acc, int lane)
+{
+    if constexpr (NV <= 9) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = i < NV ? x[i] : 0.0f;
+        float y = NV == 9 ? x[NV - 1] : 0.0f;
+        if constexpr (NV == 9) {
+            reduce_transposed<8, true>(v, y, lane);
+            if (lane == 4) atomicAdd(&acc[8], y);
+        } else {
+            reduce_transposed<8, false>(v, y, lane);
+        }
+        if ((lane & 7) == 0) {
+            const int v0 = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
+            if (v0 < NV && (NV != 9 || v0 < 8)) atomicAdd(&acc[v0], v[0]);  // ds_add_f32, no return
+        }
+    } else if constexpr (NV <= 16) {
+        float v[16];
+        float y = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = i < NV ? x[i] : 0.0f;
+        reduce_transposed<16, false>(v, y, lane);
+        if ((lane & 7) == 0) {
+            const int v0 = 2 * (((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1));
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                if (v0 + j < NV) atomicAdd(&acc[v0 + j], v[j]);
+        }
+    } else {
+        static_assert(NV <= 24, "at most 24 reduced values");
+        float v[16], w[8];
+        float y = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = x[i];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w[i] = 16 + i < NV ? x[16 + i] : 0.0f;
+        reduce_transposed<16, false>(v, y, lane);
+        reduce_transposed<8, false>(w, y, lane);
+        if ((lane & 7) == 0) {
+            const int g = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) atomicAdd(&acc[2 * g + j], v[j]);
+            if (16 + g < NV) atomicAdd(&acc[16 + g], w[0]);
+        }
+    }
+}
+
 __device__ __forceinline__ long long wave_sum_i64(long long v)
 {
 #pragma unroll
@@ -233,6 +286,13 @@ struct alignas(16) GRec {
     float amp[4];                   // a_c o 2 pi sqrt(det) / (px py nx ny)
 };
 static_assert(sizeof(GRec) == 64, "record must stay 64 B");
+
+// Coefficients of the matrix-core adjoint's polynomial of each Gaussian's cross term (c1 / c0,
+// c2 / c0, c3 / c0, c0), kept behind the n records.
+__host__ __device__ inline float4 *adj_poly(const GRec *rec, int64_t n)
+{
+    return reinterpret_cast<float4 *>(const_cast<GRec *>(rec) + n);
+}
 
 // Tilted-Gaussian record (input order), 96 bytes, written by k_tilt_records: the exp2-units
 // linear forms u = U . (m_x, m_y, k_z), v = V . (...) and k_oz = N . (...) (m in index units,
@@ -304,7 +364,9 @@ struct FwdScene {
 // Per-scene pointers of the adjoint.
 struct BwdScene {
     const GRec *rec;
-    const float2 *gpack;  // (|Gs_c|, arg Gs_c / 2 pi) region-major: [region][block][c][lane]
+    const float2 *gpack;  // Gs_c, polar and region-major [region][block][c][lane] (k_adjoint) or
+                          // sub-tile-major [sub-tile][c][row][column] (k_adjoint_mfma)
+    const int32_t *gexp;  // per sub-tile: largest binary exponent of Gs (k_adjoint_mfma)
     const BItem *bitems;
     float *bpartials;
     long long *counters;
@@ -399,7 +461,7 @@ hipError_t radix_sort_48(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, u
                          uint64_t **keys_out, uint32_t **vals_out);
 hipError_t launch_records(const GView &g, const Consts &k, const uint64_t *keys,
                           const uint32_t *vals, GRec *rec, int64_t n, const long long *counters,
-                          hipStream_t s);
+                          bool poly, hipStream_t s);
 hipError_t launch_bin_forward(const Plan &p, const uint32_t *bucket_hist, uint32_t *cum, int32_t *tile_L,
                               int2 *tile_slots, Item *items, int64_t max_items, int64_t max_slots, int base_chunk,
                               long long *counters, hipStream_t s);
@@ -454,7 +516,18 @@ hipError_t launch_grad_final(const GView &g, const Consts &k, const uint32_t *va
                              const int32_t *range_base, const float *bpartials, const GradView &grads, int64_t n,
                              const long long *counters, int chunk, hipStream_t s);
 hipError_t launch_sum_counters(long long *const *src, int n, long long *dst, hipStream_t s);
-int adjoint_occupancy(int C, int depth);
+int adjoint_occupancy(const Consts &k);
+// Whether the adjoint runs on the matrix cores (k_adjoint_mfma.hip) or term by term, and the
+// Gaussians per work-group (the binning's chunk) of the one that runs.
+constexpr int ADJ_MFMA_POINTS = 1000000;
+bool adjoint_on_mfma(const Consts &k);
+inline int adjoint_chunk(const Consts &k) { return adjoint_on_mfma(k) ? ADJ_MFMA_G : adj_wg(k.C, k.depth_grad != 0); }
+hipError_t launch_adj_pack_sub(const Consts &k, const AdjGeom &geo, int n_scenes, const float2 *gspecs, float2 *gsub,
+                               int32_t *gexp, float *table, hipStream_t s);
+int adj_sub_table_floats(int C);  // words per sub-tile of its geometry table
+hipError_t launch_adjoint_mfma(const Plan &p, const Consts &k, const BwdScene *scenes, const int32_t *prefix, int n_scenes,
+                               long long *queue, const float *sgeo, const AdjGeom &geo, int grid, hipStream_t s);
+int adjoint_mfma_occupancy(int C, int depth);
 hipError_t launch_synth(GView g, float *base, int64_t n, uint64_t seed, const Consts &k, hipStream_t s);
 // Whether the accumulation runs on the matrix cores (k_accum_mfma.hip) or term by term.
 constexpr int ACC_MFMA_POINTS = 700000;

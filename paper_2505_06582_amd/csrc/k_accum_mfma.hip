@@ -42,87 +42,22 @@
 // (Gaussian, sub-tile) at three wavelengths, a fifth of them staging, against 146 term by
 // term.  Forward of 1e5 Gaussians at 1080 x 1920 x 3: 8.6 -> 4.6 ms; 1e6 at 2160 x 3840 x 3: 304 ->
 // 123 ms.  Three wavefronts per SIMD without spills: with accumulators for t^2 too, 4.9 ms.
-#include "gws_internal.h"
+#include "mfma_f16.h"
 
 namespace gws {
-
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-typedef float float4_t __attribute__((ext_vector_type(4)));
-typedef float float2_t __attribute__((ext_vector_type(2)));
 
 constexpr int MF = 4;                    // 4-row blocks (and result registers) of a sub-tile
 constexpr int MM_CAND = 1024;            // candidates tested per round
 constexpr int MM_SLOTS = 96;             // a wavefront's list: up to 15 entries kept, 64 new, padding to 16
-constexpr float MM_P = 56.25f;           // 7.5^2: t = u v / MM_P spans [-1, 1]
-// classes of |a|: 3, 4 and 5 coefficients, 5 with c2 carried to both fp16 parts (class 6), 6 (class 7)
-constexpr float MM_A3 = 0.0175f, MM_A4 = 0.08f, MM_A5 = 0.12f, MM_A6 = 0.2f, MM_A7 = 0.35f;
 constexpr int MM_XS = 4, MM_YS = 5;      // powers of two carried by X and Y (kept inside fp16's normal range)
 constexpr int MM_E_NONE = -100000;
 constexpr int MM_EMIT = 32;              // passes after which the accumulators move to the output
-
-static __device__ __forceinline__ double frac_m(double v) { return v - floor(v); }
-
-// D_c(nu) = k_z - 1/lambda without cancellation (the grid has no evanescent frequency).
-static __device__ __forceinline__ double dprop_m(double nu2, double il) { return -nu2 / (il + sqrt(il * il - nu2)); }
 
 // An entry of a wavefront's list, 12 + 4 C floats.  Separable: lx, alpha, ly, gamma | r_x's upper
 // 20 bits and the rest, r_y's | c1, 8 c2 / P, 8 c3 / c2 / P, 8 c4 / c3 / P | per wavelength base, A,
 // c1 imaginary, z.  Term by term: alpha, beta2, gamma, z | rxf, ryf, rows, - |
 // -- | per wavelength base, amp, -, -.
 __host__ __device__ constexpr int mm_floats(int c) { return 12 + 4 * c; }
-
-static __device__ __forceinline__ half2_t to_half2(float a, float b)
-{
-    return __builtin_convertvector((float2_t){a, b}, half2_t);
-}
-static __device__ __forceinline__ uint32_t bits(half2_t h) { return __builtin_bit_cast(uint32_t, h); }
-// x - h for a pair: the part the second fp16 number carries (exact in FP32).  The -1 is opaque
-// to the optimiser so that each is one v_fma_mix_f32 instead of a conversion and a subtraction.
-static __device__ __forceinline__ float2_t rest(float re, float im, half2_t h)
-{
-    float m1 = -1.0f;
-    asm("" : "+s"(m1));
-    return (float2_t){fmaf((float)h.x, m1, re), fmaf((float)h.y, m1, im)};
-}
-static __device__ __forceinline__ uint32_t half_pair(float a, float b) { return bits(to_half2(a, b)); }
-struct Frag {
-    uint32_t r[4];
-};
-// The A operands of both parts of a complex product in six registers: (-Yi, Yr, Yi), two
-// Gaussians to a register; the real part reads (Yr, Yi), the imaginary part (-Yi, Yr).
-struct Frag6 {
-    uint32_t r[6];
-    __device__ __forceinline__ Frag re() const { return Frag{{r[2], r[3], r[4], r[5]}}; }
-    __device__ __forceinline__ Frag im() const { return Frag{{r[0], r[1], r[2], r[3]}}; }
-};
-// Four complex factors as fp16 high and low parts, (r01, r23, i01, i23).
-static __device__ __forceinline__ void split4(const float (&re)[4], const float (&im)[4], uint32_t *h, uint32_t *l)
-{
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const half2_t hr = to_half2(re[2 * i], re[2 * i + 1]), hi = to_half2(im[2 * i], im[2 * i + 1]);
-        const float2_t lr = rest(re[2 * i], re[2 * i + 1], hr), li = rest(im[2 * i], im[2 * i + 1], hi);
-        h[i] = bits(hr);
-        h[i + 2] = bits(hi);
-        l[i] = half_pair(lr.x, lr.y);
-        l[i + 2] = half_pair(li.x, li.y);
-    }
-}
-// Half x (0: low, 1: high) of a packed pair in FP32.
-static __device__ __forceinline__ float part(uint32_t p, int x)
-{
-    const half2_t h = __builtin_bit_cast(half2_t, p);
-    return x ? (float)h.y : (float)h.x;
-}
-static __device__ __forceinline__ float4_t mfma16(const Frag &a, const Frag &b, float4_t c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
-}
-static __device__ __forceinline__ uint32_t pk_mul(uint32_t a, uint32_t b)
-{
-    return bits(__builtin_bit_cast(half2_t, a) * __builtin_bit_cast(half2_t, b));
-}
 
 // The four Gaussians' factors times m0 ... m3.
 static __device__ __forceinline__ void scale_pair(Frag &b, float m0, float m1, float m2, float m3)
@@ -288,11 +223,10 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int total_items = prefix[n_scenes];
     const int hx = k.nx / 2, hy = k.ny / 2;
-    const float lim = (float)(k.tau2 * (1.0 + 1e-5)) + 1e-4f;
-    const float mrxf = (float)k.mrx, mryf = (float)k.mry;
+    const float lim = uniform_f((float)(k.tau2 * (1.0 + 1e-5)) + 1e-4f);
+    const float mrxf = uniform_f((float)k.mrx), mryf = uniform_f((float)k.mry);
     const int col = lane & (SUBX - 1), row0 = lane >> 4;
     const int yi = (col >> 2) + 4 * (col & 3);  // the row whose Y factor the lane forms: A row i is row i / 4 + 4 (i % 4)
-    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
     MLane<C> L;
     L.u = (float)col - 7.5f;
     L.v = (float)yi - 7.5f;
@@ -380,7 +314,7 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                     const int gi = base + r * WG + tid;
                     bool pred = false;
                     if (r < nr && gi < c1) {
-                        const float4 r0 = *reinterpret_cast<const float4 *>(rec + gi);
+                        const float4_t r0 = load4(rec + gi);
                         pred = ellipse_meets_rect_r(r0.x, r0.y, r0.z, 0.5f * __builtin_amdgcn_rcpf(r0.x), 0.5f * __builtin_amdgcn_rcpf(r0.z),
                                              lim, X0, X1, Y0, Y1);
                     }
@@ -393,7 +327,7 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                 for (int r = 0; r < MM_CAND / WG; ++r)
 #pragma unroll
                     for (int w = 0; w < WAVES; ++w) {
-                        if (w == wave && (bal[r] >> lane) & 1) s_idx[off + __popcll(bal[r] & lt)] = base + r * WG + tid;
+                        if (w == wave && (bal[r] >> lane) & 1) s_idx[off + rank_below(bal[r])] = base + r * WG + tid;
                         off += s_cnt[r][w];
                     }
                 if (tid == 0) s_item = off;
@@ -404,7 +338,7 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
             for (int j0 = 0; wave_live && j0 < total; j0 += 64) {
                 int cls = -1;  // -1 not on the sub-tile, 0 term by term, else the class of |a|
                 int ee = MM_E_NONE, qi = 0;
-                float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f);
+                float4_t r0 = {0.0f, 0.0f, 0.0f, 0.0f};
                 float lx = 0.0f, ly = 0.0f, qf = 0.0f;  // gradient of q at the centre, q there = qi - qf
                 const GRec *rp = rec + s_idx[min(j0 + lane, total - 1)];
                 // the sub-tile's uniform values are formed again in every batch (opaque integers): held
@@ -414,8 +348,8 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                 const float x0 = (float)max(sx, -hx) - mrxf, x1 = (float)min(sx + SUBX - 1, hx - 1) - mrxf;
                 const float y0 = (float)max(sy, -hy) - mryf, y1 = (float)min(sy + SUBX - 1, hy - 1) - mryf;
                 if (j0 + lane < total) {
-                    r0 = *reinterpret_cast<const float4 *>(rp);
-                    const float4 am = *reinterpret_cast<const float4 *>(&rp->amp[0]);
+                    r0 = load4(rp);
+                    const float4_t am = load4(rp->amp);
                     if (ellipse_meets_rect_r(r0.x, r0.y, r0.z, 0.5f * __builtin_amdgcn_rcpf(r0.x), 0.5f * __builtin_amdgcn_rcpf(r0.z),
                                              lim, x0, x1, y0, y1)) {
                         const double xe = sx + 7.5 - k.mrx, ye = sy + 7.5 - k.mry;
@@ -425,13 +359,13 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                         qf = (float)(qr - q0);
                         lx = (float)(2.0 * ax + b2 * ye);
                         ly = (float)(2.0 * gy + b2 * xe);
-                        const float aa = fabsf(r0.y) * (float)(0.6931471805599453 * 56.25), az = fabsf(r0.w);
+                        const float aa = fabsf(r0.y) * MM_A_OF_BETA2, az = fabsf(r0.w);
                         const float ampmax = fmaxf(fmaxf(fabsf(am.x), fabsf(am.y)), fmaxf(fabsf(am.z), fabsf(am.w)));
                         const float ex = fmaf(r0.x, MM_P, fabsf(lx) * 7.5f), ey = fmaf(r0.z, MM_P, fabsf(ly) * 7.5f);
                         const float ph = az * phimax;
-                        const bool ok = aa <= MM_A7 && fmaxf(ex, ey) <= 10.0f && az <= zlim && ph <= 1e-3f &&
+                        const bool ok = fmaxf(ex, ey) <= 10.0f && az <= zlim && ph <= 1e-3f &&
                                         ph * aa <= 1e-6f && ampmax <= 1e30f;
-                        cls = !ok ? 0 : (aa <= MM_A3 ? 3 : (aa <= MM_A4 ? 4 : (aa <= MM_A5 ? 5 : (aa <= MM_A6 ? 6 : 7))));
+                        cls = ok ? cross_class(aa) : 0;
                         // exponent of the entry's largest term at the sub-tile's centre
                         if (ampmax > 0.0f && ampmax <= 3.4028234663852886e38f) ee = ilogbf(ampmax) + 1 - min(qi, 200);
                     }
@@ -472,41 +406,19 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                 if (lane < npad - nf)
                     for (int i = 0; i < mm_floats(C); ++i) s_w[wave][nf + lane][i] = 0.0f;
                 if (cls >= 0) {
-                    const int pos = cls == 7   ? kept + __popcll(b7 & lt)
-                                    : cls == 6 ? n7 + __popcll(b6 & lt)
-                                    : cls == 5 ? n6 + __popcll(b5 & lt)
-                                    : cls == 4 ? n5 + __popcll(b4 & lt)
-                                    : cls == 3 ? n4 + __popcll(b3 & lt)
-                                               : __popcll(bd & lt) + npad;
+                    const int pos = cls == 7   ? kept + rank_below(b7)
+                                    : cls == 6 ? n7 + rank_below(b6)
+                                    : cls == 5 ? n6 + rank_below(b5)
+                                    : cls == 4 ? n5 + rank_below(b4)
+                                    : cls == 3 ? n4 + rank_below(b3)
+                                               : rank_below(bd) + npad;
                     float4_t *dst = reinterpret_cast<float4_t *>(&s_w[wave][pos][0]);
-                    const float4 r1 = reinterpret_cast<const float4 *>(rp)[1];
+                    const float4_t r1 = load4(&rp->rx), kap = load4(rp->kappa), am = load4(rp->amp);
                     const uint32_t rx = __float_as_uint(r1.x), ry = __float_as_uint(r1.y);
                     float ik0 = 1.0f, e0;
                     if (cls > 0) {
-                        // coefficients of exp(-a t): Taylor, and the next two orders projected onto the
-                        // lower ones by least squares over the sub-tile's points
-                        const float a = r0.y * (float)(0.6931471805599453 * 56.25);
-                        const float a2 = a * a, a3 = a2 * a, a4 = a2 * a2;
-                        float k0 = 1.0f, k1 = -a, k2 = 0.5f * a2, k3 = 0.0f, k4 = 0.0f;
-                        if (cls == 3) {
-                            k1 -= a3 * (0.45758f / 6.0f);
-                            k0 += a4 * (-0.03819f / 24.0f);
-                            k2 += a4 * (0.7252f / 24.0f);
-                        } else if (cls == 4) {
-                            const float a5 = a4 * a;
-                            k0 += a4 * (-0.03819f / 24.0f);
-                            k1 -= a5 * (-0.17743f / 120.0f);
-                            k2 += a4 * (0.7252f / 24.0f);
-                            k3 = -a3 * (1.0f / 6.0f) - a5 * (1.02948f / 120.0f);
-                        } else {
-                            // orders 5 and 6 projected, or 6 and 7 where order 5 has its own coefficient
-                            const float a6 = a3 * a3, ao = cls == 7 ? a6 * a * (1.0f / 5040.0f) : a4 * a * (1.0f / 120.0f);
-                            k0 += a6 * (0.01017f / 720.0f);
-                            k1 -= ao * (cls == 7 ? 0.0593f : -0.17743f);
-                            k2 += a6 * (-0.37059f / 720.0f);
-                            k3 = -a3 * (1.0f / 6.0f) - ao * (cls == 7 ? -0.65565f : 1.02948f);
-                            k4 = a4 * (1.0f / 24.0f) + a6 * (1.29584f / 720.0f);
-                        }
+                        float k0, k1, k2, k3, k4;
+                        cross_poly(r0.y * MM_A_OF_BETA2, cls, k0, k1, k2, k3, k4);
                         ik0 = __builtin_amdgcn_rcpf(k0);
                         e0 = k0 * ldexpf(__builtin_amdgcn_exp2f(qf), max(MM_XS - es - qi, -300));
                         dst[0] = (float4_t){lx, r0.x, ly, r0.z};
@@ -535,12 +447,12 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                         if (k.phase_mode == 1) {
                             // plain FP32 phase (precision study only)
                             const float rr = (float)cx * r1.z + (float)cy * r1.w;
-                            const float v = rp->kappa[c] - rr - r0.w * (float)s_d0[wave][c];
+                            const float v = kap[c] - rr - r0.w * (float)s_d0[wave][c];
                             bs = v - floorf(v);
                         } else {
-                            bs = (float)frac_m((double)rp->kappa[c] - ramp_rev - (double)r0.w * s_d0[wave][c]);
+                            bs = (float)frac_m((double)kap[c] - ramp_rev - (double)r0.w * s_d0[wave][c]);
                         }
-                        dst[3 + c] = (float4_t){bs, rp->amp[c] * e0, r0.w * s_phi[wave][c] * ik0, r0.w};
+                        dst[3 + c] = (float4_t){bs, am[c] * e0, r0.w * s_phi[wave][c] * ik0, r0.w};
                     }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

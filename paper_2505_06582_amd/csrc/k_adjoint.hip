@@ -129,57 +129,6 @@ hipError_t launch_adj_pack(const Consts &k, const AdjGeom &geo, int n_scenes, co
     return hipGetLastError();
 }
 
-// Reduce NV per-lane values over the wavefront and add the totals to acc[0..NV) (LDS).
-// Up to 8 values (+ 1 carried along), 16, or 24 (16 + 8) use the transposed butterfly.
-template <int NV>
-static __device__ __forceinline__ void reduce_into(float (&x)[NV], float *acc, int lane)
-{
-    if constexpr (NV <= 9) {
-        float v[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = i < NV ? x[i] : 0.0f;
-        float y = NV == 9 ? x[NV - 1] : 0.0f;
-        if constexpr (NV == 9) {
-            reduce_transposed<8, true>(v, y, lane);
-            if (lane == 4) atomicAdd(&acc[8], y);
-        } else {
-            reduce_transposed<8, false>(v, y, lane);
-        }
-        if ((lane & 7) == 0) {
-            const int v0 = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
-            if (v0 < NV && (NV != 9 || v0 < 8)) atomicAdd(&acc[v0], v[0]);  // ds_add_f32, no return
-        }
-    } else if constexpr (NV <= 16) {
-        float v[16];
-        float y = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = i < NV ? x[i] : 0.0f;
-        reduce_transposed<16, false>(v, y, lane);
-        if ((lane & 7) == 0) {
-            const int v0 = 2 * (((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1));
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                if (v0 + j < NV) atomicAdd(&acc[v0 + j], v[j]);
-        }
-    } else {
-        static_assert(NV <= 24, "at most 24 reduced values");
-        float v[16], w[8];
-        float y = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = x[i];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) w[i] = 16 + i < NV ? x[16 + i] : 0.0f;
-        reduce_transposed<16, false>(v, y, lane);
-        reduce_transposed<8, false>(w, y, lane);
-        if ((lane & 7) == 0) {
-            const int g = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) atomicAdd(&acc[2 * g + j], v[j]);
-            if (16 + g < NV) atomicAdd(&acc[16 + g], w[0]);
-        }
-    }
-}
-
 // A Gaussian accepted for the current region: its index in the item, its 4-row block mask and
 // the phase bases of the region's two sub-tiles.
 template <int C>
@@ -467,6 +416,16 @@ __global__ void __launch_bounds__(adj_wg(C, DEPTH), adj_waves_per_simd(C, DEPTH)
     }
 }
 
+// Which adjoint runs.  The matrix-core one needs every grid frequency to propagate; on smaller grids
+// supports cover few sub-tiles and more Gaussians fail the separable form's tests.  Backward,
+// this kernel against the matrix-core one (ms): 300 Gaussians at 1000 x 750, one wavelength 0.360
+// against 0.402; 5000, three wavelengths 0.840 against 0.868; 20000 at 1280 x 1024, two 1.68
+// against 1.21; 1000 at 1920 x 1080, three 1.14 against 0.98; 1e5 12.3 against 7.6.
+bool adjoint_on_mfma(const Consts &k)
+{
+    return !grid_has_evanescent(k) && (int64_t)k.nx * k.ny >= (int64_t)ADJ_MFMA_POINTS;
+}
+
 template <int C, bool DEPTH>
 static const void *adj_kernel_ptr() { return (const void *)k_adjoint<C, DEPTH>; }
 
@@ -474,6 +433,7 @@ hipError_t launch_adjoint(const Plan &p, const Consts &k, const BwdScene *scenes
                           long long *queue, const float *dpack, const double *d0, const AdjGeom &geo, int grid,
                           hipStream_t s)
 {
+    if (adjoint_on_mfma(k)) return launch_adjoint_mfma(p, k, scenes, prefix, n_scenes, queue, dpack, geo, grid, s);
 #define GWS_ADJ_LAUNCH(CC, DD)                                                                                   \
     hipLaunchKernelGGL((k_adjoint<CC, DD>), dim3(grid), dim3(adj_wg(CC, DD)), 0, s, k, p.tile_xy, scenes, prefix,  \
                        n_scenes, \
@@ -490,8 +450,10 @@ hipError_t launch_adjoint(const Plan &p, const Consts &k, const BwdScene *scenes
     return hipGetLastError();
 }
 
-int adjoint_occupancy(int C, int depth)
+int adjoint_occupancy(const Consts &k)
 {
+    const int C = k.C, depth = k.depth_grad;
+    if (adjoint_on_mfma(k)) return adjoint_mfma_occupancy(C, depth);
     const void *kp = nullptr;
     switch (C) {
     case 1: kp = depth ? adj_kernel_ptr<1, true>() : adj_kernel_ptr<1, false>(); break;

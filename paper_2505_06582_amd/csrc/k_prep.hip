@@ -13,7 +13,7 @@
 // q(m') = alpha m_x'^2 + beta2 m_x' m_y' + gamma m_y'^2 and the term is below eps of its
 // peak outside q <= log2(1/eps).  The circumscribed circle of that ellipse has radius
 // sqrt(log2(1/eps) / lambda_min) and sets the Gaussian's bucket.
-#include "gws_internal.h"
+#include "mfma_f16.h"
 
 namespace gws {
 
@@ -214,7 +214,7 @@ hipError_t radix_sort_48(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, u
 // ---------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_records(GView g, Consts k, const uint64_t *__restrict__ keys,
                                                   const uint32_t *__restrict__ vals, GRec *__restrict__ rec,
-                                                  int64_t n, const long long *__restrict__ counters)
+                                                  int64_t n, const long long *__restrict__ counters, bool poly)
 {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t nvalid = n - counters[CTR_NCULLED];
@@ -252,14 +252,20 @@ __global__ void __launch_bounds__(256) k_records(GView g, Consts k, const uint64
         }
     }
     rec[s] = r;
+    if (poly) {
+        const float a = r.beta2 * MM_A_OF_BETA2;
+        float k0, k1, k2, k3, k4;
+        cross_poly(a, cross_class(fabsf(a)), k0, k1, k2, k3, k4);
+        adj_poly(rec, n)[s] = make_float4(k1 / k0, k2 / k0, k3 / k0, k0);
+    }
 }
 
 hipError_t launch_records(const GView &g, const Consts &k, const uint64_t *keys, const uint32_t *vals,
-                          GRec *rec, int64_t n, const long long *counters, hipStream_t s)
+                          GRec *rec, int64_t n, const long long *counters, bool poly, hipStream_t s)
 {
     const int64_t blocks = (n + 255) / 256;
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_records, dim3((unsigned)blocks), dim3(256), 0, s, g, k, keys, vals, rec, n, counters);
+    hipLaunchKernelGGL(k_records, dim3((unsigned)blocks), dim3(256), 0, s, g, k, keys, vals, rec, n, counters, poly);
     return hipGetLastError();
 }
 

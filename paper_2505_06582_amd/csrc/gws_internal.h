@@ -530,7 +530,7 @@ hipError_t launch_adjoint_mfma(const Plan &p, const Consts &k, const BwdScene *s
 int adjoint_mfma_occupancy(int C, int depth);
 hipError_t launch_synth(GView g, float *base, int64_t n, uint64_t seed, const Consts &k, hipStream_t s);
 // Whether the accumulation runs on the matrix cores (k_accum_mfma.hip) or term by term.
-constexpr int ACC_MFMA_POINTS = 700000;
+constexpr int ACC_MFMA_POINTS = (1 << 22) + 1;
 bool accumulate_on_mfma(const Consts &k, int F);
 bool grid_has_evanescent(const Consts &k);
 hipError_t launch_accumulate_mfma(const Plan &p, const Consts &k, const FwdScene *scenes, const int32_t *prefix,

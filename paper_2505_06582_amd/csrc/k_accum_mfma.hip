@@ -28,7 +28,7 @@
 // 1080 x 1920 x 3: 5.4e-7 (7.0e-7 term by term); spectrum of 1e6 at 2160 x 3840 x 3: 1.4e-6 (4.5e-6).
 //
 // A Gaussian that fails a test on a sub-tile (a too large, a steep envelope, a deep Gaussian
-// where k_z curves fast, non-finite amplitude) is evaluated term by term into the same
+// where k_z curves fast, a nearly singular covariance, non-finite amplitude) is evaluated term by term into the same
 // accumulators there (lane l of the MFMA result holds column l % 16 and rows l / 16 + 4 f, the
 // term-by-term kernel's own layout).
 //
@@ -363,8 +363,11 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                         const float ampmax = fmaxf(fmaxf(fabsf(am.x), fabsf(am.y)), fmaxf(fabsf(am.z), fabsf(am.w)));
                         const float ex = fmaf(r0.x, MM_P, fabsf(lx) * 7.5f), ey = fmaf(r0.z, MM_P, fabsf(ly) * 7.5f);
                         const float ph = az * phimax;
+                        // near a singular covariance q is a small difference of large terms, and its
+                        // rounding is part of the result: kept as the term-by-term kernel rounds it
+                        const float ag4 = 4.0f * r0.x * r0.z;
                         const bool ok = fmaxf(ex, ey) <= 10.0f && az <= zlim && ph <= 1e-3f &&
-                                        ph * aa <= 1e-6f && ampmax <= 1e30f;
+                                        ph * aa <= 1e-6f && ampmax <= 1e30f && fmaf(-r0.y, r0.y, ag4) >= 0.04f * ag4;
                         cls = ok ? cross_class(aa) : 0;
                         // exponent of the entry's largest term at the sub-tile's centre
                         if (ampmax > 0.0f && ampmax <= 3.4028234663852886e38f) ee = ilogbf(ampmax) + 1 - min(qi, 200);
@@ -492,7 +495,7 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                         if (!(rows & (1u << f))) continue;
                         const float fmy = (float)((double)(sy + rw + 4 * f) - k.mry);
                         const float E = __builtin_amdgcn_exp2f(
-                            -fmaf(gamma, fmy * fmy, fmaf(beta2, fmx * fmy, alpha * fmx * fmx)));
+                            -fmaf(gamma, fmy * fmy, fmaf(beta2, fmx * fmy, alpha * (fmx * fmx))));
                         const float dyf = (float)(rw + 4 * f - 8);
 #pragma unroll
                         for (int c = 0; c < C; ++c) {

@@ -40,9 +40,9 @@ def spectrum_error(ctx, scene, grid, label, n_freq=700, half_width=None, seed=5,
     return e
 
 
-@pytest.mark.parametrize("nx,ny,c,n", [(1000, 750, 1, 1), (1000, 750, 2, 15), (1200, 600, 3, 16), (1000, 750, 4, 17),
-                                       (960, 810, 3, 63), (1200, 640, 2, 65), (1000, 750, 1, 129), (1440, 900, 4, 1025),
-                                       (1024, 720, 1, 2600)])
+@pytest.mark.parametrize("nx,ny,c,n", [(2400, 1800, 1, 1), (2400, 1800, 2, 15), (3000, 1440, 3, 16), (2400, 1800, 4, 17),
+                                       (2160, 1944, 3, 63), (3000, 1458, 2, 65), (2400, 1800, 1, 129), (2880, 1800, 4, 1025),
+                                       (4050, 1080, 1, 2600)])
 def test_list_lengths_and_ragged_grids(ctx, nx, ny, c, n):
     grid = Grid(nx, ny, 8e-6, 8e-6, LAMBDAS[:c])
     scene = gwsgen.make_scene(n, grid, 300 + n, depth_range=(-10e-3, 10e-3))
@@ -54,7 +54,7 @@ def test_list_lengths_and_ragged_grids(ctx, nx, ny, c, n):
 @pytest.mark.parametrize("sign", [1, -1])
 def test_cross_term_classes(ctx, a, sign):
     """Gaussians whose cross term on a 16 x 16 sub-tile is exactly exp(-a t), |t| <= 1."""
-    grid = Grid(1280, 1024, 8e-6, 8e-6, (520e-9,))
+    grid = Grid(2560, 2048, 8e-6, 8e-6, (520e-9,))
     scene = gwsgen.make_scene(40, grid, 77, depth_range=(-8e-3, 8e-3), sigma_px=(4.0, 4.0))
     sxy = a * grid.nx * grid.px * grid.ny * grid.py / (56.25 * 4 * math.pi ** 2)
     var = 1.3 * sxy + (4.0 * grid.px) ** 2
@@ -64,12 +64,23 @@ def test_cross_term_classes(ctx, a, sign):
     assert spectrum_error(ctx, scene, grid, "a=%g" % (sign * a), half_width=(max(16, min(hw, 640)),) * 2) < TOL
 
 
+def test_nearly_singular_covariance(ctx):
+    """Correlation 0.99: evaluated term by term.  The exponent's terms are 1 / (1 - 0.99) times its value
+    (at most 2 where the spectrum's energy is); six roundings of 2^-24 of them, the record's included."""
+    grid = Grid(2560, 2048, 8e-6, 8e-6, (520e-9,))
+    scene = gwsgen.make_scene(60, grid, 78, depth_range=(-8e-3, 8e-3), sigma_px=(4.0, 4.0))
+    scene.cov_xx[:] = scene.cov_yy[:] = np.float32((20 * grid.px) ** 2)
+    scene.cov_xy[:] = np.float32(0.99) * scene.cov_xx
+    hw = int(grid.nx / (2 * math.pi * 20) * 3)
+    assert spectrum_error(ctx, scene, grid, "singular", half_width=(hw, hw)) < 200 * 2.0 * math.log(2) * 6 * 2.0 ** -24
+
+
 def test_mixed_amplitudes_depths_and_reference_wave(ctx):
     """Amplitudes over forty orders of magnitude in one list, Gaussians at 0.5 m (outside the separable
     form's depth) among ordinary ones, a tilted reference wave."""
-    grid = Grid(1000, 750, 8e-6, 8e-6, LAMBDAS[:2])
+    grid = Grid(2400, 1800, 8e-6, 8e-6, LAMBDAS[:2])
     scene = gwsgen.make_scene(200, grid, 9, depth_range=(-10e-3, 10e-3))
-    assert spectrum_error(ctx, scene, Grid(1000, 750, 8e-6, 8e-6, LAMBDAS[:2], ref_nu=(9e3, -4e3)), "reference wave",
+    assert spectrum_error(ctx, scene, Grid(2400, 1800, 8e-6, 8e-6, LAMBDAS[:2], ref_nu=(9e3, -4e3)), "reference wave",
                           half_width=(120, 90)) < TOL
     scene.depth[::7] = np.float32(0.5)
     assert spectrum_error(ctx, scene, grid, "deep", half_width=(120, 90)) < 1e-5
@@ -83,7 +94,7 @@ def test_mixed_amplitudes_depths_and_reference_wave(ctx):
 
 def test_repeats_bitwise_and_batched(ctx):
     import torch
-    grid = Grid(1000, 750, 8e-6, 8e-6, LAMBDAS[:2])
+    grid = Grid(2400, 1800, 8e-6, 8e-6, LAMBDAS[:2])
     counts = [3000, 0, 41]
     scenes = [gwsgen.make_scene(n, grid, 60 + n) for n in counts]
     g = scene_to_torch(gwsgen.Scene.concat(scenes))

@@ -355,7 +355,6 @@ static Layout make_layout(const gws_problem *p, int64_t n, int f_fwd, int f_bwd,
     const int ntiles = ntiles_for(p->nx, p->ny, 2);
     L.n = n;
     L.F = f_fwd;
-    L.sort_blocks = sort_blocks_for(n);
     const size_t part_bytes = (size_t)fwd_max_slots_f4(n) * C * 4 * WG * sizeof(float2);
     L.max_slots = (int64_t)(part_bytes / ((size_t)C * f_fwd * WG * sizeof(float2)));
     L.max_items = L.max_slots / 2 + ntiles + 1;
@@ -375,13 +374,13 @@ static Layout make_layout(const gws_problem *p, int64_t n, int f_fwd, int f_bwd,
     size_t o = 0;
     auto take = [&](size_t bytes) { const size_t r = o; o = align256(o + std::max<size_t>(bytes, 1)); return r; };
     L.off_counters = take(sizeof(long long) * CTR_COUNT);
-    L.off_bucket_hist = take(sizeof(uint32_t) * NBUCKET);
+    L.off_bucket_end = take(sizeof(uint32_t) * NBUCKET);
     L.off_cum = take(sizeof(uint32_t) * NBUCKET);
     L.off_keys_a = take(sizeof(uint64_t) * n);
     L.off_keys_b = take(sizeof(uint64_t) * n);
     L.off_vals_a = take(sizeof(uint32_t) * n);
     L.off_vals_b = take(sizeof(uint32_t) * n);
-    L.off_sort_hist = take(sizeof(uint32_t) * 256 * L.sort_blocks);
+    L.off_sort_hist = take(sizeof(uint32_t) * sort_table_words(n));
     // the records, and behind them the matrix-core adjoint's coefficients
     L.off_records = take((sizeof(GRec) + (!fwd_only && adjoint_on_mfma(make_consts(p, 0)) ? sizeof(float4) : 0)) * n);
     L.off_tile_L = take(sizeof(int32_t) * ntiles);
@@ -470,21 +469,19 @@ struct ExactLayout {
     size_t off_keys_a = 0, off_keys_b = 0, off_vals_a = 0, off_vals_b = 0, off_sort_hist = 0, off_rec = 0,
            off_tmap = 0, off_spec = 0, off_dft = 0, off_gspec = 0, off_ckpt = 0, off_dmap = 0,
            off_pspec = 0, off_pspat = 0, off_win = 0, off_pimgs = 0, off_counters = 0, total = 0;
-    int sort_blocks = 1;
 };
 
 static ExactLayout exact_layout(const gws_problem *p, int64_t n)
 {
     ExactLayout L;
     const size_t M = (size_t)p->nx * p->ny;
-    L.sort_blocks = sort_blocks_for(n);
     size_t o = 0;
     auto take = [&](size_t bytes) { const size_t r = o; o = align256(o + std::max<size_t>(bytes, 1)); return r; };
     L.off_keys_a = take(sizeof(uint64_t) * n);
     L.off_keys_b = take(sizeof(uint64_t) * n);
     L.off_vals_a = take(sizeof(uint32_t) * n);
     L.off_vals_b = take(sizeof(uint32_t) * n);
-    L.off_sort_hist = take(sizeof(uint32_t) * 256 * L.sort_blocks);
+    L.off_sort_hist = take(sizeof(uint32_t) * sort_table_words(n));
     L.off_rec = take((size_t)64 * n);
     L.off_tmap = take(sizeof(float) * M);
     L.off_pimgs = take(sizeof(float2) * M * ((exact_batch(p->nx, p->ny) + 1) / 2));
@@ -648,7 +645,7 @@ static gws_status check_ws(gws_ctx *ctx, void *ws, size_t ws_bytes, size_t need)
 
 struct Bufs {
     long long *counters;
-    uint32_t *bucket_hist, *cum, *sort_hist, *vals_a, *vals_b;
+    uint32_t *bucket_end, *cum, *sort_hist, *vals_a, *vals_b;
     uint64_t *keys_a, *keys_b;
     GRec *rec;
     int32_t *tile_L;
@@ -664,7 +661,7 @@ static Bufs carve(const Layout &L, char *b)
 {
     Bufs r;
     r.counters = (long long *)(b + L.off_counters);
-    r.bucket_hist = (uint32_t *)(b + L.off_bucket_hist);
+    r.bucket_end = (uint32_t *)(b + L.off_bucket_end);
     r.cum = (uint32_t *)(b + L.off_cum);
     r.keys_a = (uint64_t *)(b + L.off_keys_a);
     r.keys_b = (uint64_t *)(b + L.off_keys_b);
@@ -720,11 +717,12 @@ static GradView grad_view(const gws_grads *g, int64_t off, int64_t total)
 static gws_status run_prep(gws_ctx *ctx, const Consts &k, const GView &g, const Layout &L, const Bufs &B, hipStream_t s,
                            uint64_t **keys_sorted, uint32_t **vals_sorted)
 {
-    HIP_CHECK(ctx, launch_zero_counters(B.counters, B.bucket_hist, s));
-    HIP_CHECK(ctx, launch_keys(g, k, B.keys_a, B.vals_a, B.bucket_hist, B.counters, s));
-    HIP_CHECK(ctx, radix_sort_48(B.keys_a, B.vals_a, B.keys_b, B.vals_b, B.sort_hist, g.n, L.sort_blocks, s, keys_sorted,
-                                 vals_sorted));
-    HIP_CHECK(ctx, launch_records(g, k, *keys_sorted, *vals_sorted, B.rec, g.n, B.counters,
+    HIP_CHECK(ctx, launch_zero_counters(B.counters, B.bucket_end, s));
+    HIP_CHECK(ctx, launch_keys(g, k, B.keys_a, B.vals_a, s));
+    // the forward's keys have 48 bits, the adjoint's the upper 16 of them
+    HIP_CHECK(ctx, radix_sort(B.keys_a, B.vals_a, B.keys_b, B.vals_b, B.sort_hist, g.n, k.forward ? 0 : 4, 5, s,
+                              keys_sorted, vals_sorted));
+    HIP_CHECK(ctx, launch_records(g, k, *keys_sorted, *vals_sorted, B.rec, g.n, B.bucket_end, B.counters,
                                   !k.forward && adjoint_on_mfma(k), s));
     return GWS_OK;
 }
@@ -825,7 +823,7 @@ static gws_status forward_run(gws_ctx *ctx, const gws_problem *prob, int S, cons
             // the configuration's chunk of candidates per work item, capped at n / 16 (at least 128)
             // so that a small scene's crowded tiles still split into several items
             const int chunk = (int)std::min<int64_t>(kTileCfg[cfg - 1][1], std::max<int64_t>(128, BL.n[i] / 16));
-            HIP_CHECK(ctx, launch_bin_forward(*p, B.bucket_hist, B.cum, B.tile_L, B.tile_slots, B.items, L.max_items,
+            HIP_CHECK(ctx, launch_bin_forward(*p, B.bucket_end, B.cum, B.tile_L, B.tile_slots, B.items, L.max_items,
                                               L.max_slots, chunk, B.counters, s));
             tab.s[i] = FwdScene{B.rec, B.tile_L, B.items, B.tile_slots, B.partials, spectra + (int64_t)i * CM, B.counters};
             ctrs[i] = B.counters;
@@ -965,7 +963,6 @@ static gws_status exact_forward_run(gws_ctx *ctx, const gws_problem *prob, const
     eb.vals_a = (uint32_t *)(base + L.off_vals_a);
     eb.vals_b = (uint32_t *)(base + L.off_vals_b);
     eb.sort_hist = (uint32_t *)(base + L.off_sort_hist);
-    eb.sort_blocks = L.sort_blocks;
     eb.rec = (void *)(base + L.off_rec);
     eb.tmap = (float *)(base + L.off_tmap);
     eb.pimgs = (float2 *)(base + L.off_pimgs);
@@ -1010,7 +1007,6 @@ static gws_status exact_backward_run(gws_ctx *ctx, const gws_problem *prob, cons
     eb.vals_a = (uint32_t *)(base + L.off_vals_a);
     eb.vals_b = (uint32_t *)(base + L.off_vals_b);
     eb.sort_hist = (uint32_t *)(base + L.off_sort_hist);
-    eb.sort_blocks = L.sort_blocks;
     eb.rec = (void *)(base + L.off_rec);
     eb.tmap = (float *)(base + L.off_tmap);
     eb.pimgs = (float2 *)(base + L.off_pimgs);

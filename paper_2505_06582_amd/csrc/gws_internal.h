@@ -421,12 +421,11 @@ struct Plan {
 // Workspace layout for one scene batch.
 struct Layout {
     size_t total = 0;
-    size_t off_keys_a, off_keys_b, off_vals_a, off_vals_b, off_sort_hist, off_bucket_hist, off_cum;
+    size_t off_keys_a, off_keys_b, off_vals_a, off_vals_b, off_sort_hist, off_bucket_end, off_cum;
     size_t off_counters, off_records, off_tile_L, off_tile_slots, off_items, off_range_base, off_bitems, off_partials, off_bpartials;
     size_t off_spectrum, off_gspec, off_dtab, off_d0tab, off_chunk_items;
     int32_t nsx = 0, nsy = 0, sx_min = 0, sy_min = 0, F = 4;
     int64_t n = 0;
-    int32_t sort_blocks = 0;
     int64_t max_items = 0, max_slots = 0, max_bitems = 0, max_bslots = 0;
     // item-table capacity that covers every tiling sharing this byte budget (F = 2 has the most slots)
     static int64_t max_slots_bound(size_t part_bytes, int C, int ntiles)
@@ -452,17 +451,17 @@ enum Counter {
 };
 
 // ---- kernel launchers (each enqueues on `stream`, returns hipError_t) ----
-hipError_t launch_keys(const GView &g, const Consts &k, uint64_t *keys, uint32_t *vals,
-                       uint32_t *bucket_hist, long long *counters, hipStream_t s);
-// Blocks (and 256-entry histograms) radix_sort_48 uses for n keys.
-int sort_blocks_for(int64_t n);
-hipError_t radix_sort_48(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, uint32_t *vals_b,
-                         uint32_t *block_hist, int64_t n, int nblocks, hipStream_t s,
-                         uint64_t **keys_out, uint32_t **vals_out);
+hipError_t launch_keys(const GView &g, const Consts &k, uint64_t *keys, uint32_t *vals, hipStream_t s);
+// Stable sort by the 8-bit digits first ... last of the keys (digit 0 the lowest), scratch of
+// sort_table_words(n) words.
+int64_t sort_table_words(int64_t n);
+hipError_t radix_sort(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, uint32_t *vals_b, uint32_t *table,
+                      int64_t n, int first_digit, int last_digit, hipStream_t s, uint64_t **keys_out,
+                      uint32_t **vals_out);
 hipError_t launch_records(const GView &g, const Consts &k, const uint64_t *keys,
-                          const uint32_t *vals, GRec *rec, int64_t n, const long long *counters,
+                          const uint32_t *vals, GRec *rec, int64_t n, uint32_t *bucket_end, long long *counters,
                           bool poly, hipStream_t s);
-hipError_t launch_bin_forward(const Plan &p, const uint32_t *bucket_hist, uint32_t *cum, int32_t *tile_L,
+hipError_t launch_bin_forward(const Plan &p, const uint32_t *bucket_end, uint32_t *cum, int32_t *tile_L,
                               int2 *tile_slots, Item *items, int64_t max_items, int64_t max_slots, int base_chunk,
                               long long *counters, hipStream_t s);
 hipError_t launch_bin_backward(const Plan &p, const uint64_t *keys, BItem *bitems, int2 *chunk_items,
@@ -480,7 +479,6 @@ hipError_t launch_reduce_partials(const Plan &p, const Consts &k, const FwdScene
 struct ExactBuffers {
     uint64_t *keys_a, *keys_b;
     uint32_t *vals_a, *vals_b, *sort_hist;
-    int sort_blocks;
     void *rec;     // 64-byte records, front to back
     float *tmap;   // transmittance [ny][nx]
     float2 *pimgs;  // one batch, two Gaussians per image [(B + 1) / 2][ny][nx]: the masked
@@ -537,7 +535,7 @@ hipError_t launch_accumulate_mfma(const Plan &p, const Consts &k, const FwdScene
                                   int n_scenes, long long *queue, int grid, hipStream_t s);
 int accumulate_mfma_occupancy(int C);
 int accumulate_occupancy(const Consts &k, int F);
-hipError_t launch_zero_counters(long long *counters, uint32_t *bucket_hist, hipStream_t s);
+hipError_t launch_zero_counters(long long *counters, uint32_t *bucket_end, hipStream_t s);
 hipError_t launch_copy_counters(const long long *src, long long *dst, hipStream_t s);
 int fft_col_batch(int n);
 size_t l2_workspace_bytes();

@@ -366,8 +366,7 @@ hipError_t run_exact_forward(const Plan &p, const Consts &k, const GView &g, con
     hipLaunchKernelGGL(k_exact_keys, dim3(gn), dim3(256), 0, s, g, eb.keys_a, eb.vals_a);
     uint64_t *keys = nullptr;
     uint32_t *order = nullptr;
-    hipError_t e = radix_sort_48(eb.keys_a, eb.vals_a, eb.keys_b, eb.vals_b, eb.sort_hist, n, eb.sort_blocks, s, &keys,
-                                 &order);
+    hipError_t e = radix_sort(eb.keys_a, eb.vals_a, eb.keys_b, eb.vals_b, eb.sort_hist, n, 0, 3, s, &keys, &order);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_exact_records, dim3(gn), dim3(256), 0, s, g, k, order, rec, eb.counters);
     const int B = (int)exact_batch(k.nx, k.ny);
@@ -729,8 +728,7 @@ hipError_t run_exact_backward(const Plan &p, const Consts &k, const GView &g, co
     hipLaunchKernelGGL(k_exact_keys, dim3(gn), dim3(256), 0, s, g, eb.keys_a, eb.vals_a);
     uint64_t *keys = nullptr;
     uint32_t *order = nullptr;
-    hipError_t e = radix_sort_48(eb.keys_a, eb.vals_a, eb.keys_b, eb.vals_b, eb.sort_hist, n, eb.sort_blocks, s, &keys,
-                                 &order);
+    hipError_t e = radix_sort(eb.keys_a, eb.vals_a, eb.keys_b, eb.vals_b, eb.sort_hist, n, 0, 3, s, &keys, &order);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_exact_records, dim3(gn), dim3(256), 0, s, g, k, order, rec, eb.counters);
     // Gs = FFT(dL/du)

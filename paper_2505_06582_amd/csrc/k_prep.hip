@@ -1,8 +1,9 @@
 // Per-Gaussian preprocessing, depth sort and binning of spectral supports (gfx950).
 //
 // k_keys     one thread per Gaussian: validity, spectral-support radius bucket, sort key
-//            (support radius descending, then depth descending = front to back).
-// radix sort stable LSD radix sort of the 48-bit keys, 8-bit digits, wave-ballot ranking.
+//            (forward: support radius descending, then depth descending = front to back;
+//            adjoint: level of the radius, then the support's shape).
+// radix sort stable LSD radix sort of the keys, 8-bit digits, wave-ballot ranking.
 // k_records  one thread per sorted Gaussian: the 64-byte record the accumulation reads,
 //            with every large phase quantity reduced exactly in FP64 / fixed point.
 // k_bin_*    one work-group: candidate counts per tile, chunk size, work-item lists.
@@ -21,9 +22,22 @@ static __device__ __forceinline__ bool finite_f(float v) { return (__float_as_ui
 
 static __device__ __forceinline__ double frac_d(double v) { return v - floor(v); }
 
+// The adjoint's order: its sums do not depend on it, so Gaussians whose ellipses cover the same
+// sub-tiles stand together -- levels of the radius (LPO to the octave), then the ratio of the
+// axes in four steps, then the axis' direction.  A level's largest radius bounds its tiles.
+constexpr uint32_t KEY_CULLED = 0xffffu;  // upper 16 bits of an invalid Gaussian's key, above every valid one
+constexpr int BWD_LPO = 4, BWD_LEVELS = 12 * BWD_LPO;
+static __device__ __forceinline__ int bwd_level(int bucket)
+{
+    return min(BWD_LEVELS, (int)((float)BWD_LPO * log2f((float)(bucket + 1))));
+}
+static __device__ __forceinline__ int bwd_level_bucket(int level)
+{
+    return min(NBUCKET - 1, (int)exp2f((float)(level + 1) * (1.0f / BWD_LPO)) + 1);  // one above: log2f's rounding
+}
+
 __global__ void __launch_bounds__(256) k_keys(GView g, Consts k, uint64_t *__restrict__ keys,
-                                               uint32_t *__restrict__ vals, uint32_t *__restrict__ bucket_hist,
-                                               long long *__restrict__ counters)
+                                               uint32_t *__restrict__ vals)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= g.n) return;
@@ -40,169 +54,328 @@ __global__ void __launch_bounds__(256) k_keys(GView g, Consts k, uint64_t *__res
     const double det = (double)sxx * syy - (double)sxy * sxy;
     ok = ok && sxx > 0.0f && det > 0.0;
     if (k.forward) ok = ok && o != 0.0f && any_amp;
-    uint32_t hi;
+    uint32_t hi, lo;
     if (ok) {
         const double Wx = k.nx * k.px, Wy = k.ny * k.py;
         const double a = k.K2 * sxx / (Wx * Wx), b = k.K2 * sxy / (Wx * Wy), c = k.K2 * syy / (Wy * Wy);
-        const double lmin = 0.5 * (a + c) - sqrt(0.25 * (a - c) * (a - c) + b * b);
+        const double rad = sqrt(0.25 * (a - c) * (a - c) + b * b), lmin = 0.5 * (a + c) - rad;
         int bucket = NBUCKET - 1;
         if (lmin > 0.0) {
             const double R = sqrt(k.tau2 / lmin);
             if (R < (double)(NBUCKET - 1)) bucket = (int)R;
         }
-        hi = (uint32_t)(NBUCKET - 1 - bucket);
-        atomicAdd(&bucket_hist[bucket], 1u);
+        if (k.forward) {
+            hi = (uint32_t)(NBUCKET - 1 - bucket);
+        } else {
+            const int aspect = min(3, (int)(4.0f * sqrtf(fmaxf((float)lmin, 0.0f) / (float)(lmin + 2.0 * rad))));
+            const float axis = 0.5f + 0.15915494309189535f * atan2f((float)(2.0 * b), (float)(a - c));  // [0, 1]
+            hi = (uint32_t)(((BWD_LEVELS - bwd_level(bucket)) << 10) | (aspect << 8) | min(255, (int)(256.0f * axis)));
+        }
     } else {
-        hi = 0xffffu;
-        atomicAdd((unsigned long long *)&counters[CTR_NCULLED], 1ull);
+        hi = KEY_CULLED;
     }
     // depth, descending: map the float to an ascending unsigned key, then complement
     const uint32_t u = __float_as_uint(z);
     const uint32_t asc = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-    keys[i] = ((uint64_t)hi << 32) | (uint64_t)(~asc);
+    lo = k.forward ? ~asc : 0u;
+    keys[i] = ((uint64_t)hi << 32) | (uint64_t)lo;
     vals[i] = (uint32_t)i;
 }
 
-hipError_t launch_keys(const GView &g, const Consts &k, uint64_t *keys, uint32_t *vals,
-                       uint32_t *bucket_hist, long long *counters, hipStream_t s)
+hipError_t launch_keys(const GView &g, const Consts &k, uint64_t *keys, uint32_t *vals, hipStream_t s)
 {
     const int64_t blocks = (g.n + 255) / 256;
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_keys, dim3((unsigned)blocks), dim3(256), 0, s, g, k, keys, vals, bucket_hist, counters);
+    hipLaunchKernelGGL(k_keys, dim3((unsigned)blocks), dim3(256), 0, s, g, k, keys, vals);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------
-// Stable LSD radix sort, 8-bit digits.  Each block owns ITEMS x 256 consecutive keys: 16 per
-// thread, or 4 for up to 32768 keys, where more, shorter blocks finish each pass sooner.
+// Stable LSD radix sort, 8-bit digits.  Each wavefront owns a run of consecutive keys and ranks
+// them by ballots with its own running counts, so a digit takes two barriers, not one per row of
+// keys.  Bound by latency.  Up to SORT_ONE keys: one work-group sorts them in LDS, all digits in one
+// launch.  More: per digit a histogram and a scatter, where every block owns SORT_TILE keys and adds
+// up the rows (256 counts per block) before its own itself; counting the next digit while
+// scattering took longer (global atomics: 14 us per digit of 1e4 keys).
 // ---------------------------------------------------------------------------------
-constexpr int SORT_THREADS = 256;
-static int sort_items(int64_t n) { return n <= 32768 ? 4 : 16; }
-int sort_blocks_for(int64_t n)
+constexpr int SORT_THREADS = 1024, SORT_WAVES = SORT_THREADS / 64, SORT_ITEMS = 4;
+constexpr int SORT_TILE = SORT_THREADS * SORT_ITEMS;
+// what fits one CU's LDS: 10 bytes a key and the wavefronts' counts
+constexpr int SORT_ONE_ITEMS = 12, SORT_ONE = SORT_THREADS * SORT_ONE_ITEMS;
+// above this many blocks, adding up the rows in each of them (256 KiB read per 256 rows) takes
+// longer than a launch that does it once
+constexpr int SORT_SELF_SCAN = 512;
+static int sort_blocks(int64_t n) { return (int)std::max<int64_t>(1, (n + SORT_TILE - 1) / SORT_TILE); }
+int64_t sort_table_words(int64_t n) { return (int64_t)256 * sort_blocks(n); }
+
+// Rank of the lane's digit among the wavefront's keys so far; cnt is the wavefront's row of counts.
+static __device__ __forceinline__ uint32_t sort_rank(uint32_t *cnt, uint32_t dg, bool valid)
 {
-    const int64_t tile = (int64_t)SORT_THREADS * sort_items(n);
-    return (int)std::max<int64_t>(1, (n + tile - 1) / tile);
+    uint64_t same = __ballot(valid);
+#pragma unroll
+    for (int bit = 0; bit < 8; ++bit) {
+        const uint64_t bb = __ballot((dg >> bit) & 1u);
+        same &= ((dg >> bit) & 1u) ? bb : ~bb;
+    }
+    const uint32_t below = (uint32_t)rank_below(same), old = cnt[dg];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (valid && below == 0) cnt[dg] = old + (uint32_t)__popcll(same);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    return old + below;
+}
+
+// Exclusive prefix over the 256 digits (threads 0 ... 255; every thread calls).
+static __device__ __forceinline__ uint32_t sort_digit_scan(uint32_t v, uint32_t *s_wave, int tid, int lane)
+{
+    uint32_t incl = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(incl, o);
+        if (lane >= o) incl += t;
+    }
+    if (lane == 63 && tid < 256) s_wave[tid >> 6] = incl;
+    __syncthreads();
+    uint32_t base = 0;
+    for (int w = 0; w < (tid >> 6) && w < 4; ++w) base += s_wave[w];
+    return base + incl - v;
 }
 
 template <int ITEMS>
-__global__ void __launch_bounds__(SORT_THREADS) k_sort_hist(const uint64_t *__restrict__ keys, int64_t n, int shift,
-                                                            uint32_t *__restrict__ block_hist, int nblocks)
+__global__ void __launch_bounds__(SORT_THREADS) k_sort_one(const uint64_t *__restrict__ keys_in,
+                                                           const uint32_t *__restrict__ vals_in,
+                                                           uint64_t *__restrict__ keys_out, uint32_t *__restrict__ vals_out,
+                                                           int n, int first_digit, int last_digit)
 {
-    constexpr int SORT_ITEMS = ITEMS, SORT_TILE = SORT_THREADS * ITEMS;
-    __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * SORT_TILE;
-    for (int it = 0; it < SORT_ITEMS; ++it) {
-        const int64_t i = base + (int64_t)it * SORT_THREADS + threadIdx.x;
-        if (i < n) atomicAdd(&h[(uint32_t)(keys[i] >> shift) & 0xffu], 1u);
+    __shared__ uint64_t s_key[SORT_THREADS * ITEMS];
+    __shared__ uint16_t s_idx[SORT_THREADS * ITEMS];
+    __shared__ uint32_t s_off[SORT_WAVES][256];
+    __shared__ uint32_t s_wave[4];
+    __shared__ uint64_t s_diff[SORT_WAVES];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int base = wave * (64 * ITEMS) + lane;
+    uint64_t key[ITEMS];
+    uint32_t idx[ITEMS], rank[ITEMS];
+    uint64_t diff = 0;
+    const uint64_t key0 = keys_in[0];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int i = base + it * 64;
+        idx[it] = (uint32_t)i;
+        key[it] = i < n ? keys_in[i] : key0;
+        diff |= key[it] ^ key0;
     }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) diff |= __shfl_xor(diff, o);
+    if (lane == 0) s_diff[wave] = diff;
     __syncthreads();
-    block_hist[(int64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
+    diff = 0;
+#pragma unroll
+    for (int w = 0; w < SORT_WAVES; ++w) diff |= s_diff[w];
+    for (int dg = first_digit; dg <= last_digit; ++dg) {
+        const int shift = 8 * dg;
+        if (((diff >> shift) & 0xffu) == 0) continue;  // every key holds the same digit
+        for (int j = lane; j < 256; j += 64) s_off[wave][j] = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it)
+            rank[it] = sort_rank(s_off[wave], (uint32_t)(key[it] >> shift) & 0xffu, base + it * 64 < n);
+        __syncthreads();
+        uint32_t total = 0;
+        if (tid < 256)
+#pragma unroll
+            for (int w = 0; w < SORT_WAVES; ++w) total += s_off[w][tid];
+        uint32_t run = sort_digit_scan(total, s_wave, tid, lane);
+        if (tid < 256)
+#pragma unroll
+            for (int w = 0; w < SORT_WAVES; ++w) {
+                const uint32_t c = s_off[w][tid];
+                s_off[w][tid] = run;
+                run += c;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it)
+            if (base + it * 64 < n) {
+                const uint32_t pos = s_off[wave][(uint32_t)(key[it] >> shift) & 0xffu] + rank[it];
+                s_key[pos] = key[it];
+                s_idx[pos] = (uint16_t)idx[it];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it)
+            if (base + it * 64 < n) {
+                key[it] = s_key[base + it * 64];
+                idx[it] = s_idx[base + it * 64];
+            }
+    }
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it)
+        if (base + it * 64 < n) {
+            keys_out[base + it * 64] = key[it];
+            vals_out[base + it * 64] = vals_in[idx[it]];
+        }
 }
 
-// Exclusive scan of block_hist (digit-major) in place; one block of 1024 threads.
-__global__ void __launch_bounds__(1024) k_sort_scan(uint32_t *__restrict__ block_hist, int total)
+__global__ void __launch_bounds__(SORT_THREADS) k_sort_hist(const uint64_t *__restrict__ keys, int64_t n, int shift,
+                                                            uint32_t *__restrict__ table)
 {
-    __shared__ uint32_t part[1024];
-    const int per = (total + 1023) / 1024;
-    const int b = threadIdx.x * per;
-    uint32_t sum = 0;
-    for (int j = 0; j < per && b + j < total; ++j) sum += block_hist[b + j];
-    part[threadIdx.x] = sum;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const uint32_t v = threadIdx.x >= off ? part[threadIdx.x - off] : 0u;
-        __syncthreads();
-        part[threadIdx.x] += v;
-        __syncthreads();
+    __shared__ uint32_t s_cnt[SORT_WAVES][256];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int j = lane; j < 256; j += 64) s_cnt[wave][j] = 0;
+    uint64_t key[SORT_ITEMS];
+#pragma unroll
+    for (int it = 0; it < SORT_ITEMS; ++it) {
+        const int64_t i = (int64_t)blockIdx.x * SORT_TILE + it * SORT_THREADS + tid;
+        key[it] = i < n ? keys[i] : 0;
     }
-    uint32_t run = part[threadIdx.x] - sum;
-    for (int j = 0; j < per && b + j < total; ++j) {
-        const uint32_t v = block_hist[b + j];
-        block_hist[b + j] = run;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int it = 0; it < SORT_ITEMS; ++it)
+        sort_rank(s_cnt[wave], (uint32_t)(key[it] >> shift) & 0xffu,
+                  (int64_t)blockIdx.x * SORT_TILE + it * SORT_THREADS + tid < n);
+    __syncthreads();
+    if (tid < 256) {
+        uint32_t v = 0;
+#pragma unroll
+        for (int w = 0; w < SORT_WAVES; ++w) v += s_cnt[w][tid];
+        table[(int64_t)blockIdx.x * 256 + tid] = v;
+    }
+}
+
+// Thread 256 q + d: sum of digit d over the rows of quarter q, and over those before `me`.
+static __device__ __forceinline__ void sort_rows(const uint32_t *__restrict__ table, int nb, int me, int d, int q,
+                                                 uint32_t &total, uint32_t &before)
+{
+    const int r0 = nb * q >> 2, r1 = nb * (q + 1) >> 2;
+    total = before = 0;
+#pragma unroll 8
+    for (int r = r0; r < r1; ++r) {
+        const uint32_t v = table[(int64_t)r * 256 + d];
+        total += v;
+        before += r < me ? v : 0u;
+    }
+}
+
+// Many blocks: the table's rows become output offsets, in one block.
+__global__ void __launch_bounds__(SORT_THREADS) k_sort_scan(uint32_t *__restrict__ table, int nb)
+{
+    __shared__ uint32_t part[4][256], s_wave[4];
+    const int tid = threadIdx.x, lane = tid & 63, d = tid & 255, q = tid >> 8;
+    uint32_t total, before;
+    sort_rows(table, nb, 0, d, q, total, before);
+    part[q][d] = total;
+    __syncthreads();
+    const uint32_t all = part[0][d] + part[1][d] + part[2][d] + part[3][d];
+    uint32_t run = sort_digit_scan(tid < 256 ? all : 0u, s_wave, tid, lane);
+    if (tid < 256)
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t v = part[j][d];
+            part[j][d] = run;
+            run += v;
+        }
+    __syncthreads();
+    run = part[q][d];
+    const int r0 = nb * q >> 2, r1 = nb * (q + 1) >> 2;
+    for (int r = r0; r < r1; ++r) {
+        const uint32_t v = table[(int64_t)r * 256 + d];
+        table[(int64_t)r * 256 + d] = run;
         run += v;
     }
 }
 
-template <int ITEMS>
+template <bool SCANNED>
 __global__ void __launch_bounds__(SORT_THREADS) k_sort_scatter(const uint64_t *__restrict__ keys_in,
                                                                const uint32_t *__restrict__ vals_in,
                                                                uint64_t *__restrict__ keys_out,
-                                                               uint32_t *__restrict__ vals_out, int64_t n,
-                                                               int shift, const uint32_t *__restrict__ block_hist,
-                                                               int nblocks)
+                                                               uint32_t *__restrict__ vals_out, int64_t n, int shift,
+                                                               const uint32_t *__restrict__ table)
 {
-    constexpr int SORT_ITEMS = ITEMS, SORT_TILE = SORT_THREADS * ITEMS;
-    __shared__ uint32_t run[256];          // running output offset per digit for this block
-    __shared__ uint32_t wave_cnt[SORT_THREADS / 64][256];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    run[threadIdx.x] = block_hist[(int64_t)threadIdx.x * nblocks + blockIdx.x];
-    const int64_t base = (int64_t)blockIdx.x * SORT_TILE;
+    __shared__ uint32_t s_off[SORT_WAVES][256];  // per wavefront: digit counts, then output offsets
+    __shared__ uint32_t s_part[2][4][256], s_wave[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, d = tid & 255, q = tid >> 8;
+    const int nb = gridDim.x, me = blockIdx.x;
+    const int64_t base = (int64_t)me * SORT_TILE + wave * (64 * SORT_ITEMS) + lane;
+    uint64_t key[SORT_ITEMS];
+    uint32_t val[SORT_ITEMS], rank[SORT_ITEMS];
+#pragma unroll
     for (int it = 0; it < SORT_ITEMS; ++it) {
-        const int64_t i = base + (int64_t)it * SORT_THREADS + threadIdx.x;
-        const bool valid = i < n;
-        uint64_t key = valid ? keys_in[i] : 0;
-        const uint32_t val = valid ? vals_in[i] : 0;
-        const uint32_t d = (uint32_t)(key >> shift) & 0xffu;
-        // lanes of this wave holding the same digit
-        uint64_t same = __ballot(valid);
-        for (int bit = 0; bit < 8; ++bit) {
-            const uint64_t bb = __ballot((d >> bit) & 1u);
-            same &= ((d >> bit) & 1u) ? bb : ~bb;
-        }
-        const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-        const uint32_t rank_in_wave = (uint32_t)__popcll(same & lt);
-        // zero the per-wave counts, then the lowest lane of each digit group publishes its size
-        for (int j = lane; j < 256; j += 64) wave_cnt[wave][j] = 0;
-        __syncthreads();
-        if (valid && rank_in_wave == 0) wave_cnt[wave][d] = (uint32_t)__popcll(same);
-        __syncthreads();
-        if (valid) {
-            uint32_t off = run[d];
-            for (int w = 0; w < wave; ++w) off += wave_cnt[w][d];
-            const uint32_t pos = off + rank_in_wave;
-            keys_out[pos] = key;
-            vals_out[pos] = val;
-        }
-        __syncthreads();
-        // advance the running offsets by this iteration's digit counts
-        {
-            uint32_t add = 0;
-            for (int w = 0; w < SORT_THREADS / 64; ++w) add += wave_cnt[w][threadIdx.x];
-            run[threadIdx.x] += add;
-        }
-        __syncthreads();
+        const int64_t i = base + it * 64;
+        key[it] = i < n ? keys_in[i] : 0;
+        val[it] = i < n ? vals_in[i] : 0;
     }
+    uint32_t total = 0, before = 0;
+    if (SCANNED) {
+        if (q == 0) before = table[(int64_t)me * 256 + d];
+    } else {
+        sort_rows(table, nb, me, d, q, total, before);
+        s_part[0][q][d] = total;
+        s_part[1][q][d] = before;
+    }
+    for (int j = lane; j < 256; j += 64) s_off[wave][j] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int it = 0; it < SORT_ITEMS; ++it)
+        rank[it] = sort_rank(s_off[wave], (uint32_t)(key[it] >> shift) & 0xffu, base + it * 64 < n);
+    __syncthreads();
+    uint32_t run = before;
+    if (!SCANNED) {
+        total = s_part[0][0][d] + s_part[0][1][d] + s_part[0][2][d] + s_part[0][3][d];
+        before = s_part[1][0][d] + s_part[1][1][d] + s_part[1][2][d] + s_part[1][3][d];
+        run = before + sort_digit_scan(tid < 256 ? total : 0u, s_wave, tid, lane);
+    }
+    if (tid < 256)
+        for (int w = 0; w < SORT_WAVES; ++w) {
+            const uint32_t c = s_off[w][d];
+            s_off[w][d] = run;
+            run += c;
+        }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < SORT_ITEMS; ++it)
+        if (base + it * 64 < n) {
+            const uint32_t pos = s_off[wave][(uint32_t)(key[it] >> shift) & 0xffu] + rank[it];
+            keys_out[pos] = key[it];
+            vals_out[pos] = val[it];
+        }
 }
 
-hipError_t radix_sort_48(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, uint32_t *vals_b,
-                         uint32_t *block_hist, int64_t n, int nblocks, hipStream_t s, uint64_t **keys_out,
-                         uint32_t **vals_out)
+hipError_t radix_sort(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, uint32_t *vals_b, uint32_t *table,
+                      int64_t n, int first_digit, int last_digit, hipStream_t s, uint64_t **keys_out,
+                      uint32_t **vals_out)
 {
     uint64_t *ki = keys_a, *ko = keys_b;
     uint32_t *vi = vals_a, *vo = vals_b;
-    if (n > 0) {
-        if (nblocks != sort_blocks_for(n)) return hipErrorInvalidValue;   // the caller's histogram area
-        const bool small = sort_items(n) == 4;
-        for (int pass = 0; pass < 6; ++pass) {
-            const int shift = 8 * pass;
-            if (small)
-                hipLaunchKernelGGL(k_sort_hist<4>, dim3(nblocks), dim3(SORT_THREADS), 0, s, ki, n, shift, block_hist,
-                                   nblocks);
-            else
-                hipLaunchKernelGGL(k_sort_hist<16>, dim3(nblocks), dim3(SORT_THREADS), 0, s, ki, n, shift, block_hist,
-                                   nblocks);
-            hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(1024), 0, s, block_hist, 256 * nblocks);
-            if (small)
-                hipLaunchKernelGGL(k_sort_scatter<4>, dim3(nblocks), dim3(SORT_THREADS), 0, s, ki, vi, ko, vo, n, shift,
-                                   block_hist, nblocks);
-            else
-                hipLaunchKernelGGL(k_sort_scatter<16>, dim3(nblocks), dim3(SORT_THREADS), 0, s, ki, vi, ko, vo, n,
-                                   shift, block_hist, nblocks);
+    const dim3 block(SORT_THREADS);
+    if (n > SORT_ONE) {
+        const int nb = sort_blocks(n);
+        const dim3 grid(nb);
+        for (int dg = first_digit; dg <= last_digit; ++dg) {
+            hipLaunchKernelGGL(k_sort_hist, grid, block, 0, s, ki, n, 8 * dg, table);
+            if (nb > SORT_SELF_SCAN) {
+                hipLaunchKernelGGL(k_sort_scan, dim3(1), block, 0, s, table, nb);
+                hipLaunchKernelGGL(k_sort_scatter<true>, grid, block, 0, s, ki, vi, ko, vo, n, 8 * dg, table);
+            } else {
+                hipLaunchKernelGGL(k_sort_scatter<false>, grid, block, 0, s, ki, vi, ko, vo, n, 8 * dg, table);
+            }
             uint64_t *tk = ki; ki = ko; ko = tk;
             uint32_t *tv = vi; vi = vo; vo = tv;
         }
+    } else if (n > 0) {
+#define GWS_SORT_ONE(I) \
+    hipLaunchKernelGGL(k_sort_one<I>, dim3(1), block, 0, s, ki, vi, ko, vo, (int)n, first_digit, last_digit)
+        if (n <= SORT_THREADS) GWS_SORT_ONE(1);
+        else if (n <= 2 * SORT_THREADS) GWS_SORT_ONE(2);
+        else if (n <= 4 * SORT_THREADS) GWS_SORT_ONE(4);
+        else if (n <= 8 * SORT_THREADS) GWS_SORT_ONE(8);
+        else GWS_SORT_ONE(SORT_ONE_ITEMS);
+#undef GWS_SORT_ONE
+        ki = ko;
+        vi = vo;
     }
     *keys_out = ki;
     *vals_out = vi;
@@ -214,11 +387,20 @@ hipError_t radix_sort_48(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, u
 // ---------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_records(GView g, Consts k, const uint64_t *__restrict__ keys,
                                                   const uint32_t *__restrict__ vals, GRec *__restrict__ rec,
-                                                  int64_t n, const long long *__restrict__ counters, bool poly)
+                                                  int64_t n, uint32_t *__restrict__ bucket_end,
+                                                  long long *__restrict__ counters, bool poly)
 {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nvalid = n - counters[CTR_NCULLED];
-    if (s >= nvalid) return;
+    if (s >= n) return;
+    const uint32_t hi = (uint32_t)(keys[s] >> 32);
+    if (hi == KEY_CULLED) {
+        if (s == 0) counters[CTR_NCULLED] = n;
+        return;
+    }
+    // where the keys change: the end of the bucket, of the valid Gaussians
+    const uint32_t after = s + 1 < n ? (uint32_t)(keys[s + 1] >> 32) : KEY_CULLED;
+    if (after == KEY_CULLED) counters[CTR_NCULLED] = n - (s + 1);
+    if (k.forward && after != hi) bucket_end[NBUCKET - 1 - hi] = (uint32_t)(s + 1);
     const int64_t i = vals[s];
     const double sxx = g.cov_xx[i], sxy = g.cov_xy[i], syy = g.cov_yy[i];
     const double det = sxx * syy - sxy * sxy;
@@ -261,11 +443,11 @@ __global__ void __launch_bounds__(256) k_records(GView g, Consts k, const uint64
 }
 
 hipError_t launch_records(const GView &g, const Consts &k, const uint64_t *keys, const uint32_t *vals,
-                          GRec *rec, int64_t n, const long long *counters, bool poly, hipStream_t s)
+                          GRec *rec, int64_t n, uint32_t *bucket_end, long long *counters, bool poly, hipStream_t s)
 {
     const int64_t blocks = (n + 255) / 256;
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_records, dim3((unsigned)blocks), dim3(256), 0, s, g, k, keys, vals, rec, n, counters, poly);
+    hipLaunchKernelGGL(k_records, dim3((unsigned)blocks), dim3(256), 0, s, g, k, keys, vals, rec, n, bucket_end, counters, poly);
     return hipGetLastError();
 }
 
@@ -293,7 +475,7 @@ static __device__ uint32_t block_excl_scan_1024(uint32_t v, uint32_t *tmp, uint3
 }
 
 __global__ void __launch_bounds__(1024) k_bin_forward(const int32_t *__restrict__ tile_bucket, int ntiles,
-                                                      const uint32_t *__restrict__ bucket_hist, uint32_t *__restrict__ cum,
+                                                      const uint32_t *__restrict__ bucket_end, uint32_t *__restrict__ cum,
                                                       int32_t *__restrict__ tile_L, int2 *__restrict__ tile_slots,
                                                       Item *__restrict__ items,
                                                       int64_t max_items, int64_t max_slots, int base_chunk,
@@ -302,17 +484,23 @@ __global__ void __launch_bounds__(1024) k_bin_forward(const int32_t *__restrict_
     __shared__ uint32_t tmp[1024];
     __shared__ unsigned long long red[1024];
     __shared__ int32_t chunk_sh;
-    uint32_t total;
-    // suffix sums over buckets: cum[b] = #valid Gaussians with bucket >= b
+    // cum[b] = number of valid Gaussians with bucket >= b: the largest end at or above b
     {
         const int per = NBUCKET / 1024;
         const int b0 = (1023 - threadIdx.x) * per;  // thread 0 owns the highest buckets
-        uint32_t s = 0;
-        for (int j = 0; j < per; ++j) s += bucket_hist[b0 + j];
-        const uint32_t ex = block_excl_scan_1024(s, tmp, &total);
-        uint32_t run = ex;
+        uint32_t m = 0;
+        for (int j = 0; j < per; ++j) m = max(m, bucket_end[b0 + j]);
+        tmp[threadIdx.x] = m;
+        __syncthreads();
+        for (int off = 1; off < 1024; off <<= 1) {
+            const uint32_t t = threadIdx.x >= off ? tmp[threadIdx.x - off] : 0u;
+            __syncthreads();
+            tmp[threadIdx.x] = max(tmp[threadIdx.x], t);
+            __syncthreads();
+        }
+        uint32_t run = threadIdx.x ? tmp[threadIdx.x - 1] : 0u;
         for (int j = per - 1; j >= 0; --j) {
-            run += bucket_hist[b0 + j];
+            run = max(run, bucket_end[b0 + j]);
             cum[b0 + j] = run;
         }
     }
@@ -373,11 +561,11 @@ __global__ void __launch_bounds__(1024) k_bin_forward(const int32_t *__restrict_
     }
 }
 
-hipError_t launch_bin_forward(const Plan &p, const uint32_t *bucket_hist, uint32_t *cum, int32_t *tile_L,
+hipError_t launch_bin_forward(const Plan &p, const uint32_t *bucket_end, uint32_t *cum, int32_t *tile_L,
                               int2 *tile_slots, Item *items, int64_t max_items, int64_t max_slots, int base_chunk,
                               long long *counters, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_bin_forward, dim3(1), dim3(1024), 0, s, p.tile_bucket, p.ntiles, bucket_hist, cum, tile_L,
+    hipLaunchKernelGGL(k_bin_forward, dim3(1), dim3(1024), 0, s, p.tile_bucket, p.ntiles, bucket_end, cum, tile_L,
                        tile_slots, items, max_items, max_slots, base_chunk, counters);
     return hipGetLastError();
 }
@@ -402,7 +590,7 @@ __global__ void __launch_bounds__(1024) k_bin_backward(const int32_t *__restrict
     __shared__ int32_t trb_sh, nr_sh;
     const int64_t nvalid = n - counters[CTR_NCULLED];
     const int nchunks = (int)((nvalid + chunk - 1) / chunk);
-    auto K_of = [&](int b) { return tile_cum[NBUCKET - 1 - (int)(keys[(int64_t)b * chunk] >> 32)]; };
+    auto K_of = [&](int b) { return tile_cum[bwd_level_bucket(BWD_LEVELS - (int)(keys[(int64_t)b * chunk] >> 42))]; };
     unsigned long long sumK = 0;
     for (int b = threadIdx.x; b < nchunks; b += 1024) sumK += (unsigned long long)K_of(b);
     red[threadIdx.x] = sumK;
@@ -480,11 +668,11 @@ hipError_t launch_bin_backward(const Plan &p, const uint64_t *keys, BItem *bitem
     return hipGetLastError();
 }
 
-__global__ void k_zero_counters(long long *__restrict__ counters, uint32_t *__restrict__ bucket_hist)
+__global__ void k_zero_counters(long long *__restrict__ counters, uint32_t *__restrict__ bucket_end)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t < CTR_COUNT) counters[t] = 0;
-    if (t < NBUCKET) bucket_hist[t] = 0;
+    if (t < NBUCKET) bucket_end[t] = 0;
 }
 
 __global__ void k_copy_counters(const long long *__restrict__ src, long long *__restrict__ dst)
@@ -493,9 +681,9 @@ __global__ void k_copy_counters(const long long *__restrict__ src, long long *__
     if (t < CTR_COUNT) dst[t] = src[t];
 }
 
-hipError_t launch_zero_counters(long long *counters, uint32_t *bucket_hist, hipStream_t s)
+hipError_t launch_zero_counters(long long *counters, uint32_t *bucket_end, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_zero_counters, dim3(NBUCKET / 256), dim3(256), 0, s, counters, bucket_hist);
+    hipLaunchKernelGGL(k_zero_counters, dim3(NBUCKET / 256), dim3(256), 0, s, counters, bucket_end);
     return hipGetLastError();
 }
 

@@ -418,9 +418,10 @@ __global__ void __launch_bounds__(adj_wg(C, DEPTH), adj_waves_per_simd(C, DEPTH)
 
 // Which adjoint runs.  The matrix-core one needs every grid frequency to propagate; on smaller grids
 // supports cover few sub-tiles and more Gaussians fail the separable form's tests.  Backward,
-// this kernel against the matrix-core one (ms): 300 Gaussians at 1000 x 750, one wavelength 0.360
-// against 0.402; 5000, three wavelengths 0.840 against 0.868; 20000 at 1280 x 1024, two 1.68
-// against 1.21; 1000 at 1920 x 1080, three 1.14 against 0.98; 1e5 12.3 against 7.6.
+// this kernel against the matrix-core one, 300 / 3000 / 30000 Gaussians (ms): 800 x 600, one
+// wavelength 0.17 / 0.27 / 0.67 against 0.25 / 0.44 / 0.90; 1000 x 750 0.20 / 0.32 / 0.88 against 0.23 /
+// 0.37 / 0.80; 1280 x 800 0.215 / 0.35 / 1.14 against 0.217 / 0.32 / 0.90, three wavelengths 0.37 / 0.66 /
+// 2.13 against 0.34 / 0.53 / 1.51; 1920 x 1080, three 0.48 / 0.83 / 3.99 against 0.39 / 0.59 / 2.48.
 bool adjoint_on_mfma(const Consts &k)
 {
     return !grid_has_evanescent(k) && (int64_t)k.nx * k.ny >= (int64_t)ADJ_MFMA_POINTS;
@@ -466,18 +467,48 @@ int adjoint_occupancy(const Consts &k)
     return nb;
 }
 
-// Per Gaussian: sum the item partials of its chunk in order (FP64), then the chain rule.  The
-// number of sums is a compile-time constant of the variant, so they stay in registers.
+// Per Gaussian: sum the item partials of its chunk (FP64, a fixed order), then the chain rule.  A
+// work-group takes 64 Gaussians, each wavefront every eighth partial of theirs: one thread summing
+// all of them waited on a chain of up to hundreds of loads (1e4 Gaussians at 1280 x 1024: 230 us, 42
+// now, of which the partials' 117 MB take 25).  The number of sums is a compile-time constant of
+// the variant, so they stay in registers.
+constexpr int GF_SLICES = 8;
 template <int C, bool DEPTH>
-__global__ void __launch_bounds__(256) k_grad_final(GView g, Consts k, const uint32_t *__restrict__ vals,
-                                                    const int2 *__restrict__ chunk_items,
-                                                    const int32_t *__restrict__ range_base,
-                                                    const float *__restrict__ bpartials, GradView grads, int64_t n,
-                                                    const long long *__restrict__ counters, int chunk)
+__global__ void __launch_bounds__(64 * GF_SLICES) k_grad_final(GView g, Consts k, const uint32_t *__restrict__ vals,
+                                                               const int2 *__restrict__ chunk_items,
+                                                               const int32_t *__restrict__ range_base,
+                                                               const float *__restrict__ bpartials, GradView grads,
+                                                               int64_t n, const long long *__restrict__ counters, int chunk)
 {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
+    constexpr int NV = adj_nv(C, DEPTH);
+    __shared__ double s_acc[GF_SLICES - 1][NV][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t s0 = (int64_t)blockIdx.x * 64, s = s0 + lane;
     const int64_t nvalid = n - counters[CTR_NCULLED];
+    double acc[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) acc[v] = 0.0;
+    if (s0 < nvalid) {
+        // chunks are multiples of 64 Gaussians: the work-group's share one
+        const int64_t b = s0 / chunk;
+        const int t = (int)(s0 - b * chunk) + lane;
+        const int nk = chunk_items[b].y;
+        const long long nbitems = counters[CTR_NBITEMS];
+#pragma unroll 4
+        for (int j = wave; j < nk; j += GF_SLICES) {
+            const int64_t it = (int64_t)range_base[j] + b;  // range j of chunk b
+            if (it >= nbitems) break;
+            const float *src = bpartials + (it * chunk + t) * NV;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) acc[v] += (double)src[v];
+        }
+    }
+    if (wave) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) s_acc[wave - 1][v][lane] = acc[v];
+    }
+    __syncthreads();
+    if (wave || s >= n) return;
     const int64_t i = vals[s];
     if (s >= nvalid) {
         grads.mean_x[i] = grads.mean_y[i] = 0.0f;
@@ -488,21 +519,10 @@ __global__ void __launch_bounds__(256) k_grad_final(GView g, Consts k, const uin
         for (int c = 0; c < C; ++c) grads.amplitude[(int64_t)c * grads.amp_stride + i] = 0.0f;
         return;
     }
-    constexpr int NV = adj_nv(C, DEPTH);
-    const int64_t b = s / chunk;
-    const int t = (int)(s - b * chunk);
-    const int2 ci = chunk_items[b];
-    const long long nbitems = counters[CTR_NBITEMS];
-    double acc[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) acc[v] = 0.0;
-    for (int j = 0; j < ci.y; ++j) {
-        const int64_t it = (int64_t)range_base[j] + b;  // range j of chunk b
-        if (it >= nbitems) break;
-        const float *src = bpartials + (it * chunk + t) * NV;
+    for (int w = 0; w < GF_SLICES - 1; ++w)
 #pragma unroll
-        for (int v = 0; v < NV; ++v) acc[v] += (double)src[v];
-    }
+        for (int v = 0; v < NV; ++v) acc[v] += s_acc[w][v][lane];
     const double PI = 3.14159265358979323846;
     const double sxx = g.cov_xx[i], sxy = g.cov_xy[i], syy = g.cov_yy[i];
     const double det = sxx * syy - sxy * sxy;
@@ -542,7 +562,7 @@ hipError_t launch_grad_final(const GView &g, const Consts &k, const uint32_t *va
                              const long long *counters, int chunk, hipStream_t s)
 {
     if (n == 0) return hipSuccess;
-    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    const dim3 grid((unsigned)((n + 63) / 64)), block(64 * GF_SLICES);
 #define GWS_GF(CC, DD)                                                                                                  \
     hipLaunchKernelGGL((k_grad_final<CC, DD>), grid, block, 0, s, g, k, vals, chunk_items, range_base, bpartials, grads, \
                        n, counters, chunk)

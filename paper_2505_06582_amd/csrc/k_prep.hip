@@ -577,8 +577,11 @@ hipError_t launch_bin_forward(const Plan &p, const uint32_t *bucket_end, uint32_
 // ordered range-major -- range r of every chunk that has one, then range r + 1 -- so the
 // wavefronts in flight at any time read the same tiles of the field gradient (L2 reuse).
 // Because K_b does not increase with b (chunks are sorted by support radius), the chunks
-// that have range r form a prefix [0, P_r) and item (r, b) sits at range_base[r] + b.
+// that have range r form a prefix [0, P_r) and item (r, b) sits at range_base[r] + b.  Bound by
+// latency: with the bisection in global memory and a thread writing all of its chunk's items
+// 20 chunks took 88 us, 13 now.
 // ---------------------------------------------------------------------------------
+constexpr int BWD_K_LDS = 4096;
 __global__ void __launch_bounds__(1024) k_bin_backward(const int32_t *__restrict__ tile_cum,
                                                        const uint64_t *__restrict__ keys, BItem *__restrict__ bitems,
                                                        int2 *__restrict__ chunk_items, int32_t *__restrict__ range_base,
@@ -588,9 +591,16 @@ __global__ void __launch_bounds__(1024) k_bin_backward(const int32_t *__restrict
     __shared__ uint32_t tmp[1024];
     __shared__ unsigned long long red[1024];
     __shared__ int32_t trb_sh, nr_sh;
+    __shared__ int32_t s_K[BWD_K_LDS];
     const int64_t nvalid = n - counters[CTR_NCULLED];
     const int nchunks = (int)((nvalid + chunk - 1) / chunk);
-    auto K_of = [&](int b) { return tile_cum[bwd_level_bucket(BWD_LEVELS - (int)(keys[(int64_t)b * chunk] >> 42))]; };
+    // K_b of the first chunks (all of them up to 2 million Gaussians) in LDS: the bisection below reads them
+    for (int b = threadIdx.x; b < min(nchunks, BWD_K_LDS); b += 1024)
+        s_K[b] = tile_cum[bwd_level_bucket(BWD_LEVELS - (int)(keys[(int64_t)b * chunk] >> 42))];
+    __syncthreads();
+    auto K_of = [&](int b) {
+        return b < BWD_K_LDS ? s_K[b] : tile_cum[bwd_level_bucket(BWD_LEVELS - (int)(keys[(int64_t)b * chunk] >> 42))];
+    };
     unsigned long long sumK = 0;
     for (int b = threadIdx.x; b < nchunks; b += 1024) sumK += (unsigned long long)K_of(b);
     red[threadIdx.x] = sumK;
@@ -637,21 +647,22 @@ __global__ void __launch_bounds__(1024) k_bin_backward(const int32_t *__restrict
     }
     if (threadIdx.x == 0) range_base[NR] = (int32_t)base;
     __syncthreads();
-    for (int b = threadIdx.x; b < nchunks; b += 1024) {
-        const int K = K_of(b);
-        const int nk = min((K + TRB - 1) / TRB, NR);
-        chunk_items[b] = make_int2(0, nk);
-        for (int r = 0; r < nk; ++r) {
-            const int64_t it = (int64_t)range_base[r] + b;
-            if (it < max_bitems) {
+    for (int b = threadIdx.x; b < nchunks; b += 1024) chunk_items[b] = make_int2(0, min((K_of(b) + TRB - 1) / TRB, NR));
+    // items: W threads take the chunks of a range, the work-group's 1024 / W groups its ranges
+    int lw = 0;
+    while (lw < 10 && (1 << lw) < nchunks) ++lw;
+    for (int r = threadIdx.x >> lw; r < NR; r += 1024 >> lw) {
+        const int64_t at = range_base[r];
+        const int P = range_base[r + 1] - (int)at;
+        for (int b = threadIdx.x & ((1 << lw) - 1); b < P; b += 1 << lw)
+            if (at + b < max_bitems) {
                 BItem e;
                 e.chunk = b;
                 e.k0 = r * TRB;
-                e.k1 = min((r + 1) * TRB, K);
-                e.slot = (int32_t)it;
-                bitems[it] = e;
+                e.k1 = min((r + 1) * TRB, K_of(b));
+                e.slot = (int32_t)(at + b);
+                bitems[at + b] = e;
             }
-        }
     }
     if (threadIdx.x == 0) {
         counters[CTR_NBITEMS] = (long long)(base < max_bitems ? base : max_bitems);
@@ -660,8 +671,8 @@ __global__ void __launch_bounds__(1024) k_bin_backward(const int32_t *__restrict
 }
 
 hipError_t launch_bin_backward(const Plan &p, const uint64_t *keys, BItem *bitems, int2 *chunk_items,
-                               int32_t *range_base, int max_ranges, int64_t max_bitems, long long *counters, int64_t n,
-                               int chunk, hipStream_t s)
+                               int32_t *range_base, int max_ranges, int64_t max_bitems,
+                               long long *counters, int64_t n, int chunk, hipStream_t s)
 {
     hipLaunchKernelGGL(k_bin_backward, dim3(1), dim3(1024), 0, s, p.tile_cum, keys, bitems, chunk_items, range_base,
                        max_ranges, max_bitems, counters, n, chunk);

@@ -76,7 +76,7 @@ typedef enum gws_status {
  * gws_autotune returns GWS_ERR_UNSUPPORTED for it (it has no tiling). */
 typedef enum gws_blend { GWS_BLEND_OIT = 0, GWS_BLEND_EXACT = 1 } gws_blend;
 
-/* Inverse transform: mixed-radix FP32 FFT, or the DFT as two dense complex GEMMs on the
+/* Inverse transform: mixed-radix FP32 FFT, or the DFT by dense products on the
  * matrix cores with bf16 hi/lo operand splitting (three products, FP32 accumulation). */
 typedef enum gws_xform { GWS_XFORM_FFT_FP32 = 0, GWS_XFORM_DFT_BF16X3 = 1 } gws_xform;
 

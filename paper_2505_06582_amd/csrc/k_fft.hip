@@ -433,13 +433,14 @@ static __device__ __forceinline__ int xcd_contiguous(int i, int G)
     return x * q + min(x, r) + j;
 }
 
-// With INTENSITY the results are not stored: |x|^2 goes to outf (float, same indexing).
+// With INTENSITY the results are not stored: |x|^2 goes to outf (float, same indexing).  Without
+// colwin, rows zero0 ... zero1 - 1 are zero and are not loaded.
 template <int S, bool INTENSITY, int LDSB>
 __global__ void __launch_bounds__(FFT_COL_THREADS, LDSB == FFT_COL_LDS_SMALL ? 4 : 2) k_fft_cols(const float2 *__restrict__ in, float2 *__restrict__ out,
                                                               RadixPlan pl, const float2 *__restrict__ tw, int width,
                                                               int lb, const int4 *__restrict__ colwin,
                                                               float *__restrict__ outf,
-                                                              const int4 *__restrict__ rowin)
+                                                              const int4 *__restrict__ rowin, int zero0, int zero1)
 {
     extern __shared__ float2 lds[];
     const int n = pl.n, B = 1 << lb;
@@ -474,7 +475,7 @@ __global__ void __launch_bounds__(FFT_COL_THREADS, LDSB == FFT_COL_LDS_SMALL ? 4
     } else {
         for (int i = threadIdx.x; i < n * B; i += FFT_COL_THREADS) {
             const int r = i >> lb, c = i & (B - 1);
-            lds[i] = c < bw ? src[(int64_t)r * width + c0 + c] : make_float2(0.0f, 0.0f);
+            lds[i] = c < bw && (r < zero0 || r >= zero1) ? src[(int64_t)r * width + c0 + c] : make_float2(0.0f, 0.0f);
         }
     }
     __syncthreads();
@@ -514,7 +515,9 @@ __global__ void __launch_bounds__(FFT_COL_THREADS, LDSB == FFT_COL_LDS_SMALL ? 4
 // in FP64 (Eq. 4 without cancellation), and then for every plane k multiplies the row by
 // H(nu, z_k) = exp(j 2 pi (frac(z_k / lambda_c) + z_k d_c(nu))) (zero outside the propagating
 // band and, with the half-band filter, outside |m'_x| < N_x / 4, |m'_y| < N_y / 4), times the
-// 1 / (N_x N_y) of the inverse, transforms it and stores it to plane k.
+// 1 / (N_x N_y) of the inverse, transforms it and stores it to plane k.  Rows outside the half band
+// are zero and neither formed nor read again: 8 planes of 1920 x 1080 x 3 with the filter take
+// 334 us in this and the column pass, 463 when they were.
 constexpr int STACK_MAXPT = 16;  // row elements per thread: N_x <= 16 * FFT_THREADS
 template <int S, int NPT>
 __global__ void __launch_bounds__(FFT_THREADS) k_fft_rows_stack(const float2 *__restrict__ spec,
@@ -526,7 +529,7 @@ __global__ void __launch_bounds__(FFT_THREADS) k_fft_rows_stack(const float2 *__
     const int row = blockIdx.x, c = row / ny, y = row - c * ny;
     const int myp = y < ny / 2 ? y : y - ny;
     const double nuy = (double)myp * sa.dnuy, il = sa.inv_l[c];
-    const bool yin = !sa.half_band || 4 * abs(myp) < ny;
+    if (sa.half_band && 4 * abs(myp) >= ny) return;  // zero: the column pass does not read the row
     float2 sv[NPT];
     double dv[NPT];
     bool keep[NPT];
@@ -541,7 +544,7 @@ __global__ void __launch_bounds__(FFT_THREADS) k_fft_rows_stack(const float2 *__
             const double nux = (double)mxp * sa.dnux;
             const double nu2 = fma(nux, nux, nuy * nuy);
             const double w2 = fma(il, il, -nu2);
-            keep[j] = w2 > 0.0 && yin && (!sa.half_band || 4 * abs(mxp) < nx);
+            keep[j] = w2 > 0.0 && (!sa.half_band || 4 * abs(mxp) < nx);
             if (keep[j]) {
                 dv[j] = -nu2 / (il + sqrt(w2));
                 sv[j] = spec[(int64_t)row * nx + i];
@@ -667,7 +670,7 @@ static void rows_launch(const Plan &p, const RadixPlan &px, int rows, const floa
 // One column pass over nimg images [ny][nx] in place (or, with intensity, |x|^2 to it).
 template <int S, bool INTENSITY>
 static void cols_launch(const Plan &p, const RadixPlan &py, int nimg, float2 *buf, const int4 *colwin, float *outf,
-                        hipStream_t s, const int4 *rowin = nullptr)
+                        hipStream_t s, const int4 *rowin = nullptr, int zero0 = 0, int zero1 = 0)
 {
     const ColCfg c = col_config(p.ny);
     const size_t lds = (size_t)(c.B + 1) * p.ny * sizeof(float2);
@@ -675,10 +678,10 @@ static void cols_launch(const Plan &p, const RadixPlan &py, int nimg, float2 *bu
     const dim3 grid(nimg * nslab), block(FFT_COL_THREADS);
     if (c.ldsb == FFT_COL_LDS_SMALL)
         hipLaunchKernelGGL((k_fft_cols<S, INTENSITY, FFT_COL_LDS_SMALL>), grid, block, lds, s, buf, buf, py, p.tw_y,
-                           p.nx, c.lb, colwin, outf, rowin);
+                           p.nx, c.lb, colwin, outf, rowin, zero0, zero1);
     else
         hipLaunchKernelGGL((k_fft_cols<S, INTENSITY, FFT_COL_LDS_BIG>), grid, block, lds, s, buf, buf, py, p.tw_y,
-                           p.nx, c.lb, colwin, outf, rowin);
+                           p.nx, c.lb, colwin, outf, rowin, zero0, zero1);
 }
 
 hipError_t launch_fft2d(const Plan &p, int batch, int direction, const float2 *in, float2 *out, hipStream_t s)
@@ -760,10 +763,12 @@ hipError_t launch_focal_stack(const Plan &p, const float2 *spec, float2 *planes,
         hipLaunchKernelGGL((k_fft_rows_stack<-1, 8>), g, b, row_lds, s, spec, planes, px, p.tw_x, sa);
     else
         hipLaunchKernelGGL((k_fft_rows_stack<-1, STACK_MAXPT>), g, b, row_lds, s, spec, planes, px, p.tw_x, sa);
+    // rows y with 4 |m'_y| >= N_y, which the row pass leaves out
+    const int zero0 = sa.half_band ? (p.ny + 3) / 4 : 0, zero1 = sa.half_band ? p.ny - zero0 + 1 : 0;
     if (intensity)
-        cols_launch<-1, true>(p, py, sa.K * sa.C, planes, nullptr, intensity, s);
+        cols_launch<-1, true>(p, py, sa.K * sa.C, planes, nullptr, intensity, s, nullptr, zero0, zero1);
     else
-        cols_launch<-1, false>(p, py, sa.K * sa.C, planes, nullptr, nullptr, s);
+        cols_launch<-1, false>(p, py, sa.K * sa.C, planes, nullptr, nullptr, s, nullptr, zero0, zero1);
     return hipGetLastError();
 }
 

@@ -993,6 +993,7 @@ __global__ void __launch_bounds__(256) k_tilt_grad_final(TView g, Consts k, cons
 
 static int tilt_queue_len(int nx, int ny);
 
+constexpr int TILT_ADJ_ITEMS = 8;
 template <int C>
 static hipError_t launch_tilt_adjoint_c(const Consts &k, const TRec *rec, const int2 *rect, int64_t n,
                                         const float2 *gspec, const int64_t *off, float *part, long long *counters,
@@ -1002,9 +1003,15 @@ static hipError_t launch_tilt_adjoint_c(const Consts &k, const TRec *rec, const 
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void *)k_tilt_adjoint<C>, TWG, 0) != hipSuccess ||
         nb < 1)
         nb = 1;
-    // each tile's Gaussians split into parts taken as separate items (each (Gaussian, tile) slot
-    // is still written once), so the tiles every support crowds do not hold the launch's tail
-    const int nparts = tilt_parts(n);
+    // Each tile's Gaussians split into parts taken as separate items (each (Gaussian, tile) slot is
+    // still written once, with the same bits), so the tiles many supports reach do not hold the
+    // launch's tail: eight items per resident work-group, of 512 Gaussians at least (building the
+    // tile's tables costs as much as four Gaussians' sums over it).  Backward of 12000 at 640 x 480 x 3:
+    // 4.71 -> 1.11 ms (one part per 8192: 300 items), 40000 at 256 x 256 2.09 -> 0.59, 12000 at 1920 x 1080 x 3
+    // 4.88 -> 4.61; four items per work-group: 10.2 ms for 40000 at 1280 x 1024 x 3, eight 9.8.
+    const int tiles = ((k.nx + TT - 1) / TT) * ((k.ny + TT - 1) / TT);
+    int nparts = (int)std::min<int64_t>(std::max(1, TILT_ADJ_ITEMS * n_cu * nb / tiles), (n + 511) / 512);
+    nparts = std::max(nparts, 1);
     const int nq = tilt_queue_len(k.nx, k.ny) * nparts;
     const int grid = std::max(1, std::min(n_cu * nb, nq));
     hipLaunchKernelGGL(k_tilt_adjoint<C>, dim3(grid), dim3(TWG), 0, s, k, rec, rect, n, gspec, off, part, nq, nparts,

@@ -363,7 +363,11 @@ static Layout make_layout(const gws_problem *p, int64_t n, int f_fwd, int f_bwd,
     // GPU's ~512 work-group slots -- short enough that the heaviest (the widest supports near
     // DC) do not leave the launch's tail to a few work-groups, for small scenes as for large
     // (1k Gaussians at 1080 x 1920 x 3: fwd+bwd 4.2 -> 1.8 ms; 100k: 21.1 -> 20.7 ms)
-    const int64_t nchunks = (n + ADJ_MIN_CHUNK - 1) / ADJ_MIN_CHUNK;
+    const bool mfma = adjoint_on_mfma(make_consts(p, 0));
+    const int cap = adjoint_chunk_cap(p->nx, p->ny, n, mfma);
+    const int wg_d = std::min(adj_wg(C, true), cap), wg_n = std::min(adj_wg(C, false), cap);
+    const int min_chunk = mfma ? std::min(ADJ_MFMA_G, cap) : std::min(wg_d, wg_n);
+    const int64_t nchunks = (n + min_chunk - 1) / min_chunk;
     L.max_bitems = nchunks + std::min<int64_t>(8192, nchunks * ntiles);   // no more items than (chunk, tile) pairs
     L.max_bslots = L.max_bitems;
     const int hx = p->nx / 2, hy = p->ny / 2, SY = sub_h(f_bwd);
@@ -393,10 +397,8 @@ static Layout make_layout(const gws_problem *p, int64_t n, int f_fwd, int f_bwd,
     L.off_chunk_items = take(bw * sizeof(int2) * (nchunks + 1));
     L.off_range_base = take(bw * sizeof(int32_t) * (ntiles + 2));
     L.off_bpartials = take(bw * sizeof(float) * (size_t)L.max_bslots *
-                           std::max(adjoint_on_mfma(make_consts(p, 0))
-                                        ? ADJ_MFMA_G * std::max(adj_nv(C, C < 4), adj_nv(C, false))
-                                        : 0,
-                                    std::max(adj_wg(C, true) * adj_nv(C, true), adj_wg(C, false) * adj_nv(C, false))));
+                           (mfma ? std::min(ADJ_MFMA_G, cap) * std::max(adj_nv(C, C < 4), adj_nv(C, false))
+                                 : std::max(wg_d * adj_nv(C, true), wg_n * adj_nv(C, false))));
     L.total = o;
     return L;
 }
@@ -897,9 +899,9 @@ static gws_status backward_run(gws_ctx *ctx, const gws_problem *prob, int S, con
             st = run_prep(ctx, k, scene_view(g, offsets[i], BL.n[i]), L, B, s, &keys, &vals);
             if (st != GWS_OK) return st;
             HIP_CHECK(ctx, launch_bin_backward(*p, keys, B.bitems, B.chunk_items, B.range_base, p->ntiles + 1,
-                                               L.max_bitems, B.counters, BL.n[i], adjoint_chunk(k), s));
+                                               L.max_bitems, B.counters, BL.n[i], adjoint_chunk(k, BL.n[i]), s));
             tab.s[i] = BwdScene{B.rec,    gpack + (int64_t)i * BL.pack_elems, gexp + (int64_t)i * BL.geo.nreg * 4,
-                                B.bitems, B.bpartials, B.counters, BL.n[i]};
+                                B.bitems, B.bpartials, B.counters, BL.n[i], adjoint_chunk(k, BL.n[i])};
             ctrs[i] = B.counters;
             vals_sorted[i] = vals;
         }
@@ -936,7 +938,7 @@ static gws_status backward_run(gws_ctx *ctx, const gws_problem *prob, int S, con
             const Bufs B = carve(L, base + BL.scene_off[i]);
             HIP_CHECK(ctx, launch_grad_final(scene_view(g, offsets[i], BL.n[i]), k, vals_sorted[i], B.chunk_items,
                                              B.range_base, B.bpartials, grad_view(grads, offsets[i], g->n), BL.n[i],
-                                             B.counters, adjoint_chunk(k), s));
+                                             B.counters, adjoint_chunk(k, BL.n[i]), s));
         }
     }
     HIP_CHECK(ctx, launch_sum_counters(ctrs.data(), S, ctx->d_stats, s));

@@ -43,7 +43,6 @@ constexpr int ADJ_RW = SUBX;           // region columns
 constexpr int ADJ_RH = 2 * sub_h(ADJ_F);  // region rows (64)
 constexpr int ADJ_SH = sub_h(ADJ_F);   // sub-tile rows (32)
 constexpr int ADJ_NB = ADJ_RH / 4;     // 4-row blocks per region
-constexpr int ADJ_MIN_CHUNK = 256;     // smallest work-group (and Gaussian chunk) of any variant
 static_assert(TILEX == 2 * ADJ_RW, "a tile holds two regions");
 // reduced per-Gaussian sums: Re P_c, Sfx, Sfy, Qxx, Qxy, Qyy, then Im P_c and W_c with the
 // depth gradient, else sum Im rho
@@ -371,6 +370,7 @@ struct BwdScene {
     float *bpartials;
     long long *counters;
     int64_t n;
+    int32_t chunk, pad;   // Gaussians per item
 };
 
 struct FwdTab {
@@ -519,7 +519,29 @@ int adjoint_occupancy(const Consts &k);
 // Gaussians per work-group (the binning's chunk) of the one that runs.
 constexpr int ADJ_MFMA_POINTS = 1000000;
 bool adjoint_on_mfma(const Consts &k);
-inline int adjoint_chunk(const Consts &k) { return adjoint_on_mfma(k) ? ADJ_MFMA_G : adj_wg(k.C, k.depth_grad != 0); }
+// Gaussians per item (the binning's chunk).  An item takes a tile's 2048 frequencies for all of its
+// Gaussians, so with as many as the work-group holds a few crowded tiles kept the launch's tail in
+// small scenes (compute units 42 % busy for 3000 Gaussians at 1000 x 750); smaller items repeat
+// the tile's tables and sums, and on the matrix cores fill passes of 16 worse, which weighs more
+// the more tiles there are.  Backward with 16 / 32 / 64 chunks to a scene, 1000 and 3000
+// Gaussians, one wavelength, term by term (us): 256 x 256 82 / 74 / 78 and 142 / 106 / 94, 640 x 480
+// 105 / 116 / 159 and 187 / 155 / 164, 1000 x 750 168 / 213 / 300 and 254 / 241 / 296 (whole work-groups:
+// 192 and 217, 250 and 264, 304 and 336).  On the matrix cores chunks of 512 / 256 / 128 / 64, 300
+// and 3000 Gaussians: 1280 x 800 219 / 203 / 168 / 151 and 323 / 251 / 278 / 349, 1920 x 1080 251 / 233 /
+// 200 / 219 and 371 / 369 / 430 / 463, 2000 x 2000 346 / 314 / 302 / 327 and 524 / 572 / 703 / 730.
+inline int adjoint_chunk_cap(int nx, int ny, int64_t n, bool mfma)
+{
+    const int tiles = ((nx + TILEX - 1) / TILEX) * ((ny + ADJ_RH - 1) / ADJ_RH);
+    const int want = mfma ? (tiles <= 800 ? 12 : 4) : tiles <= 64 ? 64 : tiles <= 256 ? 32 : 16;
+    int c = mfma ? 64 : 16;
+    while (c < 512 && (int64_t)want * c < n) c *= 2;
+    return c;
+}
+inline int adjoint_chunk(const Consts &k, int64_t n)
+{
+    const bool mfma = adjoint_on_mfma(k);
+    return std::min(mfma ? ADJ_MFMA_G : adj_wg(k.C, k.depth_grad != 0), adjoint_chunk_cap(k.nx, k.ny, n, mfma));
+}
 hipError_t launch_adj_pack_sub(const Consts &k, const AdjGeom &geo, int n_scenes, const float2 *gspecs, float2 *gsub,
                                int32_t *gexp, float *table, hipStream_t s);
 int adj_sub_table_floats(int C);  // words per sub-tile of its geometry table

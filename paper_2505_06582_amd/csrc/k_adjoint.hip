@@ -17,8 +17,8 @@
 // the exact phase base.  Everything the sums need per frequency -- |Gs_c|, arg Gs_c / 2 pi
 // and D_c(nu) - D_c(nu_0) -- is packed region-major once per call (k_adj_pack_g,
 // k_adj_pack_d), so a work-group of 8 wavefronts copies one region into LDS with
-// coalesced loads and every wavefront reads it from there.  The work-group owns 512
-// consecutive sorted Gaussians (one per thread) and a range of tiles; for each region,
+// coalesced loads and every wavefront reads it from there.  The work-group owns up to 512
+// consecutive sorted Gaussians (a thread tests one) and a range of tiles; for each region,
 // every thread tests its own Gaussian (exact ellipse test, 4-row block mask, FP64 phase
 // bases of both sub-tiles), then each wavefront walks its accepted Gaussians one at a time:
 // the record arrives by scalar loads, lane l evaluates column l % 16 and rows l / 16 + 4 b
@@ -189,11 +189,12 @@ __global__ void __launch_bounds__(adj_wg(C, DEPTH), adj_waves_per_simd(C, DEPTH)
         const float2 *__restrict__ gpack = S.gpack;
         const int64_t nvalid = S.n - S.counters[CTR_NCULLED];
         const BItem bi = S.bitems[q - prefix[sc]];
-        const int64_t g0 = (int64_t)bi.chunk * ADJ_WG;
+        const int CH = S.chunk;  // Gaussians of an item, one per thread (ADJ_WG at most)
+        const int64_t g0 = (int64_t)bi.chunk * CH;
         const int64_t gidx = g0 + tid;
-        const bool gvalid = gidx < nvalid;
+        const bool gvalid = tid < CH && gidx < nvalid;
         long long pairs = 0;
-        for (int i = tid; i < ADJ_WG * NV; i += ADJ_WG) s_acc[i] = 0.0f;
+        for (int i = tid; i < CH * NV; i += ADJ_WG) s_acc[i] = 0.0f;
         if (tid < 2) s_cnt[tid] = s_next[tid] = 0;
         int par = 0;  // parity of the region being processed
 
@@ -409,8 +410,8 @@ __global__ void __launch_bounds__(adj_wg(C, DEPTH), adj_waves_per_simd(C, DEPTH)
             }
         }
         __syncthreads();
-        float *dst = S.bpartials + (int64_t)bi.slot * ADJ_WG * NV;
-        for (int i = tid; i < ADJ_WG * NV; i += ADJ_WG) dst[i] = s_acc[i];
+        float *dst = S.bpartials + (int64_t)bi.slot * CH * NV;
+        for (int i = tid; i < CH * NV; i += ADJ_WG) dst[i] = s_acc[i];
         pairs = wave_sum_i64(pairs);
         if (lane == 0 && pairs) atomicAdd((unsigned long long *)&S.counters[CTR_PAIRS], (unsigned long long)pairs);
     }
@@ -418,10 +419,10 @@ __global__ void __launch_bounds__(adj_wg(C, DEPTH), adj_waves_per_simd(C, DEPTH)
 
 // Which adjoint runs.  The matrix-core one needs every grid frequency to propagate; on smaller grids
 // supports cover few sub-tiles and more Gaussians fail the separable form's tests.  Backward,
-// this kernel against the matrix-core one, 300 / 3000 / 30000 Gaussians (ms): 800 x 600, one
-// wavelength 0.17 / 0.27 / 0.67 against 0.25 / 0.44 / 0.90; 1000 x 750 0.20 / 0.32 / 0.88 against 0.23 /
-// 0.37 / 0.80; 1280 x 800 0.215 / 0.35 / 1.14 against 0.217 / 0.32 / 0.90, three wavelengths 0.37 / 0.66 /
-// 2.13 against 0.34 / 0.53 / 1.51; 1920 x 1080, three 0.48 / 0.83 / 3.99 against 0.39 / 0.59 / 2.48.
+// this kernel against the matrix-core one, 300 / 3000 / 30000 Gaussians (ms): 1000 x 750, one
+// wavelength 0.12 / 0.24 / 0.93 against 0.16 / 0.28 / 0.80; 1280 x 800 0.156 / 0.27 / 1.14 against 0.151 /
+// 0.25 / 0.91, three wavelengths 0.21 / 0.46 / 2.13 against 0.22 / 0.39 / 1.51; 1920 x 1080, three 0.36 /
+// 0.70 / 3.99 against 0.30 / 0.58 / 2.49.
 bool adjoint_on_mfma(const Consts &k)
 {
     return !grid_has_evanescent(k) && (int64_t)k.nx * k.ny >= (int64_t)ADJ_MFMA_POINTS;
@@ -483,15 +484,14 @@ __global__ void __launch_bounds__(64 * GF_SLICES) k_grad_final(GView g, Consts k
     constexpr int NV = adj_nv(C, DEPTH);
     __shared__ double s_acc[GF_SLICES - 1][NV][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int64_t s0 = (int64_t)blockIdx.x * 64, s = s0 + lane;
+    const int64_t s = (int64_t)blockIdx.x * 64 + lane;
     const int64_t nvalid = n - counters[CTR_NCULLED];
     double acc[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) acc[v] = 0.0;
-    if (s0 < nvalid) {
-        // chunks are multiples of 64 Gaussians: the work-group's share one
-        const int64_t b = s0 / chunk;
-        const int t = (int)(s0 - b * chunk) + lane;
+    if (s < nvalid) {
+        const int64_t b = s / chunk;
+        const int t = (int)(s - b * chunk);
         const int nk = chunk_items[b].y;
         const long long nbitems = counters[CTR_NBITEMS];
 #pragma unroll 4

@@ -15,7 +15,7 @@
 // a power of two per sub-tile.  X, the polynomials and all sums are FP32.  W_k of a higher order
 // than a Gaussian's class meets c_k = 0, so results do not depend on which 16 share a pass.
 //
-// Work.  A work-group of four wavefronts owns 512 consecutive sorted Gaussians and a range of
+// Work.  A work-group of four wavefronts owns up to 512 consecutive sorted Gaussians and a range of
 // tiles (the adjoint's items).  At an item's start the Gaussians are ordered by class.  Per
 // sub-tile every thread tests its two Gaussians; the accepted ones go into an LDS list, the
 // A operands into LDS, and each wavefront takes 16 listed Gaussians at a time: lane l holds
@@ -188,10 +188,11 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
         const float4 *__restrict__ poly = adj_poly(rec, S.n);
         const int64_t nvalid = S.n - S.counters[CTR_NCULLED];
         const BItem bi = S.bitems[q - prefix[sc]];
-        const int64_t g0 = (int64_t)bi.chunk * ADJ_MFMA_G;
-        const int ng = (int)min((int64_t)ADJ_MFMA_G, nvalid - g0);
+        const int CH = __builtin_amdgcn_readfirstlane(S.chunk);  // ADJ_MFMA_G at most
+        const int64_t g0 = (int64_t)bi.chunk * CH;
+        const int ng = (int)min((int64_t)CH, nvalid - g0);
         int pairs = 0;
-        for (int i = tid; i < ADJ_MFMA_G * NV; i += AM_T) s_acc[i] = 0.0f;
+        for (int i = tid; i < CH * NV; i += AM_T) s_acc[i] = 0.0f;
         // order by class (7 first)
         int cc[2];
 #pragma unroll
@@ -632,8 +633,9 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
         }
         }
         __syncthreads();
-        float *dst = S.bpartials + (int64_t)bi.slot * ADJ_MFMA_G * NV;
-        for (int i = tid; i < ADJ_MFMA_G * NV; i += AM_T) dst[i] = s_acc[i];
+        const int chunk = __builtin_amdgcn_readfirstlane(S.chunk);
+        float *dst = S.bpartials + (int64_t)bi.slot * chunk * NV;
+        for (int i = tid; i < chunk * NV; i += AM_T) dst[i] = s_acc[i];
         const long long np = wave_sum_i64((long long)pairs) * 64;
         if (lane == 0 && np) atomicAdd((unsigned long long *)&S.counters[CTR_PAIRS], (unsigned long long)np);
         __syncthreads();  // s_acc and the counters are free again

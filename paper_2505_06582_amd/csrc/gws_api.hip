@@ -715,17 +715,40 @@ static GradView grad_view(const gws_grads *g, int64_t off, int64_t total)
     return v;
 }
 
-// Preprocess + sort + records of one scene: shared by forward and backward.
-static gws_status run_prep(gws_ctx *ctx, const Consts &k, const GView &g, const Layout &L, const Bufs &B, hipStream_t s,
-                           uint64_t **keys_sorted, uint32_t **vals_sorted)
+static PrepScene prep_scene(const GView &g, const Layout &L, const Bufs &B)
 {
-    HIP_CHECK(ctx, launch_zero_counters(B.counters, B.bucket_end, s));
-    HIP_CHECK(ctx, launch_keys(g, k, B.keys_a, B.vals_a, s));
+    PrepScene S;
+    memset(&S, 0, sizeof(S));
+    S.g = g;
+    S.keys_a = B.keys_a;
+    S.keys_b = B.keys_b;
+    S.vals_a = B.vals_a;
+    S.vals_b = B.vals_b;
+    S.sort_table = B.sort_hist;
+    S.rec = B.rec;
+    S.bucket_end = B.bucket_end;
+    S.cum = B.cum;
+    S.counters = B.counters;
+    S.tile_L = B.tile_L;
+    S.tile_slots = B.tile_slots;
+    S.items = B.items;
+    S.max_items = L.max_items;
+    S.max_slots = L.max_slots;
+    S.bitems = B.bitems;
+    S.chunk_items = B.chunk_items;
+    S.range_base = B.range_base;
+    S.max_bitems = L.max_bitems;
+    S.bpartials = B.bpartials;
+    return S;
+}
+
+// Preprocess + sort + records of a group of scenes: shared by forward and backward.
+static gws_status run_prep(gws_ctx *ctx, const Consts &k, const PrepGroup &grp, hipStream_t s)
+{
+    HIP_CHECK(ctx, launch_keys(grp, k, s));
     // the forward's keys have 48 bits, the adjoint's the upper 16 of them
-    HIP_CHECK(ctx, radix_sort(B.keys_a, B.vals_a, B.keys_b, B.vals_b, B.sort_hist, g.n, k.forward ? 0 : 4, 5, s,
-                              keys_sorted, vals_sorted));
-    HIP_CHECK(ctx, launch_records(g, k, *keys_sorted, *vals_sorted, B.rec, g.n, B.bucket_end, B.counters,
-                                  !k.forward && adjoint_on_mfma(k), s));
+    HIP_CHECK(ctx, radix_sort(grp, k.forward ? 0 : 4, 5, s));
+    HIP_CHECK(ctx, launch_records(grp, k, !k.forward && adjoint_on_mfma(k), s));
     return GWS_OK;
 }
 
@@ -815,18 +838,21 @@ static gws_status forward_run(gws_ctx *ctx, const gws_problem *prob, int S, cons
     std::vector<long long *> ctrs(S);
     {
         StageScope sc(ctx, s, ST_PREP, !noalloc);
+        PrepGroup grp;
         for (int i = 0; i < S; ++i) {
             const Layout L = make_layout(prob, BL.n[i], F, ADJ_F, noalloc);
             const Bufs B = carve(L, base + BL.scene_off[i]);
-            uint64_t *keys = nullptr;
-            uint32_t *vals = nullptr;
-            st = run_prep(ctx, k, scene_view(g, offsets[i], BL.n[i]), L, B, s, &keys, &vals);
-            if (st != GWS_OK) return st;
+            PrepScene &P = grp.s[grp.n++];
+            P = prep_scene(scene_view(g, offsets[i], BL.n[i]), L, B);
             // the configuration's chunk of candidates per work item, capped at n / 16 (at least 128)
             // so that a small scene's crowded tiles still split into several items
-            const int chunk = (int)std::min<int64_t>(kTileCfg[cfg - 1][1], std::max<int64_t>(128, BL.n[i] / 16));
-            HIP_CHECK(ctx, launch_bin_forward(*p, B.bucket_end, B.cum, B.tile_L, B.tile_slots, B.items, L.max_items,
-                                              L.max_slots, chunk, B.counters, s));
+            P.base_chunk = (int)std::min<int64_t>(kTileCfg[cfg - 1][1], std::max<int64_t>(128, BL.n[i] / 16));
+            if (grp.n == PREP_GROUP || i == S - 1) {
+                st = run_prep(ctx, k, grp, s);
+                if (st != GWS_OK) return st;
+                HIP_CHECK(ctx, launch_bin_forward(*p, grp, s));
+                grp.n = 0;
+            }
             tab.s[i] = FwdScene{B.rec, B.tile_L, B.items, B.tile_slots, B.partials, spectra + (int64_t)i * CM, B.counters};
             ctrs[i] = B.counters;
         }
@@ -888,22 +914,26 @@ static gws_status backward_run(gws_ctx *ctx, const gws_problem *prob, int S, con
     memset(&tab, 0, sizeof(tab));
     tab.n = S;
     std::vector<long long *> ctrs(S);
-    std::vector<uint32_t *> vals_sorted(S);
+    std::vector<PrepGroup> groups;
     {
         StageScope sc(ctx, s, ST_PREP);
         for (int i = 0; i < S; ++i) {
             const Layout L = make_layout(prob, BL.n[i], kTileCfg[cfg - 1][0], ADJ_F);
             const Bufs B = carve(L, base + BL.scene_off[i]);
-            uint64_t *keys = nullptr;
-            uint32_t *vals = nullptr;
-            st = run_prep(ctx, k, scene_view(g, offsets[i], BL.n[i]), L, B, s, &keys, &vals);
-            if (st != GWS_OK) return st;
-            HIP_CHECK(ctx, launch_bin_backward(*p, keys, B.bitems, B.chunk_items, B.range_base, p->ntiles + 1,
-                                               L.max_bitems, B.counters, BL.n[i], adjoint_chunk(k, BL.n[i]), s));
+            groups.resize(i / PREP_GROUP + 1);
+            PrepGroup &grp = groups.back();
+            PrepScene &P = grp.s[grp.n++];
+            P = prep_scene(scene_view(g, offsets[i], BL.n[i]), L, B);
+            P.chunk = adjoint_chunk(k, BL.n[i]);
+            P.grads = grad_view(grads, offsets[i], g->n);
+            if (grp.n == PREP_GROUP || i == S - 1) {
+                st = run_prep(ctx, k, grp, s);
+                if (st != GWS_OK) return st;
+                HIP_CHECK(ctx, launch_bin_backward(*p, grp, p->ntiles + 1, s));
+            }
             tab.s[i] = BwdScene{B.rec,    gpack + (int64_t)i * BL.pack_elems, gexp + (int64_t)i * BL.geo.nreg * 4,
-                                B.bitems, B.bpartials, B.counters, BL.n[i], adjoint_chunk(k, BL.n[i])};
+                                B.bitems, B.bpartials, B.counters, BL.n[i], P.chunk, 0};
             ctrs[i] = B.counters;
-            vals_sorted[i] = vals;
         }
     }
     {
@@ -933,13 +963,7 @@ static gws_status backward_run(gws_ctx *ctx, const gws_problem *prob, int S, con
     }
     {
         StageScope sc(ctx, s, ST_FINAL);
-        for (int i = 0; i < S; ++i) {
-            const Layout L = make_layout(prob, BL.n[i], kTileCfg[cfg - 1][0], ADJ_F);
-            const Bufs B = carve(L, base + BL.scene_off[i]);
-            HIP_CHECK(ctx, launch_grad_final(scene_view(g, offsets[i], BL.n[i]), k, vals_sorted[i], B.chunk_items,
-                                             B.range_base, B.bpartials, grad_view(grads, offsets[i], g->n), BL.n[i],
-                                             B.counters, adjoint_chunk(k, BL.n[i]), s));
-        }
+        for (const PrepGroup &grp : groups) HIP_CHECK(ctx, launch_grad_final(grp, k, s));
     }
     HIP_CHECK(ctx, launch_sum_counters(ctrs.data(), S, ctx->d_stats, s));
     ctx->last_n = g->n;

@@ -349,6 +349,42 @@ struct GradView {
 
 constexpr int MAX_SCENES = 64;
 
+// One scene of a call, as its preparation kernels (keys, sort, records, binning) and the last
+// gradient kernel see it.  They take up to PREP_GROUP scenes to a launch (blockIdx.y): a scene
+// alone gives them a few work-groups for a few microseconds.
+struct PrepScene {
+    GView g;
+    uint64_t *keys_a, *keys_b;
+    uint32_t *vals_a, *vals_b, *sort_table;
+    GRec *rec;
+    uint32_t *bucket_end, *cum;
+    long long *counters;
+    // forward binning
+    int32_t *tile_L;
+    int2 *tile_slots;
+    Item *items;
+    int64_t max_items, max_slots;
+    // backward binning and gradients
+    BItem *bitems;
+    int2 *chunk_items;
+    int32_t *range_base;
+    int64_t max_bitems;
+    const float *bpartials;
+    GradView grads;
+    int32_t base_chunk, chunk;   // candidates per forward item, Gaussians per backward item
+};
+constexpr int PREP_GROUP = 8;
+struct PrepGroup {
+    int32_t n = 0;
+    PrepScene s[PREP_GROUP];
+    int64_t max_n() const
+    {
+        int64_t m = 0;
+        for (int i = 0; i < n; ++i) m = std::max(m, s[i].g.n);
+        return m;
+    }
+};
+
 // Per-scene pointers of the forward accumulation.
 struct FwdScene {
     const GRec *rec;
@@ -451,22 +487,14 @@ enum Counter {
 };
 
 // ---- kernel launchers (each enqueues on `stream`, returns hipError_t) ----
-hipError_t launch_keys(const GView &g, const Consts &k, uint64_t *keys, uint32_t *vals, hipStream_t s);
-// Stable sort by the 8-bit digits first ... last of the keys (digit 0 the lowest), scratch of
-// sort_table_words(n) words.
+hipError_t launch_keys(const PrepGroup &grp, const Consts &k, hipStream_t s);
+// Stable sort of keys_a / vals_a by the 8-bit digits first ... last of the keys (digit 0 the lowest; an
+// even number of them), scratch of sort_table_words(n) words.  vals_a is 0, 1, ... on entry.
 int64_t sort_table_words(int64_t n);
-hipError_t radix_sort(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, uint32_t *vals_b, uint32_t *table,
-                      int64_t n, int first_digit, int last_digit, hipStream_t s, uint64_t **keys_out,
-                      uint32_t **vals_out);
-hipError_t launch_records(const GView &g, const Consts &k, const uint64_t *keys,
-                          const uint32_t *vals, GRec *rec, int64_t n, uint32_t *bucket_end, long long *counters,
-                          bool poly, hipStream_t s);
-hipError_t launch_bin_forward(const Plan &p, const uint32_t *bucket_end, uint32_t *cum, int32_t *tile_L,
-                              int2 *tile_slots, Item *items, int64_t max_items, int64_t max_slots, int base_chunk,
-                              long long *counters, hipStream_t s);
-hipError_t launch_bin_backward(const Plan &p, const uint64_t *keys, BItem *bitems, int2 *chunk_items,
-                               int32_t *range_base, int max_ranges, int64_t max_bitems, long long *counters, int64_t n,
-                               int chunk, hipStream_t s);
+hipError_t radix_sort(const PrepGroup &grp, int first_digit, int last_digit, hipStream_t s);
+hipError_t launch_records(const PrepGroup &grp, const Consts &k, bool poly, hipStream_t s);
+hipError_t launch_bin_forward(const Plan &p, const PrepGroup &grp, hipStream_t s);
+hipError_t launch_bin_backward(const Plan &p, const PrepGroup &grp, int max_ranges, hipStream_t s);
 // Writes the scene table and the prefix of per-scene work-item counts, zeroes the queue head.
 hipError_t launch_fwd_table(const FwdTab &tab, FwdScene *dst, int32_t *prefix, long long *queue, hipStream_t s);
 hipError_t launch_bwd_table(const BwdTab &tab, BwdScene *dst, int32_t *prefix, long long *queue, hipStream_t s);
@@ -510,9 +538,7 @@ hipError_t launch_adj_pack(const Consts &k, const AdjGeom &geo, int n_scenes, co
 hipError_t launch_adjoint(const Plan &p, const Consts &k, const BwdScene *scenes, const int32_t *prefix, int n_scenes,
                           long long *queue, const float *dpack, const double *d0, const AdjGeom &geo, int grid,
                           hipStream_t s);
-hipError_t launch_grad_final(const GView &g, const Consts &k, const uint32_t *vals, const int2 *chunk_items,
-                             const int32_t *range_base, const float *bpartials, const GradView &grads, int64_t n,
-                             const long long *counters, int chunk, hipStream_t s);
+hipError_t launch_grad_final(const PrepGroup &grp, const Consts &k, hipStream_t s);
 hipError_t launch_sum_counters(long long *const *src, int n, long long *dst, hipStream_t s);
 int adjoint_occupancy(const Consts &k);
 // Whether the adjoint runs on the matrix cores (k_adjoint_mfma.hip) or term by term, and the
@@ -557,7 +583,6 @@ hipError_t launch_accumulate_mfma(const Plan &p, const Consts &k, const FwdScene
                                   int n_scenes, long long *queue, int grid, hipStream_t s);
 int accumulate_mfma_occupancy(int C);
 int accumulate_occupancy(const Consts &k, int F);
-hipError_t launch_zero_counters(long long *counters, uint32_t *bucket_end, hipStream_t s);
 hipError_t launch_copy_counters(const long long *src, long long *dst, hipStream_t s);
 int fft_col_batch(int n);
 size_t l2_workspace_bytes();

@@ -475,12 +475,19 @@ int adjoint_occupancy(const Consts &k)
 // the variant, so they stay in registers.
 constexpr int GF_SLICES = 8;
 template <int C, bool DEPTH>
-__global__ void __launch_bounds__(64 * GF_SLICES) k_grad_final(GView g, Consts k, const uint32_t *__restrict__ vals,
-                                                               const int2 *__restrict__ chunk_items,
-                                                               const int32_t *__restrict__ range_base,
-                                                               const float *__restrict__ bpartials, GradView grads,
-                                                               int64_t n, const long long *__restrict__ counters, int chunk)
+__global__ void __launch_bounds__(64 * GF_SLICES) k_grad_final(PrepGroup grp, Consts k)
 {
+    const PrepScene &S = grp.s[blockIdx.y];
+    const GView &g = S.g;
+    const GradView &grads = S.grads;
+    const uint32_t *__restrict__ vals = S.vals_a;
+    const int2 *__restrict__ chunk_items = S.chunk_items;
+    const int32_t *__restrict__ range_base = S.range_base;
+    const float *__restrict__ bpartials = S.bpartials;
+    const long long *__restrict__ counters = S.counters;
+    const int64_t n = g.n;
+    const int chunk = S.chunk;
+    if ((int64_t)blockIdx.x * 64 >= n) return;
     constexpr int NV = adj_nv(C, DEPTH);
     __shared__ double s_acc[GF_SLICES - 1][NV][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -557,15 +564,12 @@ __global__ void __launch_bounds__(64 * GF_SLICES) k_grad_final(GView g, Consts k
     if (DEPTH && grads.depth) grads.depth[i] = (float)(2.0 * PI * gz);
 }
 
-hipError_t launch_grad_final(const GView &g, const Consts &k, const uint32_t *vals, const int2 *chunk_items,
-                             const int32_t *range_base, const float *bpartials, const GradView &grads, int64_t n,
-                             const long long *counters, int chunk, hipStream_t s)
+hipError_t launch_grad_final(const PrepGroup &grp, const Consts &k, hipStream_t s)
 {
+    const int64_t n = grp.max_n();
     if (n == 0) return hipSuccess;
-    const dim3 grid((unsigned)((n + 63) / 64)), block(64 * GF_SLICES);
-#define GWS_GF(CC, DD)                                                                                                  \
-    hipLaunchKernelGGL((k_grad_final<CC, DD>), grid, block, 0, s, g, k, vals, chunk_items, range_base, bpartials, grads, \
-                       n, counters, chunk)
+    const dim3 grid((unsigned)((n + 63) / 64), grp.n), block(64 * GF_SLICES);
+#define GWS_GF(CC, DD) hipLaunchKernelGGL((k_grad_final<CC, DD>), grid, block, 0, s, grp, k)
     const bool d = k.depth_grad != 0;
     switch (k.C) {
     case 1: if (d) GWS_GF(1, true); else GWS_GF(1, false); break;

@@ -24,6 +24,8 @@
 // order-invariant path's spectral culling).
 #include <algorithm>
 
+#include <string.h>
+
 #include "gws_internal.h"
 
 namespace gws {
@@ -353,6 +355,22 @@ size_t exact_batch(int nx, int ny)
     return b;
 }
 
+// The keys' lower 32 bits ascending: front to back.
+static hipError_t sort_by_depth(const GView &g, const ExactBuffers &eb, hipStream_t s)
+{
+    PrepGroup grp;
+    grp.n = 1;
+    PrepScene &S = grp.s[0];
+    memset(&S, 0, sizeof(S));
+    S.g = g;
+    S.keys_a = eb.keys_a;
+    S.keys_b = eb.keys_b;
+    S.vals_a = eb.vals_a;
+    S.vals_b = eb.vals_b;
+    S.sort_table = eb.sort_hist;
+    return radix_sort(grp, 0, 3, s);
+}
+
 hipError_t run_exact_forward(const Plan &p, const Consts &k, const GView &g, const ExactBuffers &eb, float2 *spec,
                              hipStream_t s)
 {
@@ -364,9 +382,8 @@ hipError_t run_exact_forward(const Plan &p, const Consts &k, const GView &g, con
                        k.C);
     if (n == 0) return hipGetLastError();
     hipLaunchKernelGGL(k_exact_keys, dim3(gn), dim3(256), 0, s, g, eb.keys_a, eb.vals_a);
-    uint64_t *keys = nullptr;
-    uint32_t *order = nullptr;
-    hipError_t e = radix_sort(eb.keys_a, eb.vals_a, eb.keys_b, eb.vals_b, eb.sort_hist, n, 0, 3, s, &keys, &order);
+    const uint32_t *order = eb.vals_a;
+    hipError_t e = sort_by_depth(g, eb, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_exact_records, dim3(gn), dim3(256), 0, s, g, k, order, rec, eb.counters);
     const int B = (int)exact_batch(k.nx, k.ny);
@@ -726,9 +743,8 @@ hipError_t run_exact_backward(const Plan &p, const Consts &k, const GView &g, co
     ERec *rec = (ERec *)eb.rec;
     const unsigned gn = (unsigned)((n + 255) / 256);
     hipLaunchKernelGGL(k_exact_keys, dim3(gn), dim3(256), 0, s, g, eb.keys_a, eb.vals_a);
-    uint64_t *keys = nullptr;
-    uint32_t *order = nullptr;
-    hipError_t e = radix_sort(eb.keys_a, eb.vals_a, eb.keys_b, eb.vals_b, eb.sort_hist, n, 0, 3, s, &keys, &order);
+    const uint32_t *order = eb.vals_a;
+    hipError_t e = sort_by_depth(g, eb, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_exact_records, dim3(gn), dim3(256), 0, s, g, k, order, rec, eb.counters);
     // Gs = FFT(dL/du)

@@ -6,7 +6,10 @@
 // radix sort stable LSD radix sort of the keys, 8-bit digits, wave-ballot ranking.
 // k_records  one thread per sorted Gaussian: the 64-byte record the accumulation reads,
 //            with every large phase quantity reduced exactly in FP64 / fixed point.
-// k_bin_*    one work-group: candidate counts per tile, chunk size, work-item lists.
+// k_bin_*    one work-group per scene: candidate counts per tile, chunk size, work-item lists.
+//
+// Each launch takes up to PREP_GROUP scenes (blockIdx): bound by latency, they take hardly longer
+// than one (six scenes of 1e4 Gaussians at 1280 x 1024: 860 us a scene after another, 290 together).
 //
 // The spectrum of Gaussian i (Sec. 4.1, Eq. 10, in-plane so det J = 1) has modulus
 // 2 pi sqrt(det S) exp(-2 pi^2 nu^T S nu): an ellipse centred on DC.  In index units
@@ -36,10 +39,14 @@ static __device__ __forceinline__ int bwd_level_bucket(int level)
     return min(NBUCKET - 1, (int)exp2f((float)(level + 1) * (1.0f / BWD_LPO)) + 1);  // one above: log2f's rounding
 }
 
-__global__ void __launch_bounds__(256) k_keys(GView g, Consts k, uint64_t *__restrict__ keys,
-                                               uint32_t *__restrict__ vals)
+// Also clears the scene's counters and bucket ends, which the next kernels write.
+__global__ void __launch_bounds__(256) k_keys(PrepGroup grp, Consts k)
 {
+    const PrepScene &S = grp.s[blockIdx.y];
+    const GView &g = S.g;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < CTR_COUNT) S.counters[i] = 0;
+    if (i < NBUCKET) S.bucket_end[i] = 0;
     if (i >= g.n) return;
     const float sxx = g.cov_xx[i], sxy = g.cov_xy[i], syy = g.cov_yy[i];
     const float mx = g.mean_x[i], my = g.mean_y[i], z = g.depth[i], o = g.opacity[i], ph = g.phase[i];
@@ -78,15 +85,14 @@ __global__ void __launch_bounds__(256) k_keys(GView g, Consts k, uint64_t *__res
     const uint32_t u = __float_as_uint(z);
     const uint32_t asc = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
     lo = k.forward ? ~asc : 0u;
-    keys[i] = ((uint64_t)hi << 32) | (uint64_t)lo;
-    vals[i] = (uint32_t)i;
+    S.keys_a[i] = ((uint64_t)hi << 32) | (uint64_t)lo;
+    S.vals_a[i] = (uint32_t)i;
 }
 
-hipError_t launch_keys(const GView &g, const Consts &k, uint64_t *keys, uint32_t *vals, hipStream_t s)
+hipError_t launch_keys(const PrepGroup &grp, const Consts &k, hipStream_t s)
 {
-    const int64_t blocks = (g.n + 255) / 256;
-    if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_keys, dim3((unsigned)blocks), dim3(256), 0, s, g, k, keys, vals);
+    const int64_t blocks = std::max<int64_t>((grp.max_n() + 255) / 256, NBUCKET / 256);
+    hipLaunchKernelGGL(k_keys, dim3((unsigned)blocks, grp.n), dim3(256), 0, s, grp, k);
     return hipGetLastError();
 }
 
@@ -143,10 +149,7 @@ static __device__ __forceinline__ uint32_t sort_digit_scan(uint32_t v, uint32_t 
 }
 
 template <int ITEMS>
-__global__ void __launch_bounds__(SORT_THREADS) k_sort_one(const uint64_t *__restrict__ keys_in,
-                                                           const uint32_t *__restrict__ vals_in,
-                                                           uint64_t *__restrict__ keys_out, uint32_t *__restrict__ vals_out,
-                                                           int n, int first_digit, int last_digit)
+__global__ void __launch_bounds__(SORT_THREADS) k_sort_one(PrepGroup grp, int first_digit, int last_digit)
 {
     __shared__ uint64_t s_key[SORT_THREADS * ITEMS];
     __shared__ uint16_t s_idx[SORT_THREADS * ITEMS];
@@ -155,15 +158,19 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_one(const uint64_t *__res
     __shared__ uint64_t s_diff[SORT_WAVES];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int base = wave * (64 * ITEMS) + lane;
+    const PrepScene &S = grp.s[blockIdx.x];
+    if (S.g.n == 0 || S.g.n > SORT_THREADS * ITEMS) return;  // nothing, or in many blocks
+    const int n = (int)S.g.n;
+    uint64_t *const keys = S.keys_a;
     uint64_t key[ITEMS];
     uint32_t idx[ITEMS], rank[ITEMS];
     uint64_t diff = 0;
-    const uint64_t key0 = keys_in[0];
+    const uint64_t key0 = keys[0];
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
         const int i = base + it * 64;
         idx[it] = (uint32_t)i;
-        key[it] = i < n ? keys_in[i] : key0;
+        key[it] = i < n ? keys[i] : key0;
         diff |= key[it] ^ key0;
     }
 #pragma unroll
@@ -214,14 +221,18 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_one(const uint64_t *__res
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it)
         if (base + it * 64 < n) {
-            keys_out[base + it * 64] = key[it];
-            vals_out[base + it * 64] = vals_in[idx[it]];
+            keys[base + it * 64] = key[it];
+            S.vals_a[base + it * 64] = idx[it];
         }
 }
 
-__global__ void __launch_bounds__(SORT_THREADS) k_sort_hist(const uint64_t *__restrict__ keys, int64_t n, int shift,
-                                                            uint32_t *__restrict__ table)
+__global__ void __launch_bounds__(SORT_THREADS) k_sort_hist(PrepGroup grp, int shift, bool odd)
 {
+    const PrepScene &S = grp.s[blockIdx.y];
+    const int64_t n = S.g.n;
+    if (n <= SORT_ONE || (int64_t)blockIdx.x * SORT_TILE >= n) return;
+    const uint64_t *__restrict__ keys = odd ? S.keys_b : S.keys_a;
+    uint32_t *__restrict__ table = S.sort_table;
     __shared__ uint32_t s_cnt[SORT_WAVES][256];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (int j = lane; j < 256; j += 64) s_cnt[wave][j] = 0;
@@ -261,8 +272,12 @@ static __device__ __forceinline__ void sort_rows(const uint32_t *__restrict__ ta
 }
 
 // Many blocks: the table's rows become output offsets, in one block.
-__global__ void __launch_bounds__(SORT_THREADS) k_sort_scan(uint32_t *__restrict__ table, int nb)
+__global__ void __launch_bounds__(SORT_THREADS) k_sort_scan(PrepGroup grp)
 {
+    uint32_t *__restrict__ table = grp.s[blockIdx.x].sort_table;
+    const int64_t n = grp.s[blockIdx.x].g.n;
+    const int nb = (int)((n + SORT_TILE - 1) / SORT_TILE);
+    if (nb <= SORT_SELF_SCAN) return;
     __shared__ uint32_t part[4][256], s_wave[4];
     const int tid = threadIdx.x, lane = tid & 63, d = tid & 255, q = tid >> 8;
     uint32_t total, before;
@@ -287,17 +302,21 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_scan(uint32_t *__restrict
     }
 }
 
-template <bool SCANNED>
-__global__ void __launch_bounds__(SORT_THREADS) k_sort_scatter(const uint64_t *__restrict__ keys_in,
-                                                               const uint32_t *__restrict__ vals_in,
-                                                               uint64_t *__restrict__ keys_out,
-                                                               uint32_t *__restrict__ vals_out, int64_t n, int shift,
-                                                               const uint32_t *__restrict__ table)
+// odd: from keys_b / vals_b to keys_a / vals_a, else the other way.
+__global__ void __launch_bounds__(SORT_THREADS) k_sort_scatter(PrepGroup grp, int shift, bool odd)
 {
     __shared__ uint32_t s_off[SORT_WAVES][256];  // per wavefront: digit counts, then output offsets
     __shared__ uint32_t s_part[2][4][256], s_wave[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, d = tid & 255, q = tid >> 8;
-    const int nb = gridDim.x, me = blockIdx.x;
+    const PrepScene &S = grp.s[blockIdx.y];
+    const int64_t n = S.g.n;
+    const int nb = (int)((n + SORT_TILE - 1) / SORT_TILE), me = blockIdx.x;
+    if (n <= SORT_ONE || me >= nb) return;
+    const uint64_t *__restrict__ keys_in = odd ? S.keys_b : S.keys_a;
+    const uint32_t *__restrict__ vals_in = odd ? S.vals_b : S.vals_a, *__restrict__ table = S.sort_table;
+    uint64_t *__restrict__ keys_out = odd ? S.keys_a : S.keys_b;
+    uint32_t *__restrict__ vals_out = odd ? S.vals_a : S.vals_b;
+    const bool SCANNED = nb > SORT_SELF_SCAN;
     const int64_t base = (int64_t)me * SORT_TILE + wave * (64 * SORT_ITEMS) + lane;
     uint64_t key[SORT_ITEMS];
     uint32_t val[SORT_ITEMS], rank[SORT_ITEMS];
@@ -344,52 +363,48 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_scatter(const uint64_t *_
         }
 }
 
-hipError_t radix_sort(uint64_t *keys_a, uint32_t *vals_a, uint64_t *keys_b, uint32_t *vals_b, uint32_t *table,
-                      int64_t n, int first_digit, int last_digit, hipStream_t s, uint64_t **keys_out,
-                      uint32_t **vals_out)
+hipError_t radix_sort(const PrepGroup &grp, int first_digit, int last_digit, hipStream_t s)
 {
-    uint64_t *ki = keys_a, *ko = keys_b;
-    uint32_t *vi = vals_a, *vo = vals_b;
+    if ((last_digit - first_digit) % 2 == 0) return hipErrorInvalidValue;  // the result stands in keys_a
     const dim3 block(SORT_THREADS);
-    if (n > SORT_ONE) {
-        const int nb = sort_blocks(n);
-        const dim3 grid(nb);
-        for (int dg = first_digit; dg <= last_digit; ++dg) {
-            hipLaunchKernelGGL(k_sort_hist, grid, block, 0, s, ki, n, 8 * dg, table);
-            if (nb > SORT_SELF_SCAN) {
-                hipLaunchKernelGGL(k_sort_scan, dim3(1), block, 0, s, table, nb);
-                hipLaunchKernelGGL(k_sort_scatter<true>, grid, block, 0, s, ki, vi, ko, vo, n, 8 * dg, table);
-            } else {
-                hipLaunchKernelGGL(k_sort_scatter<false>, grid, block, 0, s, ki, vi, ko, vo, n, 8 * dg, table);
-            }
-            uint64_t *tk = ki; ki = ko; ko = tk;
-            uint32_t *tv = vi; vi = vo; vo = tv;
-        }
-    } else if (n > 0) {
-#define GWS_SORT_ONE(I) \
-    hipLaunchKernelGGL(k_sort_one<I>, dim3(1), block, 0, s, ki, vi, ko, vo, (int)n, first_digit, last_digit)
-        if (n <= SORT_THREADS) GWS_SORT_ONE(1);
-        else if (n <= 2 * SORT_THREADS) GWS_SORT_ONE(2);
-        else if (n <= 4 * SORT_THREADS) GWS_SORT_ONE(4);
-        else if (n <= 8 * SORT_THREADS) GWS_SORT_ONE(8);
-        else GWS_SORT_ONE(SORT_ONE_ITEMS);
-#undef GWS_SORT_ONE
-        ki = ko;
-        vi = vo;
+    int64_t one = 0, many = 0;  // the largest scene of each kind
+    for (int i = 0; i < grp.n; ++i) {
+        int64_t &m = grp.s[i].g.n > SORT_ONE ? many : one;
+        m = std::max(m, grp.s[i].g.n);
     }
-    *keys_out = ki;
-    *vals_out = vi;
+#define GWS_SORT_ONE(I) hipLaunchKernelGGL(k_sort_one<I>, dim3(grp.n), block, 0, s, grp, first_digit, last_digit)
+    if (one > 8 * SORT_THREADS) GWS_SORT_ONE(SORT_ONE_ITEMS);
+    else if (one > 4 * SORT_THREADS) GWS_SORT_ONE(8);
+    else if (one > 2 * SORT_THREADS) GWS_SORT_ONE(4);
+    else if (one > SORT_THREADS) GWS_SORT_ONE(2);
+    else if (one > 0) GWS_SORT_ONE(1);
+#undef GWS_SORT_ONE
+    if (many > 0) {
+        const int nb = sort_blocks(many);
+        const dim3 grid(nb, grp.n);
+        for (int dg = first_digit; dg <= last_digit; ++dg) {
+            const bool odd = (dg - first_digit) & 1;
+            hipLaunchKernelGGL(k_sort_hist, grid, block, 0, s, grp, 8 * dg, odd);
+            if (nb > SORT_SELF_SCAN) hipLaunchKernelGGL(k_sort_scan, dim3(grp.n), block, 0, s, grp);
+            hipLaunchKernelGGL(k_sort_scatter, grid, block, 0, s, grp, 8 * dg, odd);
+        }
+    }
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------
 // Records, in sorted order.
 // ---------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_records(GView g, Consts k, const uint64_t *__restrict__ keys,
-                                                  const uint32_t *__restrict__ vals, GRec *__restrict__ rec,
-                                                  int64_t n, uint32_t *__restrict__ bucket_end,
-                                                  long long *__restrict__ counters, bool poly)
+__global__ void __launch_bounds__(256) k_records(PrepGroup grp, Consts k, bool poly)
 {
+    const PrepScene &S = grp.s[blockIdx.y];
+    const GView &g = S.g;
+    const uint64_t *__restrict__ keys = S.keys_a;
+    const uint32_t *__restrict__ vals = S.vals_a;
+    GRec *__restrict__ rec = S.rec;
+    uint32_t *__restrict__ bucket_end = S.bucket_end;
+    long long *__restrict__ counters = S.counters;
+    const int64_t n = g.n;
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= n) return;
     const uint32_t hi = (uint32_t)(keys[s] >> 32);
@@ -442,12 +457,11 @@ __global__ void __launch_bounds__(256) k_records(GView g, Consts k, const uint64
     }
 }
 
-hipError_t launch_records(const GView &g, const Consts &k, const uint64_t *keys, const uint32_t *vals,
-                          GRec *rec, int64_t n, uint32_t *bucket_end, long long *counters, bool poly, hipStream_t s)
+hipError_t launch_records(const PrepGroup &grp, const Consts &k, bool poly, hipStream_t s)
 {
-    const int64_t blocks = (n + 255) / 256;
+    const int64_t blocks = (grp.max_n() + 255) / 256;
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_records, dim3((unsigned)blocks), dim3(256), 0, s, g, k, keys, vals, rec, n, bucket_end, counters, poly);
+    hipLaunchKernelGGL(k_records, dim3((unsigned)blocks, grp.n), dim3(256), 0, s, grp, k, poly);
     return hipGetLastError();
 }
 
@@ -474,13 +488,17 @@ static __device__ uint32_t block_excl_scan_1024(uint32_t v, uint32_t *tmp, uint3
     return incl - v;
 }
 
-__global__ void __launch_bounds__(1024) k_bin_forward(const int32_t *__restrict__ tile_bucket, int ntiles,
-                                                      const uint32_t *__restrict__ bucket_end, uint32_t *__restrict__ cum,
-                                                      int32_t *__restrict__ tile_L, int2 *__restrict__ tile_slots,
-                                                      Item *__restrict__ items,
-                                                      int64_t max_items, int64_t max_slots, int base_chunk,
-                                                      long long *__restrict__ counters)
+__global__ void __launch_bounds__(1024) k_bin_forward(const int32_t *__restrict__ tile_bucket, int ntiles, PrepGroup grp)
 {
+    const PrepScene &S = grp.s[blockIdx.x];
+    const uint32_t *__restrict__ bucket_end = S.bucket_end;
+    uint32_t *__restrict__ cum = S.cum;
+    int32_t *__restrict__ tile_L = S.tile_L;
+    int2 *__restrict__ tile_slots = S.tile_slots;
+    Item *__restrict__ items = S.items;
+    const int64_t max_items = S.max_items, max_slots = S.max_slots;
+    const int base_chunk = S.base_chunk;
+    long long *__restrict__ counters = S.counters;
     __shared__ uint32_t tmp[1024];
     __shared__ unsigned long long red[1024];
     __shared__ int32_t chunk_sh;
@@ -519,15 +537,15 @@ __global__ void __launch_bounds__(1024) k_bin_forward(const int32_t *__restrict_
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        const unsigned long long S = red[0];
-        // multi-chunk tiles need <= 2 S / CH slots: the configured base chunk, grown to fit
+        const unsigned long long sum = red[0];
+        // multi-chunk tiles need <= 2 sum / CH slots: the configured base chunk, grown to fit
         long long ch = base_chunk;
-        const long long need = (long long)((2ull * S + (unsigned long long)max_slots - 1) / (unsigned long long)max_slots);
+        const long long need = (long long)((2ull * sum + (unsigned long long)max_slots - 1) / (unsigned long long)max_slots);
         if (need > ch) ch = (need + 255) / 256 * 256;
         if (ch > (1ll << 30)) ch = 1ll << 30;
         chunk_sh = (int32_t)ch;
         counters[CTR_CHUNK] = ch;
-        counters[CTR_CAND] = (long long)S;
+        counters[CTR_CAND] = (long long)sum;
     }
     __syncthreads();
     const int CH = chunk_sh;
@@ -561,12 +579,9 @@ __global__ void __launch_bounds__(1024) k_bin_forward(const int32_t *__restrict_
     }
 }
 
-hipError_t launch_bin_forward(const Plan &p, const uint32_t *bucket_end, uint32_t *cum, int32_t *tile_L,
-                              int2 *tile_slots, Item *items, int64_t max_items, int64_t max_slots, int base_chunk,
-                              long long *counters, hipStream_t s)
+hipError_t launch_bin_forward(const Plan &p, const PrepGroup &grp, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_bin_forward, dim3(1), dim3(1024), 0, s, p.tile_bucket, p.ntiles, bucket_end, cum, tile_L,
-                       tile_slots, items, max_items, max_slots, base_chunk, counters);
+    hipLaunchKernelGGL(k_bin_forward, dim3(grp.n), dim3(1024), 0, s, p.tile_bucket, p.ntiles, grp);
     return hipGetLastError();
 }
 
@@ -582,12 +597,16 @@ hipError_t launch_bin_forward(const Plan &p, const uint32_t *bucket_end, uint32_
 // 20 chunks took 88 us, 13 now.
 // ---------------------------------------------------------------------------------
 constexpr int BWD_K_LDS = 4096;
-__global__ void __launch_bounds__(1024) k_bin_backward(const int32_t *__restrict__ tile_cum,
-                                                       const uint64_t *__restrict__ keys, BItem *__restrict__ bitems,
-                                                       int2 *__restrict__ chunk_items, int32_t *__restrict__ range_base,
-                                                       int max_ranges, int64_t max_bitems,
-                                                       long long *__restrict__ counters, int64_t n, int chunk)
+__global__ void __launch_bounds__(1024) k_bin_backward(const int32_t *__restrict__ tile_cum, int max_ranges, PrepGroup grp)
 {
+    const PrepScene &S = grp.s[blockIdx.x];
+    const uint64_t *__restrict__ keys = S.keys_a;
+    BItem *__restrict__ bitems = S.bitems;
+    int2 *__restrict__ chunk_items = S.chunk_items;
+    int32_t *__restrict__ range_base = S.range_base;
+    const int64_t max_bitems = S.max_bitems, n = S.g.n;
+    long long *__restrict__ counters = S.counters;
+    const int chunk = S.chunk;
     __shared__ uint32_t tmp[1024];
     __shared__ unsigned long long red[1024];
     __shared__ int32_t trb_sh, nr_sh;
@@ -610,12 +629,12 @@ __global__ void __launch_bounds__(1024) k_bin_backward(const int32_t *__restrict
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        const unsigned long long S = red[0];
+        const unsigned long long sum = red[0];
         long long trb = 1;
-        // items <= S / TRB + nchunks <= max_bitems
+        // items <= sum / TRB + nchunks <= max_bitems
         const long long room = max_bitems - nchunks;
         if (room > 0) {
-            const long long need = (long long)((S + (unsigned long long)room - 1) / (unsigned long long)room);
+            const long long need = (long long)((sum + (unsigned long long)room - 1) / (unsigned long long)room);
             if (need > trb) trb = need;
         } else {
             trb = 1 << 30;
@@ -670,32 +689,16 @@ __global__ void __launch_bounds__(1024) k_bin_backward(const int32_t *__restrict
     }
 }
 
-hipError_t launch_bin_backward(const Plan &p, const uint64_t *keys, BItem *bitems, int2 *chunk_items,
-                               int32_t *range_base, int max_ranges, int64_t max_bitems,
-                               long long *counters, int64_t n, int chunk, hipStream_t s)
+hipError_t launch_bin_backward(const Plan &p, const PrepGroup &grp, int max_ranges, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_bin_backward, dim3(1), dim3(1024), 0, s, p.tile_cum, keys, bitems, chunk_items, range_base,
-                       max_ranges, max_bitems, counters, n, chunk);
+    hipLaunchKernelGGL(k_bin_backward, dim3(grp.n), dim3(1024), 0, s, p.tile_cum, max_ranges, grp);
     return hipGetLastError();
-}
-
-__global__ void k_zero_counters(long long *__restrict__ counters, uint32_t *__restrict__ bucket_end)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < CTR_COUNT) counters[t] = 0;
-    if (t < NBUCKET) bucket_end[t] = 0;
 }
 
 __global__ void k_copy_counters(const long long *__restrict__ src, long long *__restrict__ dst)
 {
     const int t = threadIdx.x;
     if (t < CTR_COUNT) dst[t] = src[t];
-}
-
-hipError_t launch_zero_counters(long long *counters, uint32_t *bucket_end, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_zero_counters, dim3(NBUCKET / 256), dim3(256), 0, s, counters, bucket_end);
-    return hipGetLastError();
 }
 
 hipError_t launch_copy_counters(const long long *src, long long *dst, hipStream_t s)

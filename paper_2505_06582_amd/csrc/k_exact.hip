@@ -429,6 +429,14 @@ constexpr int EXACT_NSPAT = 8;          // Sx, Sy, Sxx, Sxy, Syy, So, pad, pad
 // real, so Gaussians 2p and 2p + 1 share one image: Vh_{2p} + j Vh_{2p+1} overwrites the packed
 // transform of pair p in pimgs (each thread reads its own two entries of image p before it
 // writes them).
+//
+// The phase e^{j phi_k} rides in H's, so F_k itself enters, and with s = Gs(m) + Gs(-m), d = Gs(m) -
+// Gs(-m) and H e^{j phi} = hc + j hs the sums and differences of Y(+-m) = Gs(+-m) conj(H e^{j phi})
+//   a = s_x hc + s_y hs,  b = d_y hc - d_x hs,  c = d_x hc + d_y hs,  e = s_y hc - s_x hs
+// carry all: X(m) + X(-m) = (F_x a + F_y b) + j (F_y c - F_x e), Vh += A / 2 (a + j b).  Bound by VALU
+// issue (195 instructions per Gaussian and 64 pairs with the two frequencies apart, 130
+// now; 500 Gaussians at 1920 x 1080 x 3: 3.02 -> 2.16 ms, of which reading and writing the images take 1.7).
+template <int C>
 __global__ void __launch_bounds__(256) k_exact_gsplat(const ERec *__restrict__ rec, int b0, int nb, Consts k,
                                                       const float2 *__restrict__ gspec, float2 *pimgs,
                                                       float *__restrict__ part)
@@ -436,9 +444,12 @@ __global__ void __launch_bounds__(256) k_exact_gsplat(const ERec *__restrict__ r
     // per wave and batch Gaussian, the wave's 16 sums: the four waves are summed in a fixed
     // order once, after the batch, so the waves never wait for each other inside it
     __shared__ float s_red[4][64][16];
+    __shared__ float s_phi[64];  // phi_k in revolutions
     const int nx = k.nx, ny = k.ny, hy = ny / 2;
     const int64_t M = (int64_t)nx * ny;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if ((int)threadIdx.x < nb)
+        s_phi[threadIdx.x] = atan2f(rec[b0 + threadIdx.x].sphi, rec[b0 + threadIdx.x].cphi) * 0.15915494309189535f;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int my = (int)(t / nx), mx = (int)(t - (int64_t)my * nx);
     // rows 0 .. Ny / 2; in the rows 0 and Ny / 2 only columns 0 .. Nx / 2 (the rest are partners)
@@ -446,24 +457,28 @@ __global__ void __launch_bounds__(256) k_exact_gsplat(const ERec *__restrict__ r
     if (!live) mx = my = 0;
     const int m = my * nx + mx, mn = (int)neg_freq(mx, my, nx, ny);  // M < 2^31
     const bool pair = live && mn != m;
-    double w[4];
-    bool prop[4];
-    float2 gs0[4], gs1[4];  // Gs_c at m and at -m
+    double w[C];
+    float2 gs[C], gd[C];  // Gs_c(m) + Gs_c(-m) and Gs_c(m) - Gs_c(-m); zero where evanescent
     {
         const int mxp = 2 * mx < nx ? mx : mx - nx, myp = 2 * my < ny ? my : my - ny;
         const double nux = mxp / (nx * k.px), nuy = myp / (ny * k.py);
         const double nu2 = nux * nux + nuy * nuy;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < C; ++c) {
             const double w2 = k.inv_lambda[c] * k.inv_lambda[c] - nu2;
-            prop[c] = live && c < k.C && w2 > 0.0;
-            w[c] = prop[c] ? sqrt(w2) : 0.0;
-            gs0[c] = (live && c < k.C) ? gspec[(int64_t)c * M + m] : make_float2(0.0f, 0.0f);
-            gs1[c] = (pair && c < k.C) ? gspec[(int64_t)c * M + mn] : make_float2(0.0f, 0.0f);
+            const bool prop = live && w2 > 0.0;
+            w[c] = prop ? sqrt(w2) : 0.0;
+            const float2 g0 = prop ? gspec[(int64_t)c * M + m] : make_float2(0.0f, 0.0f);
+            const float2 g1 = prop && pair ? gspec[(int64_t)c * M + mn] : make_float2(0.0f, 0.0f);
+            gs[c] = make_float2(g0.x + g1.x, g0.y + g1.y);
+            gd[c] = make_float2(g0.x - g1.x, g0.y - g1.y);
         }
     }
+    __syncthreads();
     float2 Fa = make_float2(0.0f, 0.0f), Fb = Fa;
     float2 Ha = Fa;  // Vh of the pair's first Gaussian at m
+    // Vh at a frequency that is its own mirror is the real part of V'(m)
+    const float hr = pair ? 0.5f : 1.0f, hi = pair ? 0.5f : 0.0f;
     for (int b = 0; b < nb; ++b) {
         const int64_t pb = (int64_t)(b >> 1) * M;
         if ((b & 1) == 0) {
@@ -478,49 +493,32 @@ __global__ void __launch_bounds__(256) k_exact_gsplat(const ERec *__restrict__ r
         const ERec &rr = rec[b0 + b];
         // the fields used below, loaded together
         const int valid = rr.valid;
-        const float rz = rr.z, cph = rr.cphi, sph = rr.sphi;
+        const float rz = rr.z;
         const float4 ramp = *reinterpret_cast<const float4 *>(rr.amp);
         const float ampc[4] = {ramp.x, ramp.y, ramp.z, ramp.w};
-        float v[EXACT_NSPEC];
+        const double zd = (double)rz, phi = (double)s_phi[b];
+        float x[EXACT_NSPEC];
 #pragma unroll
-        for (int i = 0; i < EXACT_NSPEC; ++i) v[i] = 0.0f;
-        const double zd = (double)rz;
-        float2 V0 = make_float2(0.0f, 0.0f), V1 = V0;
-        if (live && valid) {
+        for (int i = 0; i < EXACT_NSPEC; ++i) x[i] = 0.0f;
+        float vx = 0.0f, vy = 0.0f;
+        if (valid) {  // uniform
             const float2 F = (b & 1) ? Fb : Fa;
-            // e^{j phi} F at m and e^{j phi} conj(F) at -m
-            const float2 S0 = make_float2(cph * F.x - sph * F.y, cph * F.y + sph * F.x);
-            const float2 S1 = make_float2(cph * F.x + sph * F.y, sph * F.x - cph * F.y);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if (!prop[c]) continue;
-                const double ph = -zd * w[c];
-                const float tt = (float)(ph - floor(ph));
+            for (int c = 0; c < C; ++c) {
+                const float tt = (float)__builtin_amdgcn_fract(fma(-zd, w[c], phi));
                 const float hc = __builtin_amdgcn_cosf(tt), hs = __builtin_amdgcn_sinf(tt);
-                // Y = Gs conj(H) at m and at -m (zero at -m when -m = m: gs1 = 0)
-                const float2 Y0 = make_float2(gs0[c].x * hc + gs0[c].y * hs, gs0[c].y * hc - gs0[c].x * hs);
-                const float2 Y1 = make_float2(gs1[c].x * hc + gs1[c].y * hs, gs1[c].y * hc - gs1[c].x * hs);
-                // X = conj(Gs) H e^{j phi} F = conj(Y) S, summed over the two frequencies
-                const float xr = Y0.x * S0.x + Y0.y * S0.y + Y1.x * S1.x + Y1.y * S1.y;
-                const float xi = Y0.x * S0.y - Y0.y * S0.x + Y1.x * S1.y - Y1.y * S1.x;
-                const float wf = (float)w[c];
-                v[4 * c + 0] += xr;
-                v[4 * c + 1] += xi;
-                v[4 * c + 2] = fmaf(wf, xr, v[4 * c + 2]);
-                v[4 * c + 3] = fmaf(wf, xi, v[4 * c + 3]);
-                // V += A_c Y
-                const float A = ampc[c];
-                V0.x = fmaf(A, Y0.x, V0.x);
-                V0.y = fmaf(A, Y0.y, V0.y);
-                V1.x = fmaf(A, Y1.x, V1.x);
-                V1.y = fmaf(A, Y1.y, V1.y);
+                const float ya = fmaf(gs[c].x, hc, gs[c].y * hs), yb = fmaf(gd[c].y, hc, -gd[c].x * hs);
+                const float yc = fmaf(gd[c].x, hc, gd[c].y * hs), ye = fmaf(gs[c].y, hc, -gs[c].x * hs);
+                const float xr = fmaf(F.x, ya, F.y * yb), xi = fmaf(F.y, yc, -F.x * ye), wf = (float)w[c];
+                x[4 * c + 0] = xr;
+                x[4 * c + 1] = xi;
+                x[4 * c + 2] = wf * xr;
+                x[4 * c + 3] = wf * xi;
+                vx = fmaf(ampc[c], ya, vx);
+                vy = fmaf(ampc[c], yb, vy);
             }
         }
-        // V' = e^{-j phi} V at m and -m, and Vh(m) (at a frequency that is its own mirror, the
-        // real part of V'(m))
-        const float2 P0 = make_float2(cph * V0.x + sph * V0.y, cph * V0.y - sph * V0.x);
-        const float2 P1 = make_float2(cph * V1.x + sph * V1.y, cph * V1.y - sph * V1.x);
-        const float2 Hm = pair ? make_float2(0.5f * (P0.x + P1.x), 0.5f * (P0.y - P1.y)) : make_float2(P0.x, 0.0f);
+        const float2 Hm = make_float2(hr * vx, hi * vy);
         if ((b & 1) == 0) {
             Ha = Hm;
             if (b + 1 == nb && live) {  // no partner: Vh alone, Hermitian
@@ -534,9 +532,6 @@ __global__ void __launch_bounds__(256) k_exact_gsplat(const ERec *__restrict__ r
         }
         // one transposed butterfly over the 16 sums: afterwards lane l with
         // bits 0-2 clear holds sums 2 (4 b5 + 2 b4 + b3) and that + 1
-        float x[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = i < EXACT_NSPEC ? v[i] : 0.0f;
         float unused = 0.0f;
         reduce_transposed<16, false>(x, unused, lane);
         if ((lane & 7) == 0) {
@@ -775,8 +770,13 @@ hipError_t run_exact_backward(const Plan &p, const Consts &k, const GView &g, co
                            eb.rowwin, eb.pcolwin, eb.prowwin);
         e = launch_fft2d_win(p, (nb + 1) / 2, -1, eb.pimgs, eb.pimgs, eb.pcolwin, eb.prowwin, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_exact_gsplat, dim3(gsblk), dim3(256), 0, s, rec, (int)b0, nb, k, bb.gspec, eb.pimgs,
-                           bb.pspec);
+        const dim3 gsg(gsblk), gsb(256);
+        switch (k.C) {
+        case 1: hipLaunchKernelGGL(k_exact_gsplat<1>, gsg, gsb, 0, s, rec, (int)b0, nb, k, bb.gspec, eb.pimgs, bb.pspec); break;
+        case 2: hipLaunchKernelGGL(k_exact_gsplat<2>, gsg, gsb, 0, s, rec, (int)b0, nb, k, bb.gspec, eb.pimgs, bb.pspec); break;
+        case 3: hipLaunchKernelGGL(k_exact_gsplat<3>, gsg, gsb, 0, s, rec, (int)b0, nb, k, bb.gspec, eb.pimgs, bb.pspec); break;
+        default: hipLaunchKernelGGL(k_exact_gsplat<4>, gsg, gsb, 0, s, rec, (int)b0, nb, k, bb.gspec, eb.pimgs, bb.pspec); break;
+        }
         // r is read only inside each window: full row pass, columns of the pair's windows only
         e = launch_fft2d_cols_out(p, (nb + 1) / 2, +1, eb.pimgs, eb.pcolwin, s);
         if (e != hipSuccess) return e;

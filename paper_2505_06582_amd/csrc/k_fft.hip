@@ -221,7 +221,9 @@ static __device__ __forceinline__ void twiddle_powers(const float2 *wp, float2 *
     }
 }
 
-template <int R, int S, int NPT>
+// FIRST: Ns = 1, where every twiddle is one (used for S = 1; without the products by one the compiler
+// fuses other products and sums of the inverse's butterflies, and fields would not keep their bits).
+template <int R, int S, int NPT, bool FIRST>
 static __device__ __forceinline__ void row_pass_inplace(float2 *buf, int n, int Ns, const float2 *__restrict__ tw,
                                                         int tid, int sr, int sw)
 {
@@ -239,12 +241,16 @@ static __device__ __forceinline__ void row_pass_inplace(float2 *buf, int n, int 
         const int j = tid + q * FFT_THREADS;
         o[q] = 0;
         if (j < nb) {
-            const int jq = Ns > 1 ? div_small(j, mNs) : j, k = j - jq * Ns;
-            o[q] = jq * Ns * R + k;
-            const uint32_t kt8 = (uint32_t)(k * tstep) * 8u;  // < 8 n / R: 24 bits
+            if (FIRST) {
+                o[q] = j * R;
+            } else {
+                const int jq = Ns > 1 ? div_small(j, mNs) : j, k = j - jq * Ns;
+                o[q] = jq * Ns * R + k;
+                const uint32_t kt8 = (uint32_t)(k * tstep) * 8u;  // < 8 n / R: 24 bits
 #pragma unroll
-            for (int i = 0; i < NW; ++i)
-                w[q][i] = tw_at(tw, __umul24(1u << i, kt8));
+                for (int i = 0; i < NW; ++i)
+                    w[q][i] = tw_at(tw, __umul24(1u << i, kt8));
+            }
             const int a = lds_at(j, sr);
 #pragma unroll
             for (int r = 0; r < R; ++r) v[q][r] = buf[a + r * rstr];
@@ -255,13 +261,15 @@ static __device__ __forceinline__ void row_pass_inplace(float2 *buf, int n, int 
     for (int q = 0; q < KB; ++q) {
         const int j = tid + q * FFT_THREADS;
         if (j < nb) {
-            float2 wr[R];
-            twiddle_powers<R>(w[q], wr);
+            if (!FIRST) {
+                float2 wr[R];
+                twiddle_powers<R>(w[q], wr);
 #pragma unroll
-            for (int r = 1; r < R; ++r) {
-                float2 t = wr[r];
-                if (S < 0) t.y = -t.y;
-                v[q][r] = cmul(v[q][r], t);
+                for (int r = 1; r < R; ++r) {
+                    float2 t = wr[r];
+                    if (S < 0) t.y = -t.y;
+                    v[q][r] = cmul(v[q][r], t);
+                }
             }
             dftR<S, R>(v[q]);
             const int a = lds_at(o[q], sw);
@@ -272,23 +280,30 @@ static __device__ __forceinline__ void row_pass_inplace(float2 *buf, int n, int 
     __syncthreads();
 }
 
+template <int S, int NPT, bool FIRST>
+static __device__ __forceinline__ void row_pass(float2 *buf, const RadixPlan &pl, int p, int Ns, const float2 *__restrict__ tw)
+{
+    const int sr = pl.sh[p], sw = pl.sh[p + 1];
+    switch (pl.r[p]) {
+    case 2: row_pass_inplace<2, S, NPT, FIRST>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
+    case 3: row_pass_inplace<3, S, NPT, FIRST>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
+    case 4: row_pass_inplace<4, S, NPT, FIRST>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
+    case 5: row_pass_inplace<5, S, NPT, FIRST>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
+    case 9: row_pass_inplace<9, S, NPT, FIRST>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
+    case 15: row_pass_inplace<15, S, NPT, FIRST>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
+    case 16: row_pass_inplace<16, S, NPT, FIRST>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
+    default: row_pass_inplace<8, S, NPT, FIRST>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
+    }
+}
+
 template <int S, int NPT>
 static __device__ void fft_row_lds(float2 *buf, const RadixPlan &pl, const float2 *__restrict__ tw)
 {
-    int Ns = 1;
-    for (int p = 0; p < pl.nrad; ++p) {
-        const int R = pl.r[p], sr = pl.sh[p], sw = pl.sh[p + 1];
-        switch (R) {
-        case 2: row_pass_inplace<2, S, NPT>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
-        case 3: row_pass_inplace<3, S, NPT>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
-        case 4: row_pass_inplace<4, S, NPT>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
-        case 5: row_pass_inplace<5, S, NPT>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
-        case 9: row_pass_inplace<9, S, NPT>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
-        case 15: row_pass_inplace<15, S, NPT>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
-        case 16: row_pass_inplace<16, S, NPT>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
-        default: row_pass_inplace<8, S, NPT>(buf, pl.n, Ns, tw, threadIdx.x, sr, sw); break;
-        }
-        Ns *= R;
+    row_pass<S, NPT, (S > 0)>(buf, pl, 0, 1, tw);
+    int Ns = pl.r[0];
+    for (int p = 1; p < pl.nrad; ++p) {
+        row_pass<S, NPT, false>(buf, pl, p, Ns, tw);
+        Ns *= pl.r[p];
     }
 }
 
@@ -296,8 +311,8 @@ static __device__ void fft_row_lds(float2 *buf, const RadixPlan &pl, const float
 // inside when d < len.  Both v and the start lie in [0, n).
 static __device__ __forceinline__ int win_pos(int v, int2 w, int n)
 {
-    const int d = v - w.x;
-    return d < 0 ? d + n : d;
+    const uint32_t d = (uint32_t)(v - w.x);
+    return (int)min(d, d + (uint32_t)n);
 }
 // A window is one or two periodic intervals (x, y) and (z, w) as (start, length); an unused
 // second interval has length 0.  v lies in [0, n).
@@ -334,13 +349,22 @@ __global__ void __launch_bounds__(FFT_THREADS) k_fft_rows(const float2 *__restri
     // comes at most every 8 elements).
     if ((((uintptr_t)in | (uintptr_t)out) & 15) == 0) {
         const float4 *src4 = reinterpret_cast<const float4 *>(src);
-        for (int i = 2 * threadIdx.x; i < n; i += 2 * FFT_THREADS) {
-            const bool l0 = in_win(i, wi, n), l1 = in_win(i + 1, wi, n);
-            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (l0 || l1) v = src4[i >> 1];
-            const int a = lds_at(i, s0);
-            lds[a] = l0 ? make_float2(v.x, v.y) : make_float2(0.0f, 0.0f);
-            lds[a + 1] = l1 ? make_float2(v.z, v.w) : make_float2(0.0f, 0.0f);
+        if (colin) {
+            for (int i = 2 * threadIdx.x; i < n; i += 2 * FFT_THREADS) {
+                const bool l0 = in_win(i, wi, n), l1 = in_win(i + 1, wi, n);
+                float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (l0 || l1) v = src4[i >> 1];
+                const int a = lds_at(i, s0);
+                lds[a] = l0 ? make_float2(v.x, v.y) : make_float2(0.0f, 0.0f);
+                lds[a + 1] = l1 ? make_float2(v.z, v.w) : make_float2(0.0f, 0.0f);
+            }
+        } else {
+            for (int i = 2 * threadIdx.x; i < n; i += 2 * FFT_THREADS) {
+                const float4 v = src4[i >> 1];
+                const int a = lds_at(i, s0);
+                lds[a] = make_float2(v.x, v.y);
+                lds[a + 1] = make_float2(v.z, v.w);
+            }
         }
         __syncthreads();
         fft_row_lds<S, NPT>(lds, pl, tw);
@@ -348,6 +372,10 @@ __global__ void __launch_bounds__(FFT_THREADS) k_fft_rows(const float2 *__restri
         for (int i = 2 * threadIdx.x; i < n; i += 2 * FFT_THREADS) {
             const int a = lds_at(i, s1);
             const float2 v0 = lds[a], v1 = lds[a + 1];
+            if (!colout) {
+                dst4[i >> 1] = make_float4(v0.x, v0.y, v1.x, v1.y);
+                continue;
+            }
             const bool l0 = in_win(i, wo, n), l1 = in_win(i + 1, wo, n);
             if (l0 && l1) dst4[i >> 1] = make_float4(v0.x, v0.y, v1.x, v1.y);
             else if (l0) dst[i] = v0;
@@ -380,7 +408,8 @@ struct ColK {
 };
 
 
-template <int R, int S, int LDSB>
+// FIRST: as in row_pass_inplace.
+template <int R, int S, int LDSB, bool FIRST>
 static __device__ __forceinline__ void stockham_pass_inplace(float2 *buf, int n, int lb, int Ns, const float2 *tw,
                                                              int tid)
 {
@@ -407,13 +436,15 @@ static __device__ __forceinline__ void stockham_pass_inplace(float2 *buf, int n,
         const int idx = tid + q * FFT_COL_THREADS;
         if (idx < total) {
             const int j = idx >> lb, c = idx & (B - 1);
-            const int jq = Ns > 1 ? div_small(j, mNs) : j, k = j - jq * Ns;
-            const uint32_t kt8 = (uint32_t)(k * tstep) * 8u;  // < 8 n / R: 24 bits
+            const int jq = !FIRST && Ns > 1 ? div_small(j, mNs) : j, k = FIRST ? 0 : j - jq * Ns;
+            if (!FIRST) {
+                const uint32_t kt8 = (uint32_t)(k * tstep) * 8u;  // < 8 n / R: 24 bits
 #pragma unroll
-            for (int r = 1; r < R; ++r) {
-                float2 w = tw_at(tw, __umul24((uint32_t)r, kt8));
-                if (S < 0) w.y = -w.y;
-                v[q][r] = cmul(v[q][r], w);
+                for (int r = 1; r < R; ++r) {
+                    float2 w = tw_at(tw, __umul24((uint32_t)r, kt8));
+                    if (S < 0) w.y = -w.y;
+                    v[q][r] = cmul(v[q][r], w);
+                }
             }
             dftR<S, R>(v[q]);
             const int a = ((jq * Ns * R + k) << lb) + c;
@@ -422,6 +453,21 @@ static __device__ __forceinline__ void stockham_pass_inplace(float2 *buf, int n,
         }
     }
     __syncthreads();
+}
+
+template <int S, int LDSB, bool FIRST>
+static __device__ __forceinline__ void col_pass(float2 *lds, const RadixPlan &pl, int p, int lb, int Ns, const float2 *tw)
+{
+    switch (pl.r[p]) {
+    case 2: stockham_pass_inplace<2, S, LDSB, FIRST>(lds, pl.n, lb, Ns, tw, threadIdx.x); break;
+    case 3: stockham_pass_inplace<3, S, LDSB, FIRST>(lds, pl.n, lb, Ns, tw, threadIdx.x); break;
+    case 4: stockham_pass_inplace<4, S, LDSB, FIRST>(lds, pl.n, lb, Ns, tw, threadIdx.x); break;
+    case 5: stockham_pass_inplace<5, S, LDSB, FIRST>(lds, pl.n, lb, Ns, tw, threadIdx.x); break;
+    case 9: stockham_pass_inplace<9, S, LDSB, FIRST>(lds, pl.n, lb, Ns, tw, threadIdx.x); break;
+    case 15: stockham_pass_inplace<15, S, LDSB, FIRST>(lds, pl.n, lb, Ns, tw, threadIdx.x); break;
+    case 16: stockham_pass_inplace<16, S, LDSB, FIRST>(lds, pl.n, lb, Ns, tw, threadIdx.x); break;
+    default: stockham_pass_inplace<8, S, LDSB, FIRST>(lds, pl.n, lb, Ns, tw, threadIdx.x); break;
+    }
 }
 
 // Work-groups are dispatched to the 8 XCDs round robin (block i to XCD i mod 8).  Renumber them
@@ -462,50 +508,45 @@ __global__ void __launch_bounds__(FFT_COL_THREADS, LDSB == FFT_COL_LDS_SMALL ? 4
     const float2 *src = in + img * (int64_t)n * width;
     float2 *dst = out + img * (int64_t)n * width;
     const int4 wc = colwin ? colwin[img] : make_int4(0, width, 0, 0);
+    // this thread's column and first row, and its steps (FFT_COL_THREADS is a multiple of B)
+    const int tc = threadIdx.x & (B - 1), tr = threadIdx.x >> lb, rstep = FFT_COL_THREADS >> lb;
+    const int64_t pstep = (int64_t)rstep * width;
     if (colwin) {
         const int4 wr = rowin ? rowin[img] : make_int4(0, n, 0, n);
-        for (int i = threadIdx.x; i < n * B; i += FFT_COL_THREADS) {
-            const int r = i >> lb, c = i & (B - 1), v = c0 + c;
-            const bool live = c < bw && ((win_pos(v, make_int2(wc.x, wc.y), width) < wc.y &&
-                                          win_pos(r, make_int2(wr.x, wr.y), n) < wr.y) ||
-                                         (win_pos(v, make_int2(wc.z, wc.w), width) < wc.w &&
-                                          win_pos(r, make_int2(wr.z, wr.w), n) < wr.w));
-            lds[i] = live ? src[(int64_t)r * width + c0 + c] : make_float2(0.0f, 0.0f);
+        const bool la = tc < bw && win_pos(c0 + tc, make_int2(wc.x, wc.y), width) < wc.y;
+        const bool lb2 = tc < bw && win_pos(c0 + tc, make_int2(wc.z, wc.w), width) < wc.w;
+        const float2 *p = src + (int64_t)tr * width + c0 + tc;
+#pragma unroll 8
+        for (int i = threadIdx.x, r = tr; i < n * B; i += FFT_COL_THREADS, r += rstep, p += pstep) {
+            const bool live = (la && win_pos(r, make_int2(wr.x, wr.y), n) < wr.y) ||
+                              (lb2 && win_pos(r, make_int2(wr.z, wr.w), n) < wr.w);
+            lds[i] = live ? *p : make_float2(0.0f, 0.0f);
         }
     } else {
-        for (int i = threadIdx.x; i < n * B; i += FFT_COL_THREADS) {
-            const int r = i >> lb, c = i & (B - 1);
-            lds[i] = c < bw && (r < zero0 || r >= zero1) ? src[(int64_t)r * width + c0 + c] : make_float2(0.0f, 0.0f);
-        }
+        const float2 *p = src + (int64_t)tr * width + c0 + tc;
+#pragma unroll 8
+        for (int i = threadIdx.x, r = tr; i < n * B; i += FFT_COL_THREADS, r += rstep, p += pstep)
+            lds[i] = tc < bw && (r < zero0 || r >= zero1) ? *p : make_float2(0.0f, 0.0f);
     }
     __syncthreads();
-    int Ns = 1;
-    for (int p = 0; p < pl.nrad; ++p) {
-        const int R = pl.r[p];
-        switch (R) {
-        case 2: stockham_pass_inplace<2, S, LDSB>(lds, n, lb, Ns, tw_s, threadIdx.x); break;
-        case 3: stockham_pass_inplace<3, S, LDSB>(lds, n, lb, Ns, tw_s, threadIdx.x); break;
-        case 4: stockham_pass_inplace<4, S, LDSB>(lds, n, lb, Ns, tw_s, threadIdx.x); break;
-        case 5: stockham_pass_inplace<5, S, LDSB>(lds, n, lb, Ns, tw_s, threadIdx.x); break;
-        case 9: stockham_pass_inplace<9, S, LDSB>(lds, n, lb, Ns, tw_s, threadIdx.x); break;
-        case 15: stockham_pass_inplace<15, S, LDSB>(lds, n, lb, Ns, tw_s, threadIdx.x); break;
-        case 16: stockham_pass_inplace<16, S, LDSB>(lds, n, lb, Ns, tw_s, threadIdx.x); break;
-        default: stockham_pass_inplace<8, S, LDSB>(lds, n, lb, Ns, tw_s, threadIdx.x); break;
-        }
-        Ns *= R;
+    col_pass<S, LDSB, (S > 0)>(lds, pl, 0, lb, 1, tw_s);
+    int Ns = pl.r[0];
+    for (int p = 1; p < pl.nrad; ++p) {
+        col_pass<S, LDSB, false>(lds, pl, p, lb, Ns, tw_s);
+        Ns *= pl.r[p];
     }
+    const bool out_col = tc < bw && (!colwin || in_win(c0 + tc, wc, width));
+    if (!out_col) return;
+    const int64_t o = (int64_t)tr * width + c0 + tc;
     if (INTENSITY) {
-        float *dstf = outf + img * (int64_t)n * width;
-        for (int i = threadIdx.x; i < n * B; i += FFT_COL_THREADS) {
-            const int r = i >> lb, c = i & (B - 1);
+        float *p = outf + img * (int64_t)n * width + o;
+        for (int i = threadIdx.x; i < n * B; i += FFT_COL_THREADS, p += pstep) {
             const float2 v = lds[i];
-            if (c < bw && in_win(c0 + c, wc, width)) dstf[(int64_t)r * width + c0 + c] = fmaf(v.x, v.x, v.y * v.y);
+            *p = fmaf(v.x, v.x, v.y * v.y);
         }
     } else {
-        for (int i = threadIdx.x; i < n * B; i += FFT_COL_THREADS) {
-            const int r = i >> lb, c = i & (B - 1);
-            if (c < bw && in_win(c0 + c, wc, width)) dst[(int64_t)r * width + c0 + c] = lds[i];
-        }
+        float2 *p = dst + o;
+        for (int i = threadIdx.x; i < n * B; i += FFT_COL_THREADS, p += pstep) *p = lds[i];
     }
 }
 

@@ -835,7 +835,6 @@ static gws_status forward_run(gws_ctx *ctx, const gws_problem *prob, int S, cons
     FwdTab tab;
     memset(&tab, 0, sizeof(tab));
     tab.n = S;
-    std::vector<long long *> ctrs(S);
     {
         StageScope sc(ctx, s, ST_PREP, !noalloc);
         PrepGroup grp;
@@ -854,7 +853,6 @@ static gws_status forward_run(gws_ctx *ctx, const gws_problem *prob, int S, cons
                 grp.n = 0;
             }
             tab.s[i] = FwdScene{B.rec, B.tile_L, B.items, B.tile_slots, B.partials, spectra + (int64_t)i * CM, B.counters};
-            ctrs[i] = B.counters;
         }
     }
     FwdScene *dtab = (FwdScene *)(base + BL.off_ftab);
@@ -870,7 +868,7 @@ static gws_status forward_run(gws_ctx *ctx, const gws_problem *prob, int S, cons
     }
     {
         StageScope sc(ctx, s, ST_REDUCE, !noalloc);
-        HIP_CHECK(ctx, launch_reduce_partials(*p, k, dtab, S, s));
+        HIP_CHECK(ctx, launch_reduce_partials(*p, k, dtab, S, ctx->d_stats, s));
     }
     {
         StageScope sc(ctx, s, ST_XFORM_INV, !noalloc);
@@ -880,7 +878,6 @@ static gws_status forward_run(gws_ctx *ctx, const gws_problem *prob, int S, cons
             HIP_CHECK(ctx, launch_dft_bf16x3(*p, S * k.C, +1, spectra, (float2 *)out->field,
                                              (void *)(base + BL.off_dftws), s));
     }
-    HIP_CHECK(ctx, launch_sum_counters(ctrs.data(), S, ctx->d_stats, s));
     ctx->last_n = g->n;
     ctx->last_tile_config = cfg;
     return GWS_OK;
@@ -913,7 +910,6 @@ static gws_status backward_run(gws_ctx *ctx, const gws_problem *prob, int S, con
     BwdTab tab;
     memset(&tab, 0, sizeof(tab));
     tab.n = S;
-    std::vector<long long *> ctrs(S);
     std::vector<PrepGroup> groups;
     {
         StageScope sc(ctx, s, ST_PREP);
@@ -933,7 +929,6 @@ static gws_status backward_run(gws_ctx *ctx, const gws_problem *prob, int S, con
             }
             tab.s[i] = BwdScene{B.rec,    gpack + (int64_t)i * BL.pack_elems, gexp + (int64_t)i * BL.geo.nreg * 4,
                                 B.bitems, B.bpartials, B.counters, BL.n[i], P.chunk, 0};
-            ctrs[i] = B.counters;
         }
     }
     {
@@ -963,9 +958,9 @@ static gws_status backward_run(gws_ctx *ctx, const gws_problem *prob, int S, con
     }
     {
         StageScope sc(ctx, s, ST_FINAL);
-        for (const PrepGroup &grp : groups) HIP_CHECK(ctx, launch_grad_final(grp, k, s));
+        for (const PrepGroup &grp : groups)
+            HIP_CHECK(ctx, launch_grad_final(grp, k, dscenes, S, &grp == &groups.back() ? ctx->d_stats : nullptr, s));
     }
-    HIP_CHECK(ctx, launch_sum_counters(ctrs.data(), S, ctx->d_stats, s));
     ctx->last_n = g->n;
     ctx->last_tile_config = cfg;
     return GWS_OK;

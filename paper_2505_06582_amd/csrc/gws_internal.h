@@ -501,7 +501,7 @@ hipError_t launch_bwd_table(const BwdTab &tab, BwdScene *dst, int32_t *prefix, l
 hipError_t launch_accumulate(const Plan &p, const Consts &k, const FwdScene *scenes, const int32_t *prefix,
                              int n_scenes, long long *queue, int grid, hipStream_t s);
 hipError_t launch_reduce_partials(const Plan &p, const Consts &k, const FwdScene *scenes, int n_scenes,
-                                  hipStream_t s);
+                                  long long *stats, hipStream_t s);
 
 // Exact alpha wave blending (k_exact.hip): device buffers of one call.
 struct ExactBuffers {
@@ -538,7 +538,9 @@ hipError_t launch_adj_pack(const Consts &k, const AdjGeom &geo, int n_scenes, co
 hipError_t launch_adjoint(const Plan &p, const Consts &k, const BwdScene *scenes, const int32_t *prefix, int n_scenes,
                           long long *queue, const float *dpack, const double *d0, const AdjGeom &geo, int grid,
                           hipStream_t s);
-hipError_t launch_grad_final(const PrepGroup &grp, const Consts &k, hipStream_t s);
+// stats (may be NULL): also the sum of the call's counters.
+hipError_t launch_grad_final(const PrepGroup &grp, const Consts &k, const BwdScene *scenes, int n_scenes, long long *stats,
+                             hipStream_t s);
 hipError_t launch_sum_counters(long long *const *src, int n, long long *dst, hipStream_t s);
 int adjoint_occupancy(const Consts &k);
 // Whether the adjoint runs on the matrix cores (k_adjoint_mfma.hip) or term by term, and the
@@ -583,7 +585,6 @@ hipError_t launch_accumulate_mfma(const Plan &p, const Consts &k, const FwdScene
                                   int n_scenes, long long *queue, int grid, hipStream_t s);
 int accumulate_mfma_occupancy(int C);
 int accumulate_occupancy(const Consts &k, int F);
-hipError_t launch_copy_counters(const long long *src, long long *dst, hipStream_t s);
 int fft_col_batch(int n);
 size_t l2_workspace_bytes();
 hipError_t launch_l2_grad(const float2 *u, const float2 *t, float2 *g, double *loss, void *ws, int64_t n, hipStream_t s);

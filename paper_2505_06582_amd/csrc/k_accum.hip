@@ -266,8 +266,15 @@ __global__ void __launch_bounds__(WG, waves_per_simd(F)) k_accumulate(Consts k, 
 
 template <int C, int F>
 __global__ void __launch_bounds__(WG) k_reduce_partials(Consts k, const int32_t *__restrict__ tile_xy,
-                                                        const FwdScene *__restrict__ scenes)
+                                                        const FwdScene *__restrict__ scenes,
+                                                        long long *__restrict__ stats)
 {
+    // the call's statistics: its scenes' counters, complete since the accumulation
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < CTR_COUNT) {
+        long long v = 0;
+        for (unsigned i = 0; i < gridDim.y; ++i) v += scenes[i].counters[threadIdx.x];
+        stats[threadIdx.x] = v;
+    }
     const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const FwdScene S = scenes[blockIdx.y];
     const float2 *__restrict__ partials = S.partials;
@@ -376,23 +383,25 @@ hipError_t launch_accumulate(const Plan &p, const Consts &k, const FwdScene *sce
 }
 
 template <int C>
-static void launch_red_c(const Plan &p, const Consts &k, const FwdScene *scenes, int n_scenes, hipStream_t s)
+static void launch_red_c(const Plan &p, const Consts &k, const FwdScene *scenes, int n_scenes, long long *stats,
+                         hipStream_t s)
 {
     const dim3 grid(p.ntiles, n_scenes), block(WG);
     switch (p.F) {
-    case 2: hipLaunchKernelGGL((k_reduce_partials<C, 2>), grid, block, 0, s, k, p.tile_xy, scenes); break;
-    case 8: hipLaunchKernelGGL((k_reduce_partials<C, 8>), grid, block, 0, s, k, p.tile_xy, scenes); break;
-    default: hipLaunchKernelGGL((k_reduce_partials<C, 4>), grid, block, 0, s, k, p.tile_xy, scenes); break;
+    case 2: hipLaunchKernelGGL((k_reduce_partials<C, 2>), grid, block, 0, s, k, p.tile_xy, scenes, stats); break;
+    case 8: hipLaunchKernelGGL((k_reduce_partials<C, 8>), grid, block, 0, s, k, p.tile_xy, scenes, stats); break;
+    default: hipLaunchKernelGGL((k_reduce_partials<C, 4>), grid, block, 0, s, k, p.tile_xy, scenes, stats); break;
     }
 }
 
-hipError_t launch_reduce_partials(const Plan &p, const Consts &k, const FwdScene *scenes, int n_scenes, hipStream_t s)
+hipError_t launch_reduce_partials(const Plan &p, const Consts &k, const FwdScene *scenes, int n_scenes, long long *stats,
+                                  hipStream_t s)
 {
     switch (k.C) {
-    case 1: launch_red_c<1>(p, k, scenes, n_scenes, s); break;
-    case 2: launch_red_c<2>(p, k, scenes, n_scenes, s); break;
-    case 3: launch_red_c<3>(p, k, scenes, n_scenes, s); break;
-    case 4: launch_red_c<4>(p, k, scenes, n_scenes, s); break;
+    case 1: launch_red_c<1>(p, k, scenes, n_scenes, stats, s); break;
+    case 2: launch_red_c<2>(p, k, scenes, n_scenes, stats, s); break;
+    case 3: launch_red_c<3>(p, k, scenes, n_scenes, stats, s); break;
+    case 4: launch_red_c<4>(p, k, scenes, n_scenes, stats, s); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -475,8 +475,14 @@ int adjoint_occupancy(const Consts &k)
 // the variant, so they stay in registers.
 constexpr int GF_SLICES = 8;
 template <int C, bool DEPTH>
-__global__ void __launch_bounds__(64 * GF_SLICES) k_grad_final(PrepGroup grp, Consts k)
+__global__ void __launch_bounds__(64 * GF_SLICES) k_grad_final(PrepGroup grp, Consts k, const BwdScene *__restrict__ scenes,
+                                                               int n_scenes, long long *__restrict__ stats)
 {
+    if (stats && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < CTR_COUNT) {
+        long long v = 0;
+        for (int i = 0; i < n_scenes; ++i) v += scenes[i].counters[threadIdx.x];
+        stats[threadIdx.x] = v;
+    }
     const PrepScene &S = grp.s[blockIdx.y];
     const GView &g = S.g;
     const GradView &grads = S.grads;
@@ -564,12 +570,13 @@ __global__ void __launch_bounds__(64 * GF_SLICES) k_grad_final(PrepGroup grp, Co
     if (DEPTH && grads.depth) grads.depth[i] = (float)(2.0 * PI * gz);
 }
 
-hipError_t launch_grad_final(const PrepGroup &grp, const Consts &k, hipStream_t s)
+hipError_t launch_grad_final(const PrepGroup &grp, const Consts &k, const BwdScene *scenes, int n_scenes, long long *stats,
+                             hipStream_t s)
 {
     const int64_t n = grp.max_n();
-    if (n == 0) return hipSuccess;
-    const dim3 grid((unsigned)((n + 63) / 64), grp.n), block(64 * GF_SLICES);
-#define GWS_GF(CC, DD) hipLaunchKernelGGL((k_grad_final<CC, DD>), grid, block, 0, s, grp, k)
+    if (n == 0 && !stats) return hipSuccess;
+    const dim3 grid((unsigned)std::max<int64_t>(1, (n + 63) / 64), grp.n), block(64 * GF_SLICES);
+#define GWS_GF(CC, DD) hipLaunchKernelGGL((k_grad_final<CC, DD>), grid, block, 0, s, grp, k, scenes, n_scenes, stats)
     const bool d = k.depth_grad != 0;
     switch (k.C) {
     case 1: if (d) GWS_GF(1, true); else GWS_GF(1, false); break;

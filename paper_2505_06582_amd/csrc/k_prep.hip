@@ -695,18 +695,6 @@ hipError_t launch_bin_backward(const Plan &p, const PrepGroup &grp, int max_rang
     return hipGetLastError();
 }
 
-__global__ void k_copy_counters(const long long *__restrict__ src, long long *__restrict__ dst)
-{
-    const int t = threadIdx.x;
-    if (t < CTR_COUNT) dst[t] = src[t];
-}
-
-hipError_t launch_copy_counters(const long long *src, long long *dst, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_copy_counters, dim3(1), dim3(64), 0, s, src, dst);
-    return hipGetLastError();
-}
-
 // Scene tables: copy the by-value table to device memory and form the prefix sums of the
 // per-scene work-item counts (so one persistent launch can walk every scene's items).
 __global__ void k_fwd_table(FwdTab tab, FwdScene *__restrict__ dst, int32_t *__restrict__ prefix,

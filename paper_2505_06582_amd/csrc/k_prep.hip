@@ -117,12 +117,16 @@ int64_t sort_table_words(int64_t n) { return (int64_t)256 * sort_blocks(n); }
 // Rank of the lane's digit among the wavefront's keys so far; cnt is the wavefront's row of counts.
 static __device__ __forceinline__ uint32_t sort_rank(uint32_t *cnt, uint32_t dg, bool valid)
 {
-    uint64_t same = __ballot(valid);
+    const uint64_t on = __ballot(valid);
+    uint32_t lo = (uint32_t)on, hi = (uint32_t)(on >> 32);
 #pragma unroll
     for (int bit = 0; bit < 8; ++bit) {
-        const uint64_t bb = __ballot((dg >> bit) & 1u);
-        same &= ((dg >> bit) & 1u) ? bb : ~bb;
+        const int32_t m = (int32_t)(dg << (31 - bit)) >> 31;  // the digit's bit in every position
+        const uint64_t bb = __ballot(m);
+        lo &= ~((uint32_t)bb ^ (uint32_t)m);
+        hi &= ~((uint32_t)(bb >> 32) ^ (uint32_t)m);
     }
+    const uint64_t same = ((uint64_t)hi << 32) | lo;
     const uint32_t below = (uint32_t)rank_below(same), old = cnt[dg];
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -472,20 +476,62 @@ hipError_t launch_records(const PrepGroup &grp, const Consts &k, bool poly, hipS
 // candidates are split into chunks of CH; CH grows until the tiles with more than one
 // chunk need at most max_slots partial-sum slots (bounded workspace).
 // ---------------------------------------------------------------------------------
-static __device__ uint32_t block_excl_scan_1024(uint32_t v, uint32_t *tmp, uint32_t *total)
+// Scans over the 1024 threads: shuffles within each wavefront, the sixteen totals through LDS
+// (s_wave, free again on return).
+template <class Op>
+static __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, Op op)
 {
-    tmp[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const uint32_t t = threadIdx.x >= off ? tmp[threadIdx.x - off] : 0u;
-        __syncthreads();
-        tmp[threadIdx.x] += t;
-        __syncthreads();
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(v, o);
+        if ((int)(threadIdx.x & 63) >= o) v = op(v, t);
     }
-    const uint32_t incl = tmp[threadIdx.x];
-    *total = tmp[1023];
+    return v;
+}
+
+static __device__ uint32_t block_excl_scan_1024(uint32_t v, uint32_t *s_wave, uint32_t *total)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t incl = wave_incl_scan(v, [](uint32_t x, uint32_t y) { return x + y; });
+    if (lane == 63) s_wave[wave] = incl;
     __syncthreads();
-    return incl - v;
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        const uint32_t t = s_wave[w];
+        before += w < wave ? t : 0u;
+        all += t;
+    }
+    *total = all;
+    __syncthreads();
+    return before + incl - v;
+}
+
+// Largest value of the threads before this one (0 for the first).
+static __device__ uint32_t block_excl_max_1024(uint32_t v, uint32_t *s_wave)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t incl = wave_incl_scan(v, [](uint32_t x, uint32_t y) { return max(x, y); });
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    uint32_t m = __shfl_up(incl, 1);
+    if (lane == 0) m = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) m = w < wave ? max(m, s_wave[w]) : m;
+    __syncthreads();
+    return m;
+}
+
+static __device__ unsigned long long block_sum_1024(unsigned long long v, unsigned long long *s_sum)
+{
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = v;
+    __syncthreads();
+    unsigned long long all = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) all += s_sum[w];
+    return all;
 }
 
 __global__ void __launch_bounds__(1024) k_bin_forward(const int32_t *__restrict__ tile_bucket, int ntiles, PrepGroup grp)
@@ -499,8 +545,8 @@ __global__ void __launch_bounds__(1024) k_bin_forward(const int32_t *__restrict_
     const int64_t max_items = S.max_items, max_slots = S.max_slots;
     const int base_chunk = S.base_chunk;
     long long *__restrict__ counters = S.counters;
-    __shared__ uint32_t tmp[1024];
-    __shared__ unsigned long long red[1024];
+    __shared__ uint32_t tmp[16];
+    __shared__ unsigned long long red[16];
     __shared__ int32_t chunk_sh;
     // cum[b] = number of valid Gaussians with bucket >= b: the largest end at or above b
     {
@@ -508,15 +554,7 @@ __global__ void __launch_bounds__(1024) k_bin_forward(const int32_t *__restrict_
         const int b0 = (1023 - threadIdx.x) * per;  // thread 0 owns the highest buckets
         uint32_t m = 0;
         for (int j = 0; j < per; ++j) m = max(m, bucket_end[b0 + j]);
-        tmp[threadIdx.x] = m;
-        __syncthreads();
-        for (int off = 1; off < 1024; off <<= 1) {
-            const uint32_t t = threadIdx.x >= off ? tmp[threadIdx.x - off] : 0u;
-            __syncthreads();
-            tmp[threadIdx.x] = max(tmp[threadIdx.x], t);
-            __syncthreads();
-        }
-        uint32_t run = threadIdx.x ? tmp[threadIdx.x - 1] : 0u;
+        uint32_t run = block_excl_max_1024(m, tmp);
         for (int j = per - 1; j >= 0; --j) {
             run = max(run, bucket_end[b0 + j]);
             cum[b0 + j] = run;
@@ -530,14 +568,8 @@ __global__ void __launch_bounds__(1024) k_bin_forward(const int32_t *__restrict_
         tile_L[t] = (int32_t)L;
         sumL += L;
     }
-    red[threadIdx.x] = sumL;
-    __syncthreads();
-    for (int off = 512; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-        __syncthreads();
-    }
+    const unsigned long long sum = block_sum_1024(sumL, red);
     if (threadIdx.x == 0) {
-        const unsigned long long sum = red[0];
         // multi-chunk tiles need <= 2 sum / CH slots: the configured base chunk, grown to fit
         long long ch = base_chunk;
         const long long need = (long long)((2ull * sum + (unsigned long long)max_slots - 1) / (unsigned long long)max_slots);
@@ -607,8 +639,8 @@ __global__ void __launch_bounds__(1024) k_bin_backward(const int32_t *__restrict
     const int64_t max_bitems = S.max_bitems, n = S.g.n;
     long long *__restrict__ counters = S.counters;
     const int chunk = S.chunk;
-    __shared__ uint32_t tmp[1024];
-    __shared__ unsigned long long red[1024];
+    __shared__ uint32_t tmp[16];
+    __shared__ unsigned long long red[16];
     __shared__ int32_t trb_sh, nr_sh;
     __shared__ int32_t s_K[BWD_K_LDS];
     const int64_t nvalid = n - counters[CTR_NCULLED];
@@ -622,14 +654,8 @@ __global__ void __launch_bounds__(1024) k_bin_backward(const int32_t *__restrict
     };
     unsigned long long sumK = 0;
     for (int b = threadIdx.x; b < nchunks; b += 1024) sumK += (unsigned long long)K_of(b);
-    red[threadIdx.x] = sumK;
-    __syncthreads();
-    for (int off = 512; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-        __syncthreads();
-    }
+    const unsigned long long sum = block_sum_1024(sumK, red);
     if (threadIdx.x == 0) {
-        const unsigned long long sum = red[0];
         long long trb = 1;
         // items <= sum / TRB + nchunks <= max_bitems
         const long long room = max_bitems - nchunks;

@@ -134,6 +134,15 @@ __device__ __forceinline__ uint32_t row_block_mask(float a, float b2, float g, f
     return m;
 }
 
+// A persistent work-group's next item: its own number first, then from the queue (which starts at
+// the number of work-groups).  Taken from the queue too, the first items, the heaviest, went to the
+// work-groups in the order of their arrival, which gathers them on the XCD nearest the counter in some
+// processes: 12000 tilted Gaussians at 1920 x 1080 x 3 took 2.2 ms in some and 2.6 in others.
+static __device__ __forceinline__ int next_item(bool first, long long *queue)
+{
+    return first ? (int)blockIdx.x : (int)gridDim.x + (int)atomicAdd((unsigned long long *)queue, 1ull);
+}
+
 // Sum of a 64-bit counter over the 64 lanes of a wavefront (every lane gets the total).
 // Transposed butterfly reduction of V (8 or 16) per-lane values over the 64 lanes of a
 // wavefront.  Each transposed step pairs value i with value i + h and lane l with lane

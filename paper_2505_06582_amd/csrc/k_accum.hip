@@ -67,15 +67,17 @@ __global__ void __launch_bounds__(WG, waves_per_simd(F)) k_accumulate(Consts k, 
     // illumination): the support tests and the envelope take frequencies relative to it
     const float mrxf = (float)k.mrx, mryf = (float)k.mry;
 
+    bool first = true;
     for (;;) {
         if (tid == 0) {
-            const int q = (int)atomicAdd((unsigned long long *)queue, 1ull);
+            const int q = next_item(first, queue);
             int sc = 0;
             if (q < total_items)
                 while (sc + 1 < n_scenes && prefix[sc + 1] <= q) ++sc;
             s_item = q;
             s_scene = sc;
         }
+        first = false;
         __syncthreads();
         const int gitem = s_item, scene = s_scene;
         __syncthreads();

@@ -233,15 +233,17 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
     L.dx = (float)(col - 8);
     L.dy = (float)(yi - 8);
 
+    bool first = true;
     for (;;) {
         if (tid == 0) {
-            const int q = (int)atomicAdd((unsigned long long *)queue, 1ull);
+            const int q = next_item(first, queue);
             int sc = 0;
             if (q < total_items)
                 while (sc + 1 < n_scenes && prefix[sc + 1] <= q) ++sc;
             s_item = q;
             s_scene = sc;
         }
+        first = false;
         __syncthreads();
         const int gitem = __builtin_amdgcn_readfirstlane(s_item), scene = __builtin_amdgcn_readfirstlane(s_scene);
         __syncthreads();

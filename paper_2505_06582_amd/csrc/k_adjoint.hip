@@ -171,15 +171,17 @@ __global__ void __launch_bounds__(adj_wg(C, DEPTH), adj_waves_per_simd(C, DEPTH)
     const float dyr = (float)(row4 - ADJ_SH / 2);  // row offset from the sub-tile centre at block 0
     const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
 
+    bool first = true;
     for (;;) {
         if (tid == 0) {
-            const int q = (int)atomicAdd((unsigned long long *)queue, 1ull);
+            const int q = next_item(first, queue);
             int sc = 0;
             if (q < total_items)
                 while (sc + 1 < n_scenes && prefix[sc + 1] <= q) ++sc;
             s_item = q;
             s_scene = sc;
         }
+        first = false;
         __syncthreads();
         // wave-uniform from here on: scalar loads and scalar control flow
         const int q = __builtin_amdgcn_readfirstlane(s_item), sc = __builtin_amdgcn_readfirstlane(s_scene);

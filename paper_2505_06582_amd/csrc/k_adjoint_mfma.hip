@@ -169,15 +169,17 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
     const float lim = uniform_f((float)(k.tau2 * (1.0 + 1e-5)) + 1e-4f);
     const float mrxf = uniform_f((float)k.mrx), mryf = uniform_f((float)k.mry);
 
+    bool first = true;
     for (;;) {
         if (tid == 0) {
-            const int q = (int)atomicAdd((unsigned long long *)queue, 1ull);
+            const int q = next_item(first, queue);
             int sc = 0;
             if (q < total_items)
                 while (sc + 1 < n_scenes && prefix[sc + 1] <= q) ++sc;
             s_item = q;
             s_scene = sc;
         }
+        first = false;
         if (tid < 8) s_hist[tid] = 0;
         if (tid < 3) s_cnt[tid] = s_dcnt[tid] = s_next[tid] = s_tcnt[tid] = 0;
         __syncthreads();

@@ -265,8 +265,10 @@ __global__ void __launch_bounds__(TWG, tilt_waves(C)) k_tilt_accumulate(Consts k
     for (int f = 0; f < TF; ++f) dyf[f] = (float)(row0 + 4 * f - 8);
     long long pairs = 0, cand = 0;
 
+    bool first = true;
     for (;;) {
-        if (tid == 0) s_tile = (int)atomicAdd((unsigned long long *)&counters[CTR_WORK], 1ull);
+        if (tid == 0) s_tile = next_item(first, &counters[CTR_WORK]);
+        first = false;
         __syncthreads();
         const int q = s_tile;
         __syncthreads();
@@ -597,8 +599,10 @@ __global__ void __launch_bounds__(TWG, tilt_adj_waves(C)) k_tilt_adjoint(Consts 
     const float dxf = (float)(col - 16);
     long long pairs = 0;
 
+    bool first = true;
     for (;;) {
-        if (tid == 0) s_tile = (int)atomicAdd((unsigned long long *)&counters[CTR_WORK], 1ull);
+        if (tid == 0) s_tile = next_item(first, &counters[CTR_WORK]);
+        first = false;
         __syncthreads();
         const int q = s_tile;
         __syncthreads();

@@ -1014,8 +1014,10 @@ static hipError_t launch_tilt_adjoint_c(const Consts &k, const TRec *rec, const 
     // 4.71 -> 1.11 ms (one part per 8192: 300 items), 40000 at 256 x 256 2.09 -> 0.59, 12000 at 1920 x 1080 x 3
     // 4.88 -> 4.61; four items per work-group: 10.2 ms for 40000 at 1280 x 1024 x 3, eight 9.8.
     const int tiles = ((k.nx + TT - 1) / TT) * ((k.ny + TT - 1) / TT);
-    int nparts = (int)std::min<int64_t>(std::max(1, TILT_ADJ_ITEMS * n_cu * nb / tiles), (n + 511) / 512);
-    nparts = std::max(nparts, 1);
+    // Never fewer parts than the forward's (one per 8192 Gaussians): many long items on a large grid
+    // hold the tail too.
+    const int64_t fill = std::min<int64_t>(TILT_ADJ_ITEMS * n_cu * nb / tiles, (n + 511) / 512);
+    const int nparts = (int)std::max<int64_t>(fill, tilt_parts(n));
     const int nq = tilt_queue_len(k.nx, k.ny) * nparts;
     const int grid = std::max(1, std::min(n_cu * nb, nq));
     hipLaunchKernelGGL(k_tilt_adjoint<C>, dim3(grid), dim3(TWG), 0, s, k, rec, rect, n, gspec, off, part, nq, nparts,

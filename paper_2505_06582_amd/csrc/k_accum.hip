@@ -341,7 +341,7 @@ bool grid_has_evanescent(const Consts &k)
 // 50000 Gaussians of 2-20 pixels at three wavelengths, this kernel against the matrix cores
 // (ms): 1000 x 750 0.224 / 0.424 / 2.08 against 0.216 / 0.394 / 1.45, 1920 x 1080 0.339 / 0.820 / 4.53
 // against 0.315 / 0.551 / 2.75.  Above, the time is the larger matter (1e6 at 3840 x 2160: 304 ms
-// against 123) and the matrix-core sum also the closer one (4.5e-6 against 1.4e-6).
+// against 119) and the matrix-core sum also the closer one (4.5e-6 against 1.4e-6).
 bool accumulate_on_mfma(const Consts &k, int F)
 {
     return F == 4 && !grid_has_evanescent(k) && (int64_t)k.nx * k.ny >= (int64_t)ACC_MFMA_POINTS;

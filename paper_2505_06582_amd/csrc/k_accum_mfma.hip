@@ -41,7 +41,7 @@
 // Bound now: VALU issue (85 % busy; the matrix units a quarter), 45 VALU instructions per
 // (Gaussian, sub-tile) at three wavelengths, a fifth of them staging, against 146 term by
 // term.  Forward of 1e5 Gaussians at 1080 x 1920 x 3: 8.6 -> 4.6 ms; 1e6 at 2160 x 3840 x 3: 304 ->
-// 123 ms.  Three wavefronts per SIMD without spills: with accumulators for t^2 too, 4.9 ms.
+// 119 ms.  Three wavefronts per SIMD without spills: with accumulators for t^2 too, 4.9 ms.
 #include "mfma_f16.h"
 
 namespace gws {

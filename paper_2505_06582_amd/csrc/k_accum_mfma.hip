@@ -51,6 +51,7 @@ constexpr int MM_CAND = 1024;            // candidates tested per round
 constexpr int MM_SLOTS = 96;             // a wavefront's list: up to 15 entries kept, 64 new, padding to 16
 constexpr int MM_XS = 4, MM_YS = 5;      // powers of two carried by X and Y (kept inside fp16's normal range)
 constexpr int MM_E_NONE = -100000;
+constexpr int MM_SLACK = 80;             // powers of two by which a term-by-term term may exceed the running exponent
 constexpr int MM_EMIT = 32;              // passes after which the accumulators move to the output
 
 // An entry of a wavefront's list, 12 + 4 C floats.  Separable: lx, alpha, ly, gamma | r_x's upper
@@ -352,8 +353,9 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                 if (j0 + lane < total) {
                     r0 = load4(rp);
                     const float4_t am = load4(rp->amp);
-                    if (ellipse_meets_rect_r(r0.x, r0.y, r0.z, 0.5f * __builtin_amdgcn_rcpf(r0.x), 0.5f * __builtin_amdgcn_rcpf(r0.z),
-                                             lim, x0, x1, y0, y1)) {
+                    const float qmin = ellipse_min_q(r0.x, r0.y, r0.z, 0.5f * __builtin_amdgcn_rcpf(r0.x),
+                                                     0.5f * __builtin_amdgcn_rcpf(r0.z), x0, x1, y0, y1);
+                    if (qmin <= lim) {
                         const double xe = sx + 7.5 - k.mrx, ye = sy + 7.5 - k.mry;
                         const double ax = (double)r0.x * xe, gy = (double)r0.z * ye, b2 = r0.y;
                         const double q0 = fmin(xe * (ax + b2 * ye) + gy * ye, 1e6), qr = rint(q0);
@@ -371,8 +373,13 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                         const bool ok = fmaxf(ex, ey) <= 10.0f && az <= zlim && ph <= 1e-3f &&
                                         ph * aa <= 1e-6f && ampmax <= 1e30f && fmaf(-r0.y, r0.y, ag4) >= 0.04f * ag4;
                         cls = ok ? cross_class(aa) : 0;
-                        // exponent of the entry's largest term at the sub-tile's centre
-                        if (ampmax > 0.0f && ampmax <= 3.4028234663852886e38f) ee = ilogbf(ampmax) + 1 - min(qi, 200);
+                        // exponent of a separable entry's largest term, within 2^20: the one at the sub-tile's
+                        // centre.  Any other entry is FP32 all through and only has to keep to its range: it
+                        // asks for MM_SLACK less than its largest term (a steep envelope can fall by hundreds
+                        // of powers of two from the sub-tile's edge to its centre), so that its factor
+                        // 2^(XS + YS - erun) amp stays below 2^(8 + 32 + MM_SLACK)
+                        if (ampmax > 0.0f && ampmax <= 3.4028234663852886e38f)
+                            ee = ilogbf(ampmax) + 1 - (cls ? min(qi, 200) : (int)fminf(fmaxf(qmin, 0.0f), 32.0f) + MM_SLACK);
                     }
                 }
                 const uint64_t b7 = __ballot(cls == 7), b6 = __ballot(cls == 6), b5 = __ballot(cls == 5), b4 = __ballot(cls == 4),

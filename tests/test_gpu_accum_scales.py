@@ -1,0 +1,81 @@
+"""GPU parity of the matrix-core spectrum accumulation with the FP64 oracle where the scales of its
+factors can go wrong: supports of a few frequencies (an envelope that falls by many powers of two within
+a sub-tile), record amplitudes down to FP32's smallest numbers, wavelengths of very different
+strength, sub-tiles whose centre lies beyond the grid."""
+import math
+
+import numpy as np
+import pytest
+
+import gwsgen
+from gwsgen import Grid
+from gpu_util import oracle_dft_ready, problem, rel_l2, scene_to_torch, to_numpy
+
+pytestmark = pytest.mark.gpu
+
+# A term's factors carry 1e-7 rms each from the polynomial and the fp16 pairs; the phase's FP32
+# roundings (three at up to 4 revolutions, 2^-22 of a revolution each, 2 pi / sqrt(3)) are 1.5e-6 at
+# most and half of that in the mean.  2e-6 bounds their sum.
+TOL = 2e-6
+LAMBDAS = (638e-9, 520e-9, 450e-9, 570e-9)
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    import paper_2505_06582_amd as gws
+    assert torch.cuda.is_available()
+    return gws.context(0)
+
+
+def spectra(ctx, scene, grid, mx, my):
+    """(the library's spectrum at centred indices, the oracle's), and the field must be finite."""
+    import torch
+    mx, my = (mx % grid.nx).astype(np.int32), (my % grid.ny).astype(np.int32)
+    field, spec = ctx.forward(problem(grid), scene_to_torch(scene), want_spectrum=True)
+    assert bool(torch.isfinite(torch.view_as_real(field)).all())
+    return to_numpy(spec)[:, my, mx], oracle_dft_ready(scene, grid, mx, my)
+
+
+def block(half):
+    m = np.arange(-half, half + 1)
+    my, mx = np.meshgrid(m, m, indexing="ij")
+    return mx.ravel(), my.ravel()
+
+
+def wide(grid, frac, seed):
+    """One Gaussian of standard deviation frac * W on both axes."""
+    g = gwsgen.make_scene(1, grid, seed, depth_range=(-5e-3, 5e-3))
+    g.cov_xx[:] = g.cov_yy[:] = np.float32((frac * grid.nx * grid.px) ** 2)
+    g.cov_xy[:] = 0.0
+    g.amplitude[:] = 0.5
+    g.opacity[:] = 1.0
+    return g
+
+
+@pytest.mark.parametrize("frac", [0.1, 0.15, 0.2, 0.25, 0.3, 0.5])
+def test_one_wide_gaussian(ctx, frac):
+    grid = Grid(2400, 1800, 8e-6, 8e-6, LAMBDAS[:2])
+    got, ref = spectra(ctx, wide(grid, frac, 4), grid, *block(20))
+    assert rel_l2(got, ref) < TOL
+
+
+@pytest.mark.parametrize("n", [2, 129, 1025])
+def test_a_wide_gaussian_after_ordinary_ones(ctx, n):
+    """The widest is last in the order: alone in its tile's last chunk of 128 for 129 and 1025."""
+    grid = Grid(2400, 1800, 8e-6, 8e-6, LAMBDAS[:1])
+    scene = gwsgen.Scene.concat([gwsgen.make_scene(n - 1, grid, 40 + n, sigma_px=(17.0, 20.0)), wide(grid, 0.2, 5)])
+    got, ref = spectra(ctx, scene, grid, *block(20))
+    assert rel_l2(got, ref) < TOL
+
+
+def test_faint_ordinary_gaussians_under_a_wide_one(ctx):
+    """Where the wide one's support ends (8 to 40 frequencies from DC) only the ordinary ones are left:
+    the scale there must be the wide one's value there, not its peak."""
+    grid = Grid(2400, 1800, 8e-6, 8e-6, LAMBDAS[:1])
+    scene = gwsgen.Scene.concat([gwsgen.make_scene(60, grid, 6), wide(grid, 0.2, 5)])
+    scene.amplitude[:, :60] *= np.float32(1e-3)
+    mx, my = block(40)
+    far = np.hypot(mx, my) > 8
+    got, ref = spectra(ctx, scene, grid, mx[far], my[far])
+    assert rel_l2(got, ref) < TOL

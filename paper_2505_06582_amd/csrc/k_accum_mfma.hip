@@ -427,12 +427,14 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                     float4_t *dst = reinterpret_cast<float4_t *>(&s_w[wave][pos][0]);
                     const float4_t r1 = load4(&rp->rx), kap = load4(rp->kappa), am = load4(rp->amp);
                     const uint32_t rx = __float_as_uint(r1.x), ry = __float_as_uint(r1.y);
-                    float ik0 = 1.0f, e0;
+                    float ik0 = 1.0f, e0 = 1.0f;  // the amplitude's factor is e0 2^ne: e0 near 1, ne beyond FP32's range for the
+                    int ne;                       // smallest amplitudes, so it is applied to the amplitude itself
                     if (cls > 0) {
                         float k0, k1, k2, k3, k4;
                         cross_poly(r0.y * MM_A_OF_BETA2, cls, k0, k1, k2, k3, k4);
                         ik0 = __builtin_amdgcn_rcpf(k0);
-                        e0 = k0 * ldexpf(__builtin_amdgcn_exp2f(qf), max(MM_XS - es - qi, -300));
+                        e0 = k0 * __builtin_amdgcn_exp2f(qf);
+                        ne = MM_XS - es - qi;
                         dst[0] = (float4_t){lx, r0.x, ly, r0.z};
                         const int32_t rx20 = (int32_t)(rx & 0xfffff000u), ry20 = (int32_t)(ry & 0xfffff000u);
                         dst[1] = (float4_t){(float)rx20 * 0x1p-32f, (float)(rx & 0xfffu) * 0x1p-32f,
@@ -444,7 +446,7 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                         pairs += SUBX * SUBX / 64;
                     } else {
                         const uint32_t rows = row_block_mask<MF>(r0.x, r0.y, r0.z, lim, x0, x1, sy, hy, mryf);
-                        e0 = ldexpf(1.0f, max(min(MM_XS + MM_YS - es, 127), -149));
+                        ne = MM_XS + MM_YS - es;
                         dst[0] = (float4_t){r0.x, r0.y, r0.z, r0.w};
                         dst[1] = (float4_t){r1.z, r1.w, __uint_as_float(rows), 0.0f};
                         pairs += __popc(rows);
@@ -464,7 +466,7 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                         } else {
                             bs = (float)frac_m((double)kap[c] - ramp_rev - (double)r0.w * s_d0[wave][c]);
                         }
-                        dst[3 + c] = (float4_t){bs, am[c] * e0, r0.w * s_phi[wave][c] * ik0, r0.w};
+                        dst[3 + c] = (float4_t){bs, ldexpf(am[c], ne) * e0, r0.w * s_phi[wave][c] * ik0, r0.w};
                     }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

@@ -79,3 +79,37 @@ def test_faint_ordinary_gaussians_under_a_wide_one(ctx):
     far = np.hypot(mx, my) > 8
     got, ref = spectra(ctx, scene, grid, mx[far], my[far])
     assert rel_l2(got, ref) < TOL
+
+
+@pytest.mark.parametrize("log2amp", [-100, -118, -122, -124, -126, -128, -130, -136, -140])
+@pytest.mark.parametrize("zero", [False, True])
+def test_smallest_amplitudes(ctx, log2amp, zero):
+    """Record amplitudes of 2^log2amp, alone on their sub-tiles or beside a wavelength of amplitude 0.  Record
+    and spectrum are FP32 numbers, below 2^-126 in steps of 2^-149: half a step each, of values
+    that are 2^-6 of the amplitude where the support's energy is."""
+    grid = Grid(2400, 1800, 8e-6, 8e-6, LAMBDAS[:2])
+    scene = gwsgen.make_scene(3, grid, 21, sigma_px=(6.0, 8.0), depth_range=(-5e-3, 5e-3))
+    det = scene.cov_xx.astype(np.float64) * scene.cov_yy - scene.cov_xy.astype(np.float64) ** 2
+    norm = 2 * math.pi * np.sqrt(det) / (grid.px * grid.py * grid.nx * grid.ny)
+    scene.opacity[:] = 1.0
+    scene.amplitude[:] = (2.0 ** log2amp / norm).astype(np.float32)
+    if zero:
+        scene.amplitude[1] = 0.0
+    rng = np.random.default_rng(3)
+    got, ref = spectra(ctx, scene, grid, rng.integers(-100, 100, 700), rng.integers(-80, 80, 700))
+    step = 2.0 ** -149 / 2.0 ** log2amp
+    err = rel_l2(got[0], ref[0])
+    print("  2^%d: %.3e" % (log2amp, err), flush=True)
+    assert err < TOL + (0.5 + 0.5 * 64) * step
+    if zero:
+        assert not np.any(got[1])
+
+
+@pytest.mark.parametrize("log2amp", [-40, -90, -120])
+def test_a_faint_wide_gaussian(ctx, log2amp):
+    grid = Grid(2400, 1800, 8e-6, 8e-6, LAMBDAS[:1])
+    scene = wide(grid, 0.25, 4)
+    norm = 2 * math.pi * float(scene.cov_xx[0]) / (grid.px * grid.py * grid.nx * grid.ny)
+    scene.amplitude[:] = np.float32(2.0 ** log2amp / norm)
+    got, ref = spectra(ctx, scene, grid, *block(20))
+    assert rel_l2(got, ref) < TOL

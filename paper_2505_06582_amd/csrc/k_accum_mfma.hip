@@ -273,7 +273,9 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 const double il = k.inv_lambda[c];
-                const double D0 = dprop_m(nx0 * nx0 + ny0 * ny0, il);
+                // the centre can lie up to 7.5 indices beyond the grid, and there beyond the propagating disk:
+                // any finite D0 will do then, every entry going term by term
+                const double D0 = dprop_m(fmin(nx0 * nx0 + ny0 * ny0, il * il), il);
                 s_d0[wave][c] = D0;
                 const double wm = il * il - xm * xm - ym * ym;
                 L.gx[c] = L.gy[c] = 0.0f;

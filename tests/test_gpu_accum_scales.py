@@ -113,3 +113,20 @@ def test_a_faint_wide_gaussian(ctx, log2amp):
     scene.amplitude[:] = np.float32(2.0 ** log2amp / norm)
     got, ref = spectra(ctx, scene, grid, *block(20))
     assert rel_l2(got, ref) < TOL
+
+
+@pytest.mark.parametrize("nx,ny", [(2500, 1800), (2500, 2500), (3750, 1250)])
+def test_sub_tiles_beyond_the_propagating_disk(ctx, nx, ny):
+    """Half sizes of 16 i + 1 ... 7: the outermost sub-tiles' centres lie beyond the grid, and with a pitch
+    just above lambda / sqrt(2) beyond 1 / lambda, though every grid frequency propagates."""
+    lam = 520e-9
+    p = lam / math.sqrt(2.0) * 1.001
+    grid = Grid(nx, ny, p, p, (lam,))
+    scene = gwsgen.make_scene(40, grid, 12, depth_range=(-10e-6, 10e-6), sigma_px=(0.5, 0.8))
+    rng = np.random.default_rng(5)
+    hx, hy = nx // 2, ny // 2
+    mx = np.concatenate([rng.integers(-hx, hx, 500), rng.integers(hx - 16, hx, 200)])
+    my = np.concatenate([rng.integers(-hy, hy, 500), rng.integers(-hy, -hy + 16, 200)])
+    got, ref = spectra(ctx, scene, grid, mx, my)
+    # at the disk's edge k_z falls by 0.1 / lambda within a sub-tile: 2 revolutions at 10 um, as above
+    assert rel_l2(got, ref) < TOL

@@ -19,8 +19,8 @@
 // Precision.  Each FP32 factor is split into two fp16 numbers, both rounded to nearest
 // (x = h + l, |x - h - l| <= 2^-24 |x|, FP32's own rounding), the products h h, h l and l h are
 // accumulated in FP32 (l l is below 2^-24).  fp16's range is met by exact powers of two: the
-// running exponent e of the largest term met so far is taken out of the factors (accumulators
-// are rescaled when it grows) and factors are kept in 2^+-15.  The polynomial is the Taylor
+// running exponent e of the wavelength's largest term met so far is taken out of the factors
+// (accumulators are rescaled when it grows) and factors are kept in 2^+-15.  The polynomial is the Taylor
 // polynomial with the next two orders projected onto it by least squares over the
 // sub-tile's 256 points: relative rms error at most 1e-7 for |a| <= 0.0175, 0.08, 0.2, 0.35 with
 // 3, 4, 5, 6 coefficients.  q at the centre, its gradient and the phase base are formed in FP64
@@ -50,7 +50,7 @@ constexpr int MF = 4;                    // 4-row blocks (and result registers) 
 constexpr int MM_CAND = 1024;            // candidates tested per round
 constexpr int MM_SLOTS = 96;             // a wavefront's list: up to 15 entries kept, 64 new, padding to 16
 constexpr int MM_XS = 4, MM_YS = 5;      // powers of two carried by X and Y (kept inside fp16's normal range)
-constexpr int MM_E_NONE = -100000;
+constexpr int MM_E_NONE = -100000;       // so far only zeros, which any power of two leaves
 constexpr int MM_SLACK = 80;             // powers of two by which a term-by-term term may exceed the running exponent
 constexpr int MM_EMIT = 32;              // passes after which the accumulators move to the output
 
@@ -201,7 +201,7 @@ static __device__ __forceinline__ void mm_pass(const float (&ent)[MM_SLOTS][mm_f
 }
 
 // Wavefronts per SIMD the kernel is compiled for.
-__host__ __device__ constexpr int mm_waves(int c) { return c <= 3 ? 3 : 2; }
+__host__ __device__ constexpr int mm_waves(int c) { return c == 1 ? 4 : c <= 3 ? 3 : 2; }
 
 // Work items, tile order, chunks and partial-sum slots are k_accumulate's (F = 4).  Uniform values
 // are taken through readfirstlane: held in vector registers they spilt the matrix passes.
@@ -302,7 +302,9 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
         for (int r = 0; r < 2; ++r)
 #pragma unroll
             for (int c = 0; c < C; ++c) M.re[r][c] = M.im[r][c] = (float4_t){0.0f, 0.0f, 0.0f, 0.0f};
-        int erun = MM_E_NONE;  // the accumulators hold sums times 2^(XS + YS - erun)
+        int erun[C];  // the accumulators of wavelength c hold sums times 2^(XS + YS - erun[c])
+#pragma unroll
+        for (int c = 0; c < C; ++c) erun[c] = MM_E_NONE;
         bool emitted = false;
         int npass = 0;  // passes in the accumulators
         int kept = 0, keptR = 3;  // entries of the list's front not yet evaluated (< 16), their class
@@ -342,7 +344,8 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
             const bool last = base + MM_CAND >= c1;
             for (int j0 = 0; wave_live && j0 < total; j0 += 64) {
                 int cls = -1;  // -1 not on the sub-tile, 0 term by term, else the class of |a|
-                int ee = MM_E_NONE, qi = 0;
+                int eq = 0, qi = 0;
+                bool grows = false;
                 float4_t r0 = {0.0f, 0.0f, 0.0f, 0.0f};
                 float lx = 0.0f, ly = 0.0f, qf = 0.0f;  // gradient of q at the centre, q there = qi - qf
                 const GRec *rp = rec + s_idx[min(j0 + lane, total - 1)];
@@ -380,16 +383,16 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                         // asks for MM_SLACK less than its largest term (a steep envelope can fall by hundreds
                         // of powers of two from the sub-tile's edge to its centre), so that its factor
                         // 2^(XS + YS - erun) amp stays below 2^(8 + 32 + MM_SLACK)
-                        if (ampmax > 0.0f && ampmax <= 3.4028234663852886e38f)
-                            ee = ilogbf(ampmax) + 1 - (cls ? min(qi, 200) : (int)fminf(fmaxf(qmin, 0.0f), 32.0f) + MM_SLACK);
+                        eq = cls ? min(qi, 200) : (int)fminf(fmaxf(qmin, 0.0f), 32.0f) + MM_SLACK;
+                        // a wavelength is a sum of its own, with a running exponent of its own: a faint one beside a
+                        // strong one would otherwise lose its factors' low fp16 parts
+#pragma unroll
+                        for (int c = 0; c < C; ++c) grows |= fabsf(ldexpf(am[c], -eq - erun[c])) >= 1.0f;
                     }
                 }
                 const uint64_t b7 = __ballot(cls == 7), b6 = __ballot(cls == 6), b5 = __ballot(cls == 5), b4 = __ballot(cls == 4),
                                b3 = __ballot(cls == 3), bd = __ballot(cls == 0);
-                if (__ballot(ee > erun)) {
-#pragma unroll
-                    for (int d = 32; d >= 1; d >>= 1) ee = max(ee, __shfl_xor(ee, d));
-                    ee = __builtin_amdgcn_readfirstlane(ee);
+                if (__ballot(grows)) {
                     if (kept) {  // evaluated at the scale they were written for
                         if (lane < 16 - kept)
                             for (int i = 0; i < mm_floats(C); ++i) s_w[wave][kept + lane][i] = 0.0f;
@@ -400,17 +403,23 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                         kept = 0;
                         keptR = 3;
                     }
-                    const float sc = erun == MM_E_NONE ? 1.0f : ldexpf(1.0f, max(erun - ee, -200));
 #pragma unroll
-                    for (int r = 0; r < 2; ++r)
+                    for (int c = 0; c < C; ++c) {
+                        const float ac = rp->amp[c];
+                        int ee = MM_E_NONE;
+                        if (grows && __builtin_amdgcn_classf(ac, 0x198)) ee = __builtin_amdgcn_frexp_expf(ac) - eq;  // finite, not 0
 #pragma unroll
-                        for (int c = 0; c < C; ++c) {
+                        for (int d = 32; d >= 1; d >>= 1) ee = max(ee, __shfl_xor(ee, d));
+                        const int en = max(__builtin_amdgcn_readfirstlane(ee), erun[c]);
+                        const float sc = erun[c] == MM_E_NONE ? 1.0f : ldexpf(1.0f, max(erun[c] - en, -200));
+#pragma unroll
+                        for (int r = 0; r < 2; ++r) {
                             M.re[r][c] *= sc;
                             M.im[r][c] *= sc;
                         }
-                    erun = ee;
+                        erun[c] = en;
+                    }
                 }
-                const int es = erun == MM_E_NONE ? 0 : erun;
                 const int n7 = kept + __popcll(b7), n6 = n7 + __popcll(b6), n5 = n6 + __popcll(b5), n4 = n5 + __popcll(b4), nf = n4 + __popcll(b3);
                 const int nd = __popcll(bd);
                 auto class_at = [&](int i) { return i < n7 ? 7 : i < n6 ? 6 : (i < n5 ? 5 : (i < n4 ? 4 : 3)); };  // of a new entry
@@ -429,14 +438,14 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                     float4_t *dst = reinterpret_cast<float4_t *>(&s_w[wave][pos][0]);
                     const float4_t r1 = load4(&rp->rx), kap = load4(rp->kappa), am = load4(rp->amp);
                     const uint32_t rx = __float_as_uint(r1.x), ry = __float_as_uint(r1.y);
-                    float ik0 = 1.0f, e0 = 1.0f;  // the amplitude's factor is e0 2^ne: e0 near 1, ne beyond FP32's range for the
-                    int ne;                       // smallest amplitudes, so it is applied to the amplitude itself
+                    float ik0 = 1.0f, e0 = 1.0f;  // the amplitude's factor is e0 2^(ne - erun): e0 near 1, the power beyond FP32's
+                    int ne;                       // range for the smallest amplitudes, so it is applied to the amplitude itself
                     if (cls > 0) {
                         float k0, k1, k2, k3, k4;
                         cross_poly(r0.y * MM_A_OF_BETA2, cls, k0, k1, k2, k3, k4);
                         ik0 = __builtin_amdgcn_rcpf(k0);
                         e0 = k0 * __builtin_amdgcn_exp2f(qf);
-                        ne = MM_XS - es - qi;
+                        ne = MM_XS - qi;
                         dst[0] = (float4_t){lx, r0.x, ly, r0.z};
                         const int32_t rx20 = (int32_t)(rx & 0xfffff000u), ry20 = (int32_t)(ry & 0xfffff000u);
                         dst[1] = (float4_t){(float)rx20 * 0x1p-32f, (float)(rx & 0xfffu) * 0x1p-32f,
@@ -448,7 +457,7 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                         pairs += SUBX * SUBX / 64;
                     } else {
                         const uint32_t rows = row_block_mask<MF>(r0.x, r0.y, r0.z, lim, x0, x1, sy, hy, mryf);
-                        ne = MM_XS + MM_YS - es;
+                        ne = MM_XS + MM_YS;
                         dst[0] = (float4_t){r0.x, r0.y, r0.z, r0.w};
                         dst[1] = (float4_t){r1.z, r1.w, __uint_as_float(rows), 0.0f};
                         pairs += __popc(rows);
@@ -468,7 +477,7 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                         } else {
                             bs = (float)frac_m((double)kap[c] - ramp_rev - (double)r0.w * s_d0[wave][c]);
                         }
-                        dst[3 + c] = (float4_t){bs, ldexpf(am[c], ne) * e0, r0.w * s_phi[wave][c] * ik0, r0.w};
+                        dst[3 + c] = (float4_t){bs, ldexpf(am[c], ne - erun[c]) * e0, r0.w * s_phi[wave][c] * ik0, r0.w};
                     }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -562,7 +571,6 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                 int sx = sx0, sy = sy0, cl = col, rw = row0;
                 asm volatile("" : "+s"(sx), "+s"(sy), "+v"(cl), "+v"(rw));  // formed here, as above
                 const int mxp = sx + cl;
-                const int eo = (erun == MM_E_NONE ? 0 : erun) - MM_XS - MM_YS;
 #pragma unroll
                 for (int f = 0; f < MF; ++f) {
                     const int myp = sy + rw + 4 * f;
@@ -571,6 +579,7 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                     const int mx = mxp < 0 ? mxp + k.nx : mxp, my = myp < 0 ? myp + k.ny : myp;
 #pragma unroll
                     for (int c = 0; c < C; ++c) {
+                        const int eo = erun[c] - MM_XS - MM_YS;
                         float2 v;
                         v.x = ldexpf(fmaf(t, M.re[1][c][f], M.re[0][c][f]), eo);
                         v.y = ldexpf(fmaf(t, M.im[1][c][f], M.im[0][c][f]), eo);

@@ -115,6 +115,24 @@ def test_a_faint_wide_gaussian(ctx, log2amp):
     assert rel_l2(got, ref) < TOL
 
 
+@pytest.mark.parametrize("ratio", [1e-2, 1e-3, 1e-4, 1e-5, 1e-6, 1e-8, 1e-20, 1e-35])
+def test_wavelengths_of_different_strength(ctx, ratio):
+    """Each wavelength is a sum of its own: the same bound for each."""
+    grid = Grid(2400, 1800, 8e-6, 8e-6, LAMBDAS[:3])
+    scene = gwsgen.make_scene(150, grid, 31, depth_range=(-10e-3, 10e-3))
+    scene.amplitude[0] *= np.float32(math.sqrt(ratio))
+    scene.amplitude[2] *= np.float32(ratio)
+    rng = np.random.default_rng(4)
+    got, ref = spectra(ctx, scene, grid, rng.integers(-300, 300, 700), rng.integers(-225, 225, 700))
+    errs = [rel_l2(got[c], ref[c]) for c in range(3)]
+    print("  %g: %s" % (ratio, errs), flush=True)
+    # 1e-35: record amplitudes near 1e-40, in steps of 2^-149, half a step for record and result each (values
+    # 2^-6 of the amplitude)
+    norm = 2 * math.pi * np.sqrt(np.median(scene.cov_xx.astype(np.float64) * scene.cov_yy)) / (grid.px * grid.py * grid.nx * grid.ny)
+    for c, r in ((0, math.sqrt(ratio)), (1, 1.0), (2, ratio)):
+        assert errs[c] < TOL + 33 * 2.0 ** -149 / (r * 0.25 * norm), (c, errs)
+
+
 @pytest.mark.parametrize("nx,ny", [(2500, 1800), (2500, 2500), (3750, 1250)])
 def test_sub_tiles_beyond_the_propagating_disk(ctx, nx, ny):
     """Half sizes of 16 i + 1 ... 7: the outermost sub-tiles' centres lie beyond the grid, and with a pitch

@@ -305,13 +305,13 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
             if (cnt + dcnt == 0) continue;  // uniform
             const int et = __builtin_amdgcn_readfirstlane(S.gexp[sub]);
             {
-                const float sc2 = ldexpf(1.0f, max(min(AM_GS - et, 127), -126));
                 const float2 *gs = S.gpack + (int64_t)sub * C * 256;
                 const int tv = here_v(tid);
                 for (int i = tv; i < C * 128; i += AM_T) {
                     const int c = i >> 7, u = i & 15, vp = (i >> 4) & 7;
                     const float2_t p = load2(gs + c * 256 + 32 * vp + u), p2 = load2(gs + c * 256 + 32 * vp + 16 + u);
-                    float r0 = p.x * sc2, i0 = p.y * sc2, r1 = p2.x * sc2, i1 = p2.y * sc2;
+                    float r0 = ldexpf(p.x, AM_GS - et), i0 = ldexpf(p.y, AM_GS - et);
+                    float r1 = ldexpf(p2.x, AM_GS - et), i1 = ldexpf(p2.y, AM_GS - et);
                     const float w0 = ((float)(2 * vp) - 7.5f) * (1.0f / 7.5f), w1 = ((float)(2 * vp) - 6.5f) * (1.0f / 7.5f);
                     const int at = (u + 16 * (vp >> 1)) * 4 + (vp & 1);
 #pragma unroll
@@ -373,9 +373,7 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
                         const double q0 = fmin(xe * (ax + b2 * ye) + gy * ye, 1e6), qr = rint(q0);
                         lx = (float)(2.0 * ax + b2 * ye);
                         ly = (float)(2.0 * gy + b2 * xe);
-                        e0 = on ? co.w * ldexpf(__builtin_amdgcn_exp2f((float)(qr - q0)),
-                                                max(et - AM_GS - AM_YS - (int)qr, -300))
-                                : 0.0f;
+                        e0 = on ? co.w * ldexpf(__builtin_amdgcn_exp2f((float)(qr - q0)), -(int)qr) : 0.0f;
                         const int cx = sx + 8, cy = sy + 8;
                         const uint32_t ramp = (uint32_t)cx * __float_as_uint(r1.x) + (uint32_t)cy * __float_as_uint(r1.y);
                         const double ramp_rev = (double)ramp * (1.0 / 4294967296.0);
@@ -566,7 +564,8 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
                         if constexpr (!DEPTH) x[C + 5] = i0s;
                     }
                     // sums over the four lane groups: register i of lane l then holds value
-                    // (NVP / 4) (2 b5 + b4) + i
+                    // (NVP / 4) (2 b5 + b4) + i.  The powers of two of Gs and Y come back last: in X they would take
+                    // the factors of a small Gs out of FP32's normal range long before the sums
 #pragma unroll
                     for (int i = 0; i < NVP / 2; ++i) {
                         const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[i]), __float_as_uint(x[i + NVP / 2]), false, false);
@@ -577,7 +576,7 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
                         const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[i]), __float_as_uint(x[i + NVP / 4]), false, false);
                         x[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
                         const int v = (NVP / 4) * g + i;
-                        if (on && v < NV) atomicAdd(&s_acc[o * NV + v], x[i]);  // ds_add_f32, no return
+                        if (on && v < NV) atomicAdd(&s_acc[o * NV + v], ldexpf(x[i], et - AM_GS - AM_YS));  // ds_add_f32, no return
                     }
                 } else {
                     // term by term: lane l takes column l % 16 and rows l / 16 + 4 f

@@ -1,0 +1,64 @@
+"""GPU parity of the matrix-core adjoint with the FP64 oracle gradient where the scales of its operands
+can go wrong: field gradients down to FP32's smallest numbers, wavelengths of very different strength,
+field gradients with a mean (a spectrum with one frequency far above the rest) or with gratings
+(single frequencies on the axes)."""
+import math
+
+import numpy as np
+import pytest
+
+import gwsgen
+import oracle
+from gwsgen import Grid
+from gpu_util import problem, rel_l2, scene_to_torch, to_numpy
+
+pytestmark = pytest.mark.gpu
+
+# Per term the phase's FP32 roundings are 1.5e-6 at most (three of 2^-22 of a revolution), the
+# polynomial and the fp16 pairs 1e-7 each; a sum weighted by m or m^2 may cancel to about a third of
+# its terms' norm.  5e-6 bounds the normwise error of every gradient.
+TOL = 5e-6
+LAMBDAS = (638e-9, 520e-9, 450e-9, 570e-9)
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    import paper_2505_06582_amd as gws
+    assert torch.cuda.is_available()
+    return gws.context(0)
+
+
+def gradients(ctx, scene, grid, G, depth=True):
+    """{name: (the library's, the oracle's for the library's own FP32 spectrum of G)}: the error of the sums
+    alone, without the transform's, which is in proportion to the whole field gradient."""
+    import torch
+    Gt = torch.from_numpy(np.ascontiguousarray(G, dtype=np.complex64)).cuda()
+    got = ctx.backward(problem(grid), scene_to_torch(scene), Gt, want_depth=depth)
+    spec = to_numpy(ctx.dft2d(Gt, -1)).astype(np.complex128)
+    sx, sy = oracle.signed_freq_index(grid.nx), oracle.signed_freq_index(grid.ny)
+    spec *= np.where((sy[:, None] + sx[None, :]) % 2 == 0, 1.0, -1.0) / (grid.nx * grid.ny * grid.px * grid.py)
+    ref = oracle.param_grads_from_spectrum_grad(scene, grid, spec)
+    out = {k: (to_numpy(got[k]), np.asarray(r)) for k, r in ref.items() if got.get(k) is not None}
+    assert len(out) >= (9 if depth else 8)
+    return out
+
+
+@pytest.mark.parametrize("scale", [1e-20, 1e-30, 1e-36, 1e-40])
+def test_smallest_field_gradients(ctx, scale):
+    """Below 2^-126 FP32 numbers are steps of 2^-149.  The sums over wavelengths round products of the field
+    gradient's spectrum (scale sqrt(N)) and the record's amplitude; results round once."""
+    grid = Grid(1024, 1000, 8e-6, 8e-6, LAMBDAS[:1])
+    scene = gwsgen.make_scene(24, grid, 51, depth_range=(-10e-3, 10e-3))
+    G = (gwsgen.make_target(grid, 4242) * np.float32(scale)).astype(np.complex64)
+    half = 2.0 ** -150
+    det = scene.cov_xx.astype(np.float64) * scene.cov_yy - scene.cov_xy.astype(np.float64) ** 2
+    amp = np.median(scene.amplitude[0] * scene.opacity * 2 * math.pi * np.sqrt(det)) / (grid.px * grid.py * grid.nx * grid.ny)
+    spec = scale * math.sqrt(grid.nx * grid.ny)
+    for k, (got, ref) in gradients(ctx, scene, grid, G).items():
+        tol = TOL + half * math.sqrt(ref.size) / np.linalg.norm(ref)
+        if k != "amplitude":
+            tol += 3 * 4 * half / (spec * amp)  # a third, as above
+        e = rel_l2(got, ref)
+        print("  %g %s %.2e (%.2e)" % (scale, k, e, tol), flush=True)
+        assert e < tol, (k, e, tol)

@@ -12,7 +12,7 @@
 //
 // A and B are fp16 pairs as in the forward (k <= 3: products h h, h l, l h; k >= 4, which only
 // multiply c_3 and smaller or c_2 in Z_2, one product), accumulated in FP32.  Gs is scaled by
-// a power of two per sub-tile.  X, the polynomials and all sums are FP32.  W_k of a higher order
+// a power of two per sub-tile and wavelength.  X, the polynomials and all sums are FP32.  W_k of a higher order
 // than a Gaussian's class meets c_k = 0, so results do not depend on which 16 share a pass.
 //
 // Work.  A work-group of four wavefronts owns up to 512 consecutive sorted Gaussians and a range of
@@ -52,31 +52,29 @@ static __device__ __forceinline__ int sub_index(const AdjGeom &geo, int tx, int 
     return ((ty - geo.ty_min) * 4 + s) * (2 * geo.ntx) + (tx - geo.tx_min) * 2 + h;
 }
 
-// Gs sub-tile-major (zero outside the grid) and the largest finite binary exponent per sub-tile.
+// Gs sub-tile-major (zero outside the grid) and the largest finite binary exponent per sub-tile and
+// wavelength (a faint wavelength's Gs on a strong one's scale would lose its low fp16 parts).
 __global__ void __launch_bounds__(256) k_adj_pack_sub(Consts k, AdjGeom geo, const float2 *__restrict__ gspec,
                                                       float2 *__restrict__ gsub, int32_t *__restrict__ gexp)
 {
-    __shared__ int s_e[4];
+    __shared__ int s_e[4][4];
     const int sub = blockIdx.x, t = threadIdx.x, sx = sub % (2 * geo.ntx), sy = sub / (2 * geo.ntx);
     const int mxp = (geo.tx_min * 2 + sx) * 16 + (t & 15), myp = (geo.ty_min * 4 + sy) * 16 + (t >> 4);
     const int hx = k.nx / 2, hy = k.ny / 2;
     const bool in = mxp >= -hx && mxp < hx && myp >= -hy && myp < hy;
     const int mx = mxp < 0 ? mxp + k.nx : mxp, my = myp < 0 ? myp + k.ny : myp;
-    int e = -1000;
     for (int c = 0; c < k.C; ++c) {
         float2 v = make_float2(0.0f, 0.0f);
         if (in) v = gspec[((int64_t)c * k.ny + my) * k.nx + mx];
         const float m = fmaxf(fabsf(v.x), fabsf(v.y));
-        if (m > 0.0f && m <= 3.4028234663852886e38f) e = max(e, ilogbf(m));
+        int e = -1000;
+        if (m > 0.0f && m <= 3.4028234663852886e38f) e = ilogbf(m);
+        for (int d = 32; d >= 1; d >>= 1) e = max(e, __shfl_xor(e, d));
+        if ((t & 63) == 0) s_e[c][t >> 6] = e;
         gsub[((int64_t)sub * k.C + c) * 256 + t] = v;
     }
-    for (int d = 32; d >= 1; d >>= 1) e = max(e, __shfl_xor(e, d));
-    if ((t & 63) == 0) s_e[t >> 6] = e;
     __syncthreads();
-    if (t == 0) {
-        e = max(max(s_e[0], s_e[1]), max(s_e[2], s_e[3]));
-        gexp[sub] = e == -1000 ? 0 : e;
-    }
+    if (t < k.C) gexp[sub * k.C + t] = max(max(s_e[t][0], s_e[t][1]), max(s_e[t][2], s_e[t][3]));
 }
 
 // Geometry of a sub-tile, the same for every scene (float words of its row of the table): the
@@ -136,16 +134,18 @@ hipError_t launch_adj_pack_sub(const Consts &k, const AdjGeom &geo, int n_scenes
     hipLaunchKernelGGL(k_adj_sub_geo, dim3(nsub), dim3(128), 0, s, k, geo, table);
     for (int i = 0; i < n_scenes; ++i)
         hipLaunchKernelGGL(k_adj_pack_sub, dim3(nsub), dim3(256), 0, s, k, geo, gspecs + (int64_t)i * M,
-                           gsub + (int64_t)i * per, gexp + (int64_t)i * nsub);
+                           gsub + (int64_t)i * per, gexp + (int64_t)i * nsub * k.C);
     return hipGetLastError();
 }
 
 // The sub-tile's tables in LDS.
-template <int C>
+template <int C, int NVP>
 struct AmTile {
     uint32_t a[C][4][2][256];  // conj(Gs) w^k: [c][k][high, low][lane * 4 + r], r = re 01, re 23, im 01, im 23
     float geo[C][AS_C];        // the sub-tile's row of the geometry table
     float dd[C][256];          // D_c(nu) - D_c(centre), for the term-by-term entries
+    int rel[C];                // exponent of the wavelength's Gs less the largest
+    int ex[NVP];               // exponent of each sum
     __device__ __forceinline__ double d0(int c) const { return *reinterpret_cast<const double *>(&geo[c][32]); }
 };
 
@@ -155,7 +155,7 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
                    const int32_t *__restrict__ prefix, int n_scenes, long long *__restrict__ queue, const float *__restrict__ sgeo, AdjGeom geo)
 {
     constexpr int NV = adj_nv(C, DEPTH), NVP = (NV + 3) & ~3;
-    __shared__ __attribute__((aligned(16))) AmTile<C> s_t;
+    __shared__ __attribute__((aligned(16))) AmTile<C, NVP> s_t;
     __shared__ float s_acc[ADJ_MFMA_G * NV];
     __shared__ uint16_t s_perm[ADJ_MFMA_G];         // Gaussians in class order
     __shared__ uint16_t s_tlist[ADJ_MFMA_G];        // those that reach the tile
@@ -303,15 +303,25 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
             // the previous sub-tile's counters, used again two sub-tiles from now
             if (tid == 0) s_cnt[prev] = s_dcnt[prev] = s_next[prev] = 0;
             if (cnt + dcnt == 0) continue;  // uniform
-            const int et = __builtin_amdgcn_readfirstlane(S.gexp[sub]);
+            // exponents of the wavelengths' Gs (-1000: all zero) and the largest of them
+            int et[C], etm = -1000;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                et[c] = __builtin_amdgcn_readfirstlane(S.gexp[sub * C + c]);
+                etm = max(etm, et[c]);
+            }
             {
                 const float2 *gs = S.gpack + (int64_t)sub * C * 256;
                 const int tv = here_v(tid);
                 for (int i = tv; i < C * 128; i += AM_T) {
                     const int c = i >> 7, u = i & 15, vp = (i >> 4) & 7;
+                    int e = et[0];
+#pragma unroll
+                    for (int q = 1; q < C; ++q) e = c == q ? et[q] : e;
+                    const int ng = AM_GS - e;
                     const float2_t p = load2(gs + c * 256 + 32 * vp + u), p2 = load2(gs + c * 256 + 32 * vp + 16 + u);
-                    float r0 = ldexpf(p.x, AM_GS - et), i0 = ldexpf(p.y, AM_GS - et);
-                    float r1 = ldexpf(p2.x, AM_GS - et), i1 = ldexpf(p2.y, AM_GS - et);
+                    float r0 = ldexpf(p.x, ng), i0 = ldexpf(p.y, ng);
+                    float r1 = ldexpf(p2.x, ng), i1 = ldexpf(p2.y, ng);
                     const float w0 = ((float)(2 * vp) - 7.5f) * (1.0f / 7.5f), w1 = ((float)(2 * vp) - 6.5f) * (1.0f / 7.5f);
                     const int at = (u + 16 * (vp >> 1)) * 4 + (vp & 1);
 #pragma unroll
@@ -327,6 +337,15 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
                         r1 *= w1;
                         i1 *= w1;
                     }
+                }
+                if (tv < NVP) {
+                    // sums of one wavelength have its exponent, those over all the largest
+                    const int c = tv < C ? tv : (DEPTH && tv >= C + 5 ? (tv - 5) % C : C);
+                    int e = etm;
+#pragma unroll
+                    for (int q = 0; q < C; ++q) e = c == q ? et[q] : e;
+                    s_t.ex[tv] = e - AM_GS - AM_YS;
+                    if (tv < C) s_t.rel[tv] = e - etm;
                 }
                 for (int i = tv; i < C * AS_C; i += AM_T) (&s_t.geo[0][0])[i] = srow[AS_HEAD + i];
                 if (dcnt) {
@@ -408,7 +427,11 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
                     }
                     const uint32_t w01 = half_pair(u0 * (1.0f / 7.5f), (u0 + 1.0f) * (1.0f / 7.5f)),
                                    w23 = half_pair((u0 + 2.0f) * (1.0f / 7.5f), (u0 + 3.0f) * (1.0f / 7.5f));
-                    const float am[4] = {amv.x, amv.y, amv.z, amv.w};
+                    // Gs_c is held on its own scale: the sums over wavelengths take it on the largest's
+                    float am[4] = {amv.x, amv.y, amv.z, amv.w};
+                    if constexpr (C > 1)
+#pragma unroll
+                        for (int c = 0; c < C; ++c) am[c] = ldexpf(am[c], s_t.rel[c]);
                     float R0[4], I0[4], R1[4], I1[4], R2[4];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) R0[j] = I0[j] = R1[j] = I1[j] = R2[j] = 0.0f;
@@ -571,12 +594,13 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
                         const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[i]), __float_as_uint(x[i + NVP / 2]), false, false);
                         x[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
                     }
+                    const int v0 = (NVP / 4) * (here_v(lane) >> 4);
 #pragma unroll
                     for (int i = 0; i < NVP / 4; ++i) {
                         const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[i]), __float_as_uint(x[i + NVP / 4]), false, false);
                         x[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-                        const int v = (NVP / 4) * g + i;
-                        if (on && v < NV) atomicAdd(&s_acc[o * NV + v], ldexpf(x[i], et - AM_GS - AM_YS));  // ds_add_f32, no return
+                        const int v = v0 + i;
+                        if (on && v < NV) atomicAdd(&s_acc[o * NV + v], ldexpf(x[i], s_t.ex[v]));  // ds_add_f32, no return
                     }
                 } else {
                     // term by term: lane l takes column l % 16 and rows l / 16 + 4 f

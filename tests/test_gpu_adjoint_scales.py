@@ -62,3 +62,25 @@ def test_smallest_field_gradients(ctx, scale):
         e = rel_l2(got, ref)
         print("  %g %s %.2e (%.2e)" % (scale, k, e, tol), flush=True)
         assert e < tol, (k, e, tol)
+
+
+@pytest.mark.parametrize("ratio", [1e-3, 1e-5, 1e-6, 1e-8, 1e-12])
+@pytest.mark.parametrize("depth", [True, False])
+def test_wavelengths_of_different_strength(ctx, ratio, depth):
+    """Each wavelength's field gradient is a gradient of its own: the same bound for the amplitudes of
+    each, and, where the strong wavelengths' amplitudes vanish, for everything else."""
+    grid = Grid(1024, 1000, 8e-6, 8e-6, LAMBDAS[:3])
+    scene = gwsgen.make_scene(24, grid, 52, depth_range=(-10e-3, 10e-3))
+    scene.amplitude[:2] = 0.0
+    G = gwsgen.make_target(grid, 4243)
+    G[0] *= np.float32(math.sqrt(ratio))
+    G[2] *= np.float32(ratio)
+    worst = {}
+    for k, (got, ref) in gradients(ctx, scene, grid, G, depth).items():
+        if k == "amplitude":
+            for c in range(3):
+                worst["amplitude[%d]" % c] = rel_l2(got[c], ref[c])
+        else:
+            worst[k] = rel_l2(got, ref)
+    print("  %g: %s" % (ratio, {k: "%.1e" % v for k, v in worst.items()}), flush=True)
+    assert max(worst.values()) < TOL, worst

@@ -440,7 +440,7 @@ static BatchLayout make_batch_layout(const gws_problem *p, int S, const int64_t 
     // the matrix-core adjoint's exponents and geometry table, or the term-by-term one's propagation
     // tables
     const bool mm = adjoint_on_mfma(make_consts(p, 0));
-    B.off_gexp = take(bw * mm * sizeof(int32_t) * (size_t)S * B.geo.nreg * 4 * C);
+    B.off_gexp = take(bw * mm * sizeof(int32_t) * (size_t)S * B.geo.nreg * 4 * (C + 1));
     B.off_dpack = take(bw * sizeof(float) * (mm ? (size_t)B.geo.nreg * 4 * adj_sub_table_floats(C) : (size_t)B.pack_elems));
     B.off_d0 = take(bw * !mm * sizeof(double) * (size_t)B.geo.nreg * 2 * C);
     // the split-bf16 DFT's operand planes (both directions), when that transform is chosen
@@ -927,7 +927,7 @@ static gws_status backward_run(gws_ctx *ctx, const gws_problem *prob, int S, con
                 if (st != GWS_OK) return st;
                 HIP_CHECK(ctx, launch_bin_backward(*p, grp, p->ntiles + 1, s));
             }
-            tab.s[i] = BwdScene{B.rec,    gpack + (int64_t)i * BL.pack_elems, gexp + (int64_t)i * BL.geo.nreg * 4 * k.C,
+            tab.s[i] = BwdScene{B.rec,    gpack + (int64_t)i * BL.pack_elems, gexp + (int64_t)i * BL.geo.nreg * 4 * (k.C + 1),
                                 B.bitems, B.bpartials, B.counters, BL.n[i], P.chunk, 0};
         }
     }

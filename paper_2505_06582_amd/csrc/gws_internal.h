@@ -416,7 +416,7 @@ struct BwdScene {
     const GRec *rec;
     const float2 *gpack;  // Gs_c, polar and region-major [region][block][c][lane] (k_adjoint) or
                           // sub-tile-major [sub-tile][c][row][column] (k_adjoint_mfma)
-    const int32_t *gexp;  // per sub-tile and wavelength: largest binary exponent of Gs (k_adjoint_mfma)
+    const int32_t *gexp;  // per sub-tile: largest binary exponent of each Gs_c, spikes (k_adjoint_mfma)
     const BItem *bitems;
     float *bpartials;
     long long *counters;

@@ -52,29 +52,65 @@ static __device__ __forceinline__ int sub_index(const AdjGeom &geo, int tx, int 
     return ((ty - geo.ty_min) * 4 + s) * (2 * geo.ntx) + (tx - geo.tx_min) * 2 + h;
 }
 
-// Gs sub-tile-major (zero outside the grid) and the largest finite binary exponent per sub-tile and
-// wavelength (a faint wavelength's Gs on a strong one's scale would lose its low fp16 parts).
+// Gs sub-tile-major (zero outside the grid), the largest finite binary exponent per sub-tile and
+// wavelength (a faint wavelength's Gs on a strong one's scale would lose its low fp16 parts), and per
+// sub-tile whether a few of its frequencies stand out: a mean of the field gradient, a grating.  The
+// separable form sums moments about the sub-tile's centre, where the weight such a frequency has (zero, on
+// an axis) comes out as a difference, and fp16 pairs hold the rest on its scale: with a mean of ten times
+// the spread the gradients of 20-pixel means were 1e-4 off.  A sub-tile whose largest |Gs|^2 exceeds
+// AM_SPIKE times its mean goes term by term: a single frequency six times the others' size still
+// passes, of independent frequencies (exponential |Gs|^2) one sub-tile in 256 e^-AM_SPIKE = 6e-14 does not.
+// gexp: C exponents and that flag for each sub-tile.
+constexpr float AM_SPIKE = 36.0f;
+template <int C>
 __global__ void __launch_bounds__(256) k_adj_pack_sub(Consts k, AdjGeom geo, const float2 *__restrict__ gspec,
                                                       float2 *__restrict__ gsub, int32_t *__restrict__ gexp)
 {
-    __shared__ int s_e[4][4];
-    const int sub = blockIdx.x, t = threadIdx.x, sx = sub % (2 * geo.ntx), sy = sub / (2 * geo.ntx);
-    const int mxp = (geo.tx_min * 2 + sx) * 16 + (t & 15), myp = (geo.ty_min * 4 + sy) * 16 + (t >> 4);
+    __shared__ float s_m[C][4], s_q[C][4], s_s[C][4];  // per wavefront: largest component, largest |Gs|^2, sum of |Gs|^2
+    const int sub = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int x0 = (geo.tx_min * 2 + sub % (2 * geo.ntx)) * 16, y0 = (geo.ty_min * 4 + sub / (2 * geo.ntx)) * 16;
+    const int mxp = x0 + (t & 15), myp = y0 + (t >> 4);
     const int hx = k.nx / 2, hy = k.ny / 2;
     const bool in = mxp >= -hx && mxp < hx && myp >= -hy && myp < hy;
     const int mx = mxp < 0 ? mxp + k.nx : mxp, my = myp < 0 ? myp + k.ny : myp;
-    for (int c = 0; c < k.C; ++c) {
-        float2 v = make_float2(0.0f, 0.0f);
-        if (in) v = gspec[((int64_t)c * k.ny + my) * k.nx + mx];
-        const float m = fmaxf(fabsf(v.x), fabsf(v.y));
-        int e = -1000;
-        if (m > 0.0f && m <= 3.4028234663852886e38f) e = ilogbf(m);
-        for (int d = 32; d >= 1; d >>= 1) e = max(e, __shfl_xor(e, d));
-        if ((t & 63) == 0) s_e[c][t >> 6] = e;
-        gsub[((int64_t)sub * k.C + c) * 256 + t] = v;
+    float2 v[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) v[c] = in ? gspec[((int64_t)c * k.ny + my) * k.nx + mx] : make_float2(0.0f, 0.0f);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        gsub[((int64_t)sub * C + c) * 256 + t] = v[c];
+        float m = fmaxf(fabsf(v[c].x), fabsf(v[c].y));
+        if (!(m <= 3.4028234663852886e38f)) m = 0.0f;
+        for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
+        if (lane == 0) s_m[c][wave] = m;
     }
     __syncthreads();
-    if (t < k.C) gexp[sub * k.C + t] = max(max(s_e[t][0], s_e[t][1]), max(s_e[t][2], s_e[t][3]));
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const float m = fmaxf(fmaxf(s_m[c][0], s_m[c][1]), fmaxf(s_m[c][2], s_m[c][3]));
+        const int e = m > 0.0f ? ilogbf(m) : -1000;
+        if (t == 0) gexp[(int64_t)sub * (C + 1) + c] = e;
+        const float x = ldexpf(v[c].x, -e), y = ldexpf(v[c].y, -e), q = fmaf(x, x, y * y);
+        float qm = q, qs = q;
+        for (int d = 32; d >= 1; d >>= 1) {
+            qm = fmaxf(qm, __shfl_xor(qm, d));
+            qs += __shfl_xor(qs, d);
+        }
+        if (lane == 0) {
+            s_q[c][wave] = qm;
+            s_s[c][wave] = qs;
+        }
+    }
+    __syncthreads();
+    if (t == 0) {
+        const float count = (float)((min(x0 + 16, hx) - max(x0, -hx)) * (min(y0 + 16, hy) - max(y0, -hy)));  // on the grid
+        bool spike = false;
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            spike |= fmaxf(fmaxf(s_q[c][0], s_q[c][1]), fmaxf(s_q[c][2], s_q[c][3])) * count >
+                     AM_SPIKE * ((s_s[c][0] + s_s[c][1]) + (s_s[c][2] + s_s[c][3]));
+        gexp[(int64_t)sub * (C + 1) + C] = spike;
+    }
 }
 
 // Geometry of a sub-tile, the same for every scene (float words of its row of the table): the
@@ -132,9 +168,18 @@ hipError_t launch_adj_pack_sub(const Consts &k, const AdjGeom &geo, int n_scenes
     const int nsub = 4 * geo.nreg;
     const int64_t M = (int64_t)k.nx * k.ny * k.C, per = (int64_t)nsub * k.C * 256;
     hipLaunchKernelGGL(k_adj_sub_geo, dim3(nsub), dim3(128), 0, s, k, geo, table);
+#define GWS_PACK(CC)                                                                                              \
+    hipLaunchKernelGGL(k_adj_pack_sub<CC>, dim3(nsub), dim3(256), 0, s, k, geo, gspecs + (int64_t)i * M,                \
+                       gsub + (int64_t)i * per, gexp + (int64_t)i * nsub * (CC + 1))
     for (int i = 0; i < n_scenes; ++i)
-        hipLaunchKernelGGL(k_adj_pack_sub, dim3(nsub), dim3(256), 0, s, k, geo, gspecs + (int64_t)i * M,
-                           gsub + (int64_t)i * per, gexp + (int64_t)i * nsub * k.C);
+        switch (k.C) {
+        case 1: GWS_PACK(1); break;
+        case 2: GWS_PACK(2); break;
+        case 3: GWS_PACK(3); break;
+        case 4: GWS_PACK(4); break;
+        default: return hipErrorInvalidValue;
+        }
+#undef GWS_PACK
     return hipGetLastError();
 }
 
@@ -262,7 +307,9 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
             {
                 int sx = sx0, sy = sy0;
                 asm volatile("" : "+s"(sx), "+s"(sy));
-                const float zlim = srow[0], phimax = srow[1];
+                const float phimax = srow[1];
+                const bool spike = S.gexp[sub * (C + 1) + C] != 0;
+                const float zlim = spike ? -1.0f : srow[0];  // |z| beyond it: term by term
                 const float x0 = (float)max(sx, -hx) - mrxf, x1 = (float)min(sx + 15, hx - 1) - mrxf;
                 const float y0 = (float)max(sy, -hy) - mryf, y1 = (float)min(sy + 15, hy - 1) - mryf;
                 const float xe = (float)sx + 7.5f - mrxf, ye = (float)sy + 7.5f - mryf;
@@ -307,7 +354,7 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
             int et[C], etm = -1000;
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                et[c] = __builtin_amdgcn_readfirstlane(S.gexp[sub * C + c]);
+                et[c] = __builtin_amdgcn_readfirstlane(S.gexp[sub * (C + 1) + c]);
                 etm = max(etm, et[c]);
             }
             {

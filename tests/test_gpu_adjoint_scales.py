@@ -84,3 +84,25 @@ def test_wavelengths_of_different_strength(ctx, ratio, depth):
             worst[k] = rel_l2(got, ref)
     print("  %g: %s" % (ratio, {k: "%.1e" % v for k, v in worst.items()}), flush=True)
     assert max(worst.values()) < TOL, worst
+
+
+def plane(grid, kx, ky):
+    """exp(j 2 pi (kx x / W + ky y / H)) on the pixels, x measured from the centre pixel."""
+    x, y = np.arange(grid.nx) - grid.nx // 2, np.arange(grid.ny) - grid.ny // 2
+    return np.exp(2j * math.pi * ky * y / grid.ny)[:, None] * np.exp(2j * math.pi * kx * x / grid.nx)[None, :]
+
+
+@pytest.mark.parametrize("waves", [[(0, 0, 1)], [(0, 0, 10)], [(0, 0, 100)], [(3, 0, 10), (-3, 0, 10)], [(0, 5, 10), (0, -5, 10)],
+                                   [(0, 0, 10), (1, 0, 5), (-1, 0, 5), (0, 1, 5), (0, -1, 5)], [(-40, 0, 10), (0, 70, 10)]])
+def test_mean_and_gratings(ctx, waves):
+    """Field gradients of unit spread with plane waves of the given amplitudes: the waves on an axis add
+    nothing to that axis' moments, so those keep the accuracy of the rest."""
+    grid = Grid(1920, 1080, 8e-6, 8e-6, LAMBDAS[:1])
+    sigma = (20.0, 20.0) if len(waves) == 1 else (2.0, 20.0)
+    scene = gwsgen.make_scene(16, grid, 53, depth_range=(-10e-3, 10e-3), sigma_px=sigma)
+    G = gwsgen.make_target(grid, 4244).astype(np.complex128)
+    for kx, ky, a in waves:
+        G += a * plane(grid, kx, ky)
+    worst = {k: rel_l2(got, ref) for k, (got, ref) in gradients(ctx, scene, grid, G).items()}
+    print("  %s: %s" % (waves, {k: "%.1e" % v for k, v in worst.items()}), flush=True)
+    assert max(worst.values()) < TOL, worst

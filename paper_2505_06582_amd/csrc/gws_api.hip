@@ -928,7 +928,7 @@ static gws_status backward_run(gws_ctx *ctx, const gws_problem *prob, int S, con
                 HIP_CHECK(ctx, launch_bin_backward(*p, grp, p->ntiles + 1, s));
             }
             tab.s[i] = BwdScene{B.rec,    gpack + (int64_t)i * BL.pack_elems, gexp + (int64_t)i * BL.geo.nreg * 4 * (k.C + 1),
-                                B.bitems, B.bpartials, B.counters, BL.n[i], P.chunk, 0};
+                                B.bitems, B.bpartials, B.counters, (int32_t)BL.n[i], P.chunk};
         }
     }
     {

@@ -420,8 +420,8 @@ struct BwdScene {
     const BItem *bitems;
     float *bpartials;
     long long *counters;
-    int64_t n;
-    int32_t chunk, pad;   // Gaussians per item
+    int32_t n;            // below 2^31
+    int32_t chunk;        // Gaussians per item
 };
 
 struct FwdTab {
@@ -434,6 +434,9 @@ struct BwdTab {
     int32_t pad;
     BwdScene s[MAX_SCENES];
 };
+// The tables and scene groups go to their kernels by value: with the other arguments within the 4 KB that
+// a launch may always pass.
+static_assert(sizeof(FwdTab) <= 4000 && sizeof(BwdTab) <= 4000 && sizeof(PrepGroup) <= 3700, "kernel arguments beyond 4 KB");
 
 // Scalar problem constants passed by value to kernels.
 struct Consts {

@@ -106,3 +106,18 @@ def test_mean_and_gratings(ctx, waves):
     worst = {k: rel_l2(got, ref) for k, (got, ref) in gradients(ctx, scene, grid, G).items()}
     print("  %s: %s" % (waves, {k: "%.1e" % v for k, v in worst.items()}), flush=True)
     assert max(worst.values()) < TOL, worst
+
+
+def test_largest_batch_equals_one_call_per_scene(ctx):
+    """64 scenes, the most one call takes: the whole scene table."""
+    import torch
+    grid = Grid(1024, 1000, 8e-6, 8e-6, LAMBDAS[:1])
+    scenes = [gwsgen.make_scene(1 + i % 4, grid, 700 + i) for i in range(64)]
+    offsets = np.concatenate([[0], np.cumsum([s.n for s in scenes])]).tolist()
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    G = torch.randn((64, 1, grid.ny, grid.nx), dtype=torch.complex64, device="cuda", generator=gen)
+    batch = ctx.backward_batched(problem(grid), scene_to_torch(gwsgen.Scene.concat(scenes)), offsets, G)
+    for s in (0, 1, 30, 62, 63):
+        one = ctx.backward(problem(grid), scene_to_torch(scenes[s]), G[s].contiguous())
+        for k, v in one.items():
+            assert torch.equal(v, batch[k][..., offsets[s]:offsets[s + 1]]), (s, k)

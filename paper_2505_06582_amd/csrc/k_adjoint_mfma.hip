@@ -475,10 +475,7 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
                     const uint32_t w01 = half_pair(u0 * (1.0f / 7.5f), (u0 + 1.0f) * (1.0f / 7.5f)),
                                    w23 = half_pair((u0 + 2.0f) * (1.0f / 7.5f), (u0 + 3.0f) * (1.0f / 7.5f));
                     // Gs_c is held on its own scale: the sums over wavelengths take it on the largest's
-                    float am[4] = {amv.x, amv.y, amv.z, amv.w};
-                    if constexpr (C > 1)
-#pragma unroll
-                        for (int c = 0; c < C; ++c) am[c] = ldexpf(am[c], s_t.rel[c]);
+                    const float am[4] = {amv.x, amv.y, amv.z, amv.w};
                     float R0[4], I0[4], R1[4], I1[4], R2[4];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) R0[j] = I0[j] = R1[j] = I1[j] = R2[j] = 0.0f;
@@ -586,11 +583,12 @@ __global__ void __launch_bounds__(AM_T, DEPTH || C > 3 ? 2 : 3)
                             }
                         }
                         const float4_t gx = *reinterpret_cast<const float4_t *>(&s_t.geo[c][4 * g]);
+                        const float amc = C > 1 ? ldexpf(am[c], s_t.rel[c]) : am[c];
 #pragma unroll
                         for (int j = 0; j < 4; ++j) {
                             const float th = fmaf(-z, gx[j], base[c] - tx[j]);
                             const float Xr = Ex[j] * __builtin_amdgcn_cosf(th), Xi = Ex[j] * __builtin_amdgcn_sinf(th);
-                            const float ar = am[c] * Xr, ai = am[c] * Xi;
+                            const float ar = amc * Xr, ai = amc * Xi;
                             x[c] = fmaf(-Xi, z0i[j], fmaf(Xr, z0r[j], x[c]));
                             if constexpr (DEPTH) {
                                 const float p0i = fmaf(Xr, z0i[j], Xi * z0r[j]), p1i = fmaf(Xr, z1i[j], Xi * z1r[j]);

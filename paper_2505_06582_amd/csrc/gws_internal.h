@@ -76,10 +76,10 @@ struct AdjGeom {
 // rectangle that does not hold the origin its minimum lies on an edge, where q is a 1-D
 // parabola: the test below is exact (up to FP32 rounding).  ia = 1/(2a), ig = 1/(2g).
 // ---------------------------------------------------------------------------------
-__device__ __forceinline__ float ellipse_min_q(float a, float b2, float g, float ia, float ig, float x0, float x1,
-                                               float y0, float y1)
+// The smallest q on the rectangle's edges.
+__device__ __forceinline__ float ellipse_edge_min(float a, float b2, float g, float ia, float ig, float x0, float x1,
+                                                  float y0, float y1)
 {
-    if (x0 <= 0.0f && x1 >= 0.0f && y0 <= 0.0f && y1 >= 0.0f) return 0.0f;
     float m;
     float y = fminf(fmaxf(-b2 * x0 * ig, y0), y1);
     m = x0 * (a * x0 + b2 * y) + g * y * y;
@@ -92,10 +92,19 @@ __device__ __forceinline__ float ellipse_min_q(float a, float b2, float g, float
     return m;
 }
 
+// The smallest q on the rectangle.
+__device__ __forceinline__ float ellipse_min_q(float a, float b2, float g, float ia, float ig, float x0, float x1,
+                                               float y0, float y1)
+{
+    if (x0 <= 0.0f && x1 >= 0.0f && y0 <= 0.0f && y1 >= 0.0f) return 0.0f;
+    return ellipse_edge_min(a, b2, g, ia, ig, x0, x1, y0, y1);
+}
+
 __device__ __forceinline__ bool ellipse_meets_rect_r(float a, float b2, float g, float ia, float ig, float lim,
                                                      float x0, float x1, float y0, float y1)
 {
-    return ellipse_min_q(a, b2, g, ia, ig, x0, x1, y0, y1) <= lim;
+    if (x0 <= 0.0f && x1 >= 0.0f && y0 <= 0.0f && y1 >= 0.0f) return true;
+    return ellipse_edge_min(a, b2, g, ia, ig, x0, x1, y0, y1) <= lim;
 }
 
 // Bit f is set when the support meets the 4-row block f of a sub-tile: columns [x0, x1],

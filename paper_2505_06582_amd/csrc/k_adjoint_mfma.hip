@@ -57,16 +57,17 @@ static __device__ __forceinline__ int sub_index(const AdjGeom &geo, int tx, int 
 // sub-tile whether a few of its frequencies stand out: a mean of the field gradient, a grating.  The
 // separable form sums moments about the sub-tile's centre, where the weight such a frequency has (zero, on
 // an axis) comes out as a difference, and fp16 pairs hold the rest on its scale: with a mean of ten times
-// the spread the gradients of 20-pixel means were 1e-4 off.  A sub-tile whose largest |Gs|^2 exceeds
-// AM_SPIKE times its mean goes term by term: a single frequency six times the others' size still
-// passes, of independent frequencies (exponential |Gs|^2) one sub-tile in 256 e^-AM_SPIKE = 6e-14 does not.
+// the spread the gradients of 20-pixel means were 1e-4 off.  A sub-tile whose largest component of Gs
+// has a square above AM_SPIKE times the mean |Gs|^2 goes term by term: a single frequency five times
+// the others' size still passes; of independent normal components 512 erfc(5) = 8e-10 of the
+// sub-tiles do not.
 // gexp: C exponents and that flag for each sub-tile.
-constexpr float AM_SPIKE = 36.0f;
+constexpr float AM_SPIKE = 25.0f;
 template <int C>
 __global__ void __launch_bounds__(256) k_adj_pack_sub(Consts k, AdjGeom geo, const float2 *__restrict__ gspec,
                                                       float2 *__restrict__ gsub, int32_t *__restrict__ gexp)
 {
-    __shared__ float s_m[C][4], s_q[C][4], s_s[C][4];  // per wavefront: largest component, largest |Gs|^2, sum of |Gs|^2
+    __shared__ float s_m[C][4], s_s[C][4];  // per wavefront: largest component, sum of |Gs|^2
     const int sub = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int x0 = (geo.tx_min * 2 + sub % (2 * geo.ntx)) * 16, y0 = (geo.ty_min * 4 + sub / (2 * geo.ntx)) * 16;
     const int mxp = x0 + (t & 15), myp = y0 + (t >> 4);
@@ -85,21 +86,17 @@ __global__ void __launch_bounds__(256) k_adj_pack_sub(Consts k, AdjGeom geo, con
         if (lane == 0) s_m[c][wave] = m;
     }
     __syncthreads();
+    float top[C];  // the largest component, 1 ... 2 on its own scale
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const float m = fmaxf(fmaxf(s_m[c][0], s_m[c][1]), fmaxf(s_m[c][2], s_m[c][3]));
         const int e = m > 0.0f ? ilogbf(m) : -1000;
         if (t == 0) gexp[(int64_t)sub * (C + 1) + c] = e;
-        const float x = ldexpf(v[c].x, -e), y = ldexpf(v[c].y, -e), q = fmaf(x, x, y * y);
-        float qm = q, qs = q;
-        for (int d = 32; d >= 1; d >>= 1) {
-            qm = fmaxf(qm, __shfl_xor(qm, d));
-            qs += __shfl_xor(qs, d);
-        }
-        if (lane == 0) {
-            s_q[c][wave] = qm;
-            s_s[c][wave] = qs;
-        }
+        top[c] = ldexpf(m, -e);
+        const float x = ldexpf(v[c].x, -e), y = ldexpf(v[c].y, -e);
+        float q = fmaf(x, x, y * y);
+        for (int d = 32; d >= 1; d >>= 1) q += __shfl_xor(q, d);
+        if (lane == 0) s_s[c][wave] = q;
     }
     __syncthreads();
     if (t == 0) {
@@ -107,8 +104,7 @@ __global__ void __launch_bounds__(256) k_adj_pack_sub(Consts k, AdjGeom geo, con
         bool spike = false;
 #pragma unroll
         for (int c = 0; c < C; ++c)
-            spike |= fmaxf(fmaxf(s_q[c][0], s_q[c][1]), fmaxf(s_q[c][2], s_q[c][3])) * count >
-                     AM_SPIKE * ((s_s[c][0] + s_s[c][1]) + (s_s[c][2] + s_s[c][3]));
+            spike |= top[c] * top[c] * count > AM_SPIKE * ((s_s[c][0] + s_s[c][1]) + (s_s[c][2] + s_s[c][3]));
         gexp[(int64_t)sub * (C + 1) + C] = spike;
     }
 }

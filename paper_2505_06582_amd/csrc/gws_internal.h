@@ -158,7 +158,6 @@ static __device__ __forceinline__ int next_item(bool first, long long *queue)
     return first ? (int)blockIdx.x : (int)gridDim.x + (int)atomicAdd((unsigned long long *)queue, 1ull);
 }
 
-// Sum of a 64-bit counter over the 64 lanes of a wavefront (every lane gets the total).
 // Transposed butterfly reduction of V (8 or 16) per-lane values over the 64 lanes of a
 // wavefront.  Each transposed step pairs value i with value i + h and lane l with lane
 // l ^ d: the lane with the d bit clear keeps and sums the first value of the pair, its
@@ -293,6 +292,7 @@ static __device__ __forceinline__ void reduce_into(float (&x)[NV], float *acc, i
     }
 }
 
+// Sum of a 64-bit counter over the 64 lanes of a wavefront (every lane gets the total).
 __device__ __forceinline__ long long wave_sum_i64(long long v)
 {
 #pragma unroll
@@ -486,7 +486,7 @@ struct Layout {
     size_t total = 0;
     size_t off_keys_a, off_keys_b, off_vals_a, off_vals_b, off_sort_hist, off_bucket_end, off_cum;
     size_t off_counters, off_records, off_tile_L, off_tile_slots, off_items, off_range_base, off_bitems, off_partials, off_bpartials;
-    size_t off_spectrum, off_gspec, off_dtab, off_d0tab, off_chunk_items;
+    size_t off_chunk_items;
     int32_t nsx = 0, nsy = 0, sx_min = 0, sy_min = 0, F = 4;
     int64_t n = 0;
     int64_t max_items = 0, max_slots = 0, max_bitems = 0, max_bslots = 0;

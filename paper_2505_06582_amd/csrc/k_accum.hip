@@ -334,14 +334,15 @@ bool grid_has_evanescent(const Consts &k)
 }
 
 // Which accumulation runs.  The matrix-core one is laid out for 16-row sub-tiles (F = 4) and needs
-// every grid frequency to propagate.  It sums in another order and rounds other intermediate
-// values (5e-7 of the field), so a double-precision loss of the field moves by 1e-8.  Grids
-// up to 2048 x 2048 points, on which scenes are optimised and such losses recorded, keep this
-// kernel and its bits, although the matrix-core one is the faster from 1000 x 750 on: 500 / 5000 /
-// 50000 Gaussians of 2-20 pixels at three wavelengths, this kernel against the matrix cores
-// (ms): 1000 x 750 0.224 / 0.424 / 2.08 against 0.216 / 0.394 / 1.45, 1920 x 1080 0.339 / 0.820 / 4.53
-// against 0.315 / 0.551 / 2.75.  Above, the time is the larger matter (1e6 at 3840 x 2160: 304 ms
-// against 119) and the matrix-core sum also the closer one (4.5e-6 against 1.4e-6).
+// every grid frequency to propagate.  The line at 2048 x 2048 points is not where it becomes
+// the faster: that is from 1000 x 750 on (500 / 5000 / 50000 Gaussians of 2-20 pixels at three
+// wavelengths, this kernel against the matrix cores (ms): 1000 x 750 0.224 / 0.424 / 2.08 against 0.216 /
+// 0.394 / 1.45, 1920 x 1080 0.339 / 0.820 / 4.53 against 0.315 / 0.551 / 2.75).  It keeps results on
+// the smaller grids the same bits from version to version: the matrix-core sum adds in another
+// order and rounds other intermediate values (each kernel is some 5e-7 of the field from the
+// exact sum), which moves a loss summed in double precision by 1e-8.  Above the line every
+// result did change, by as little, for the time (1e6 at 3840 x 2160: 304 ms against 120) and the error
+// (4.5e-6 against 1.4e-6).
 bool accumulate_on_mfma(const Consts &k, int F)
 {
     return F == 4 && !grid_has_evanescent(k) && (int64_t)k.nx * k.ny >= (int64_t)ACC_MFMA_POINTS;

@@ -17,15 +17,17 @@
 // Orders 2 and up, small, fold u and v into their fp16 factors and share M_1.
 //
 // Precision.  Each FP32 factor is split into two fp16 numbers, both rounded to nearest
-// (x = h + l, |x - h - l| <= 2^-24 |x|, FP32's own rounding), the products h h, h l and l h are
-// accumulated in FP32 (l l is below 2^-24).  fp16's range is met by exact powers of two: the
+// (x = h + l, |x - h - l| <= 2^-23 |x| while l is a normal fp16 number, 2^-25 where it is not: below
+// |x| = 2^-2 at the latest, against a strongest factor of about 2^4), the products h h, h l and l h
+// are accumulated in FP32 (l l is at most 2^-22 of h h).  fp16's range is met by exact powers of two: the
 // running exponent e of the wavelength's largest term met so far is taken out of the factors
 // (accumulators are rescaled when it grows) and factors are kept in 2^+-15.  The polynomial is the Taylor
 // polynomial with the next two orders projected onto it by least squares over the
 // sub-tile's 256 points: relative rms error at most 1e-7 for |a| <= 0.0175, 0.08, 0.2, 0.35 with
-// 3, 4, 5, 6 coefficients.  q at the centre, its gradient and the phase base are formed in FP64
-// by the staging lane, and the ramp m . r is exact.  Field error against FP64, 10k Gaussians at
-// 1080 x 1920 x 3: 5.4e-7 (7.0e-7 term by term); spectrum of 1e6 at 2160 x 3840 x 3: 1.4e-6 (4.5e-6).
+// 3, 4, 5, 6 coefficients (2.4e-7 for one of five at |a| = 0.2 that shares a pass with six, whose
+// sixth it then takes besides its projection).  q at the centre, its gradient and the phase base are formed in FP64
+// by the staging lane, and the ramp m . r is exact.  Spectrum error against FP64, 40 Gaussians at
+// 2400 x 1800 x 2: 3.4e-7 (6.0e-7 term by term); 1e6 at 2160 x 3840 x 3: 1.4e-6 (4.5e-6).
 //
 // A Gaussian that fails a test on a sub-tile (a too large, a steep envelope, a deep Gaussian
 // where k_z curves fast, a nearly singular covariance, non-finite amplitude) is evaluated term by term into the same
@@ -38,10 +40,11 @@
 // are formed in the lanes that feed them, with no exchange between lanes.  One pass takes 16
 // Gaussians; what does not fill a pass stays in the wavefront's list for the next batch.
 //
-// Bound now: VALU issue (85 % busy; the matrix units a quarter), 45 VALU instructions per
+// Bound now: VALU issue (91 % of the busy cycles; the matrix units 23 %), 41 VALU instructions per
 // (Gaussian, sub-tile) at three wavelengths, a fifth of them staging, against 146 term by
-// term.  Forward of 1e5 Gaussians at 1080 x 1920 x 3: 8.6 -> 4.6 ms; 1e6 at 2160 x 3840 x 3: 304 ->
-// 119 ms.  Three wavefronts per SIMD without spills: with accumulators for t^2 too, 4.9 ms.
+// term.  Forward of 1e6 at 2160 x 3840 x 3: 304 -> 120 ms; 3e5 at one wavelength 15.5 ms.  Three
+// wavefronts per SIMD with seven registers spilt, outside the passes; accumulators for t^2 too
+// would spill inside them.
 #include "mfma_f16.h"
 
 namespace gws {
@@ -52,7 +55,7 @@ constexpr int MM_SLOTS = 96;             // a wavefront's list: up to 15 entries
 constexpr int MM_XS = 4, MM_YS = 5;      // powers of two carried by X and Y (kept inside fp16's normal range)
 constexpr int MM_E_NONE = -100000;       // so far only zeros, which any power of two leaves
 constexpr int MM_SLACK = 80;             // powers of two by which a term-by-term term may exceed the running exponent
-constexpr int MM_EMIT = 32;              // passes after which the accumulators move to the output
+constexpr int MM_EMIT = 32;              // passes after which a round's end moves the accumulators to the output
 
 // An entry of a wavefront's list, 12 + 4 C floats.  Separable: lx, alpha, ly, gamma | r_x's upper
 // 20 bits and the rest, r_y's | c1, 8 c2 / P, 8 c3 / c2 / P, 8 c4 / c3 / P | per wavelength base, A,
@@ -200,7 +203,8 @@ static __device__ __forceinline__ void mm_pass(const float (&ent)[MM_SLOTS][mm_f
     }
 }
 
-// Wavefronts per SIMD the kernel is compiled for.
+// Wavefronts per SIMD the kernel is compiled for (one wavelength: 3e5 Gaussians at 2160 x 3840 with four
+// 15.5 ms, with three 16.7).
 __host__ __device__ constexpr int mm_waves(int c) { return c == 1 ? 4 : c <= 3 ? 3 : 2; }
 
 // Work items, tile order, chunks and partial-sum slots are k_accumulate's (F = 4).  Uniform values
@@ -564,8 +568,8 @@ __global__ void __launch_bounds__(WG, mm_waves(C)) k_accumulate_mfma(Consts k, c
                 kept = 0;
             }
             // S = M_0 + t M_1 at the lane's four frequencies.  The matrix units' running FP32 sums round
-            // less well than single additions, so about every 500 Gaussians they move to the output
-            // and are added there (one sum over 1e5 Gaussians at 2160 x 3840 was 1.2e-5 off; it is
+            // less well than single additions, so after 500 Gaussians or more (looked at after a round of
+            // candidates: 1500 at most) they move to the output and are added there (one sum over 1e5 Gaussians at 2160 x 3840 was 1.2e-5 off; it is
             // 1.4e-6 off this way, 4.5e-6 term by term).
             if (npass >= MM_EMIT || last) {
                 int sx = sx0, sy = sy0, cl = col, rw = row0;

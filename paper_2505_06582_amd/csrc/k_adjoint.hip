@@ -420,11 +420,13 @@ __global__ void __launch_bounds__(adj_wg(C, DEPTH), adj_waves_per_simd(C, DEPTH)
 }
 
 // Which adjoint runs.  The matrix-core one needs every grid frequency to propagate; on smaller grids
-// supports cover few sub-tiles and more Gaussians fail the separable form's tests.  Backward,
-// this kernel against the matrix-core one, 300 / 3000 / 30000 Gaussians (ms): 1000 x 750, one
-// wavelength 0.12 / 0.24 / 0.93 against 0.16 / 0.28 / 0.80; 1280 x 800 0.156 / 0.27 / 1.14 against 0.151 /
-// 0.25 / 0.91, three wavelengths 0.21 / 0.46 / 2.13 against 0.22 / 0.39 / 1.51; 1920 x 1080, three 0.36 /
-// 0.70 / 3.99 against 0.30 / 0.58 / 2.49.
+// supports cover few sub-tiles and more Gaussians fail the separable form's tests.  The line goes by
+// the grid alone, although the count moves it a little (at 1000 x 750 the matrix cores win with 30000
+// Gaussians, at 1280 x 800 x 3 they lose 5 % with 300): a batch's scenes, of any counts, share a
+// launch and its tables.  Backward, this kernel against the matrix-core one, 300 / 3000 / 30000
+// Gaussians (ms): 1000 x 750, one wavelength 0.12 / 0.24 / 0.93 against 0.16 / 0.28 / 0.80; 1280 x 800
+// 0.156 / 0.27 / 1.14 against 0.151 / 0.25 / 0.91, three wavelengths 0.21 / 0.46 / 2.13 against 0.22 / 0.39 /
+// 1.51; 1920 x 1080, three 0.36 / 0.70 / 3.99 against 0.30 / 0.58 / 2.49.
 bool adjoint_on_mfma(const Consts &k)
 {
     return !grid_has_evanescent(k) && (int64_t)k.nx * k.ny >= (int64_t)ADJ_MFMA_POINTS;

@@ -22,14 +22,15 @@
 // Gaussian l % 16, evaluates X at columns 4 (l / 16) + j and Y at rows 4 (l / 16) + j (the
 // layouts of the result and of B), and the sums over the four lane groups go to the Gaussian's
 // LDS accumulators.  Every Gaussian is visited once per sub-tile, so the order of its sums is
-// fixed.  Gaussians that fail the separable form's tests there are evaluated term by term.
+// fixed.  Gaussians that fail the separable form's tests there, and all of them where a few frequencies
+// of Gs stand out, are evaluated term by term.
 //
-// Bound: VALU issue (75 % busy), 77 VALU instructions per (Gaussian, sub-tile) at three
-// wavelengths against 212 term by term: about 50 evaluate and combine, the rest test the
-// Gaussians and build the operands, once per sub-tile.  1e5 Gaussians at 1080 x 1920 x 3: 11.6 ->
-// 6.9 ms.  Three wavefronts per SIMD (two: 8.6 ms for the backward instead of 7.6), which the
-// opaque copies of indices make possible.  Gradients against FP64, 1000 Gaussians at
-// 1080 x 1920 x 3: 2.5e-7 ... 5.7e-7 (3.4e-7 ... 1.7e-6 term by term).
+// Bound: VALU issue (80 % of the busy cycles, the matrix units 21 %), 74 VALU instructions per
+// (Gaussian, sub-tile) at three wavelengths against 212 term by term: about 50 evaluate and combine,
+// the rest test the Gaussians and build the operands, once per sub-tile.  1e5 Gaussians at
+// 1080 x 1920 x 3: 11.7 -> 7.1 ms.  Three wavefronts per SIMD (two: 8.6 ms for the backward instead of
+// 7.6), which the opaque copies of indices make possible.  Gradients against FP64, 1000 Gaussians at
+// 1080 x 1920 x 3: 2.2e-7 ... 6.8e-7 (3.4e-7 ... 1.7e-6 term by term).
 #include "mfma_f16.h"
 
 namespace gws {

@@ -10,7 +10,7 @@
 //   C[q] = sum_m e[m] cos(2 pi m q / L),  S[q] = sum_m o[m] sin(2 pi m q / L),  m, q = 0 ... L / 2,
 //   X_p[q] = C[q] +- j S[q],  X_p[L - q] = C[q] -+ j S[q].
 // That leaves 1 / (4 R) of the complex products with the whole matrix F[m][n] = w_N^(m n), which
-// bound the transform before (matrix units at 54 %): 3840 x 2160 x 3 took 3.08 ms, 0.76 now, of
+// bound the transform before (matrix units at 54 %): 3840 x 2160 x 3 took 3.08 ms, 0.73 now, of
 // which the two folds' memory passes are 0.23; 1920 x 1080 x 3 0.55 -> 0.16, 256 x 256 0.058 -> 0.028.
 // R = 1 with larger tiles: 2.5 ms.  Error against FP64 as before, 5.3e-6 (5.5e-6).
 //

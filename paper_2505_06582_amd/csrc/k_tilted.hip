@@ -1009,8 +1009,8 @@ static hipError_t launch_tilt_adjoint_c(const Consts &k, const TRec *rec, const 
         nb = 1;
     // Each tile's Gaussians split into parts taken as separate items (each (Gaussian, tile) slot is
     // still written once, with the same bits), so the tiles many supports reach do not hold the
-    // launch's tail: eight items per resident work-group, of 512 Gaussians at least (building the
-    // tile's tables costs as much as four Gaussians' sums over it).  Backward of 12000 at 640 x 480 x 3:
+    // launch's tail: eight items per resident work-group, but no more parts than one per 512 Gaussians
+    // (building the tile's tables costs as much as four Gaussians' sums over it).  Backward of 12000 at 640 x 480 x 3:
     // 4.71 -> 1.11 ms (one part per 8192: 300 items), 40000 at 256 x 256 2.09 -> 0.59, 12000 at 1920 x 1080 x 3
     // 4.88 -> 4.61; four items per work-group: 10.2 ms for 40000 at 1280 x 1024 x 3, eight 9.8.
     const int tiles = ((k.nx + TT - 1) / TT) * ((k.ny + TT - 1) / TT);
